@@ -2,6 +2,7 @@
 // zeroing, FP64 reductions, bit hash and the device-side field generator.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <string.h>
 
 #include <algorithm>
 #include <mutex>
@@ -223,192 +224,241 @@ __global__ __launch_bounds__(256) void zero_interior_kernel(Dims d, T *f, int nb
 }
 
 // ---------------------------------------------------------------------------
-// FP64 reductions: pass 1 gives each of RB blocks a fixed set of rows
-// (row r = (j, k) pairs, rows b, b + RB, ...), each thread a fixed set of
-// row slots and columns; block partials are combined by a fixed LDS tree.  Pass 2 reduces
-// the RB partials in one block the same way.  No atomics, so the result is
-// bitwise reproducible.
+// Rows cut into pieces, for the kernels that stream the interior in memory
+// order (reductions, Euler update).  A piece is up to R rows of one level; a
+// row is cpr chunks of V consecutive points, the last one moved back so that
+// it ends at itot (its first `ov` points repeat the chunk before it and are
+// masked).  The loads are 16 bytes wide at element alignment, so any itot >= V
+// and any layout takes the same path.  The level is one per piece, which
+// leaves one 32-bit multiplication per chunk for the row index and one
+// metric read per piece.
 // ---------------------------------------------------------------------------
-constexpr int RB = 4096;   // pass-1 blocks
+struct RowPieces {
+    uint32_t cpr;    // chunks per row
+    uint32_t magic;  // (e * magic) >> 32 = e / cpr for e < R * cpr (0 when R = 1: row 0)
+    uint32_t ov;     // repeated points of a row's last chunk
+    uint32_t R, ng;  // rows per piece, pieces per level
+    uint32_t np;     // pieces
+};
+
+// e / cpr by multiplication with the rounded-up reciprocal is exact while
+// e * cpr < 2^32; here e < 2^14, and cpr <= 2^13 where a piece has two rows.
+RowPieces row_pieces(const HostArgs &a, int V, int64_t chunks_per_piece)
+{
+    RowPieces r;
+    r.cpr = (uint32_t)((a.itot + V - 1) / V);
+    r.ov = r.cpr * (uint32_t)V - (uint32_t)a.itot;
+    r.R = (uint32_t)std::max<int64_t>(1, std::min<int64_t>(a.jtot, std::min<int64_t>(chunks_per_piece, 1 << 14) / r.cpr));
+    r.magic = r.R == 1 ? 0u : (uint32_t)((((uint64_t)1 << 32) + r.cpr - 1) / r.cpr);
+    r.ng = ((uint32_t)a.jtot + r.R - 1) / r.R;
+    r.np = r.ng * (uint32_t)a.ktot;
+    return r;
+}
+
+// Points per 16-byte chunk, or 1 for rows narrower than that.
+inline int row_chunk(const HostArgs &a)
+{
+    const int V = a.dtype == KL_F32 ? 4 : 2;
+    return a.itot >= V ? V : 1;
+}
+
+// One chunk of a piece: its offset from the piece's first point, and the first
+// of its V points that counts (V: none, for a thread beyond the piece's end).
+template <int V>
+__device__ __forceinline__ int64_t chunk_at(const RowPieces &rp, int64_t js, uint32_t e, uint32_t n, int &lo)
+{
+    const uint32_t ec = e < n ? e : n - 1;
+    const uint32_t row = rp.cpr == 1 ? ec : __umulhi(ec, rp.magic);
+    const uint32_t c = ec - row * rp.cpr;
+    const uint32_t ov = V > 1 && c == rp.cpr - 1 ? rp.ov : 0u;
+    lo = e < n ? (int)ov : V;
+    return (int64_t)row * js + (int64_t)(c * (uint32_t)V - ov);
+}
+
+// ---------------------------------------------------------------------------
+// FP64 reductions.  Pass 1: block b of nb sums pieces b, b + nb, ...; a thread
+// takes every RT-th chunk of a piece, M in flight at a time; partials are
+// combined by a fixed tree (lanes, then waves).  Pass 2 reduces the nb
+// partials in one block the same way.  No atomics, and the mapping depends
+// only on the grid, so the result is bitwise reproducible.  The conservation
+// sums weight a level's sum once per piece.
+//
+// Bound by HBM (one read of the fields) down to about 10^7 points, below that
+// by the two launches.  1024 chunks a piece keep 12 16-byte loads in flight
+// per thread (6 for the checksums, whose nine sums need the registers) and
+// still give a 128^3 grid 512 blocks; at most RED_MAXB blocks (8 per CU) keep
+// pass 2 to a few loads per thread.  Against 4096 blocks of scattered rows, a
+// division per point and row, and a nine-value tree over LDS for both kinds:
+// 512^3 FP32 sums 351 -> 266 us (6.06 TB/s), checksums 311 -> 281 us; 128^3
+// 27 -> 12 us; 301x203x151 (one point per load before) 102 -> 24 us.
+// ---------------------------------------------------------------------------
+constexpr int RB = 4096;   // pass-1 blocks of the hash, and the scratch's partial count
 constexpr int RT = 256;    // threads per block
-constexpr int RQ = 9;      // values per partial
+constexpr int RQ = 9;      // most values per partial
+constexpr int RED_MAXB = 2048;
+constexpr int RT2 = 512;   // threads of pass 2
+static_assert(RED_MAXB <= RB, "the reductions' partials fit the scratch");
 
-__device__ __forceinline__ double comb(int q_is_max, double a, double b)
+template <int WHAT>
+struct RedShape {
+    static constexpr int NQ = WHAT == 0 ? 3 : 9;
+    static constexpr int M = WHAT == 0 ? 4 : 2;  // chunks in flight per thread
+    __device__ static constexpr bool is_max(int q) { return WHAT == 1 && q % 3 == 2; }
+};
+
+struct RedPlan {
+    RowPieces rp;
+    int nb;  // pass-1 blocks
+};
+
+RedPlan red_plan(const HostArgs &a)
 {
-    return q_is_max ? fmax(a, b) : a + b;
+    RedPlan p;
+    const int V = row_chunk(a);
+    const int64_t total = (int64_t)((a.itot + V - 1) / V) * a.jtot * a.ktot;
+    p.rp = row_pieces(a, V, std::min<int64_t>(4096, std::max<int64_t>(1024, total / RED_MAXB)));
+    p.nb = (int)std::min<uint32_t>(RED_MAXB, p.rp.np);
+    return p;
 }
 
-template <int NQ>
-__device__ void block_tree(double (&acc)[NQ], const int (&is_max)[NQ], double *out)
+// Reduce acc over the block's NT threads; thread q < NQ writes value q to
+// out[q * stride].
+template <int WHAT, int NT>
+__device__ __forceinline__ void block_tree(double (&acc)[RedShape<WHAT>::NQ], double *out, int64_t stride)
 {
-    __shared__ double sh[RT][NQ];
+    constexpr int NQ = RedShape<WHAT>::NQ, NW = NT / 64;
+    __shared__ double sh[NW][NQ];
 #pragma unroll
-    for (int q = 0; q < NQ; ++q) sh[threadIdx.x][q] = acc[q];
-    __syncthreads();
-    for (int s = RT / 2; s > 0; s >>= 1) {
-        if ((int)threadIdx.x < s) {
+    for (int s = 32; s > 0; s >>= 1)
 #pragma unroll
-            for (int q = 0; q < NQ; ++q)
-                sh[threadIdx.x][q] = comb(is_max[q], sh[threadIdx.x][q], sh[threadIdx.x + s][q]);
+        for (int q = 0; q < NQ; ++q) {
+            const double o = __shfl_down(acc[q], (unsigned)s, 64);
+            acc[q] = RedShape<WHAT>::is_max(q) ? fmax(acc[q], o) : acc[q] + o;
         }
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) {
+    const int lane = (int)threadIdx.x & 63, wave = (int)threadIdx.x >> 6;
+    if (lane == 0)
 #pragma unroll
-        for (int q = 0; q < NQ; ++q) out[q] = sh[0][q];
+        for (int q = 0; q < NQ; ++q) sh[wave][q] = acc[q];
+    __syncthreads();
+    if ((int)threadIdx.x < NQ) {
+        const int q = (int)threadIdx.x;
+        double r = sh[0][q];
+        for (int w = 1; w < NW; ++w) r = WHAT == 1 && q % 3 == 2 ? fmax(r, sh[w][q]) : r + sh[w][q];
+        out[q * stride] = r;
     }
 }
 
-// Pass 1.  Each thread reads V consecutive points of a row with one vector
-// load (V > 1 when the rows are aligned to it).  A row has cpr = itot / V
-// chunks; when a row has fewer chunks than the block has threads, a pass
-// covers rpp = RT / cpr rows at once (thread t: row slot t / cpr, chunk
-// t % cpr).  Block b owns rows b, b + RB, b + 2 RB, ...; slot s takes the
-// n-th of them for n = s, s + rpp, ...; two rows are loaded before either
-// is accumulated.  The mapping depends only on the grid, so the result is
-// the same on every run.
-template <typename T, int V>
-__device__ __forceinline__ void red_load(T (&x)[V], const T *p)
-{
-    if constexpr (V == 1) {
-        x[0] = *p;
-    } else {
-        typedef T VT __attribute__((ext_vector_type(V)));
-        const VT y = *reinterpret_cast<const VT *>(p);
-#pragma unroll
-        for (int n = 0; n < V; ++n) x[n] = y[n];
-    }
-}
-
-// Pass-1 block b of a reduction (partial + b * RQ receives its partial).
-template <typename T, int V>
-__device__ __forceinline__ void reduce_block(const Dims &d, int what, int kw0, const T *f0, const T *f1,
+// Pass-1 block b of nb; its partial value q goes to partial[q * nb + b].
+template <typename T, int V, int WHAT>
+__device__ __forceinline__ void reduce_block(const Dims &d, const RedPlan &pl, int kw0, const T *f0, const T *f1,
                                              const T *f2, const T *dzi, const T *dzhi, int b, double *partial)
 {
-    double acc[RQ];
-    int is_max[RQ];
-#pragma unroll
-    for (int q = 0; q < RQ; ++q) {
-        acc[q] = 0.0;
-        is_max[q] = (what == 1 && q % 3 == 2);
-    }
-    const int64_t nrows = (int64_t)d.jtot * d.ktot;
-    const int cpr = d.itot / V;
-    const bool wide = cpr >= RT;
-    const int rpp = wide ? 1 : RT / cpr;
-    const int slot = wide ? 0 : (int)threadIdx.x / cpr;
-    const int c0 = wide ? (int)threadIdx.x : (int)threadIdx.x % cpr;
-    const int cstep = wide ? RT : cpr;
-    const int64_t rstep = (int64_t)rpp * RB;
+    constexpr int NQ = RedShape<WHAT>::NQ;
+    const RowPieces &rp = pl.rp;
     const T *f3[3] = {f0, f1, f2};
-
-    // one row's contribution of chunk c, values already loaded
-    auto add = [&](const T (&x)[3][V], int k) {
-        if (what == 0) {
-            const double wz = 1.0 / (double)dzi[k], wzh = 1.0 / (double)dzhi[k];
+    constexpr int M = RedShape<WHAT>::M;
+    double acc[NQ];
+    T mx[3] = {T(0), T(0), T(0)};  // checksums: the largest |f| so far, exact in T
 #pragma unroll
-            for (int n = 0; n < V; ++n) {
-                acc[0] += (double)x[0][n] * wz;
-                acc[1] += (double)x[1][n] * wz;
-                if (k >= kw0) acc[2] += (double)x[2][n] * wzh;
-            }
-        } else {
+    for (int q = 0; q < NQ; ++q) acc[q] = 0.0;
+    for (uint32_t p = (uint32_t)b; p < rp.np; p += (uint32_t)pl.nb) {
+        const int k = 1 + (int)(p / rp.ng);
+        const uint32_t j0 = (p % rp.ng) * rp.R;
+        const uint32_t left = (uint32_t)d.jtot - j0;
+        const uint32_t n = (left < rp.R ? left : rp.R) * rp.cpr;
+        const int64_t base = at(d, 1, 1 + (int)j0, k);
+        double s[3] = {0.0, 0.0, 0.0};
+        for (uint32_t e0 = threadIdx.x; e0 < n; e0 += M * RT) {
+            T x[M][3][V];
+            int lo[M];
 #pragma unroll
-            for (int f = 0; f < 3; ++f) {
-                if (f3[f] == nullptr) continue;
+            for (int m = 0; m < M; ++m) {
+                const int64_t o = base + chunk_at<V>(rp, d.js, e0 + m * RT, n, lo[m]);
 #pragma unroll
-                for (int n = 0; n < V; ++n) {
-                    const double y = (double)x[f][n];
-                    acc[3 * f] += y;
-                    acc[3 * f + 1] += y * y;
-                    acc[3 * f + 2] = fmax(acc[3 * f + 2], fabs(y));
+                for (int f = 0; f < 3; ++f) {
+                    if (WHAT == 1 && f3[f] == nullptr) {
+#pragma unroll
+                        for (int i = 0; i < V; ++i) x[m][f][i] = T(0);
+                    } else {
+                        uload<T, V>(x[m][f], f3[f] + o);
+                    }
                 }
             }
-        }
-    };
-    auto load = [&](T (&x)[3][V], int64_t base) {
 #pragma unroll
-        for (int f = 0; f < 3; ++f) {
-            if (f3[f] != nullptr)
-                red_load<T, V>(x[f], f3[f] + base);
-            else
+            for (int m = 0; m < M; ++m)
 #pragma unroll
-                for (int n = 0; n < V; ++n) x[f][n] = T(0);
+                for (int f = 0; f < 3; ++f)
+#pragma unroll
+                    for (int i = 0; i < V; ++i) {
+                        const T xi = i < lo[m] ? T(0) : x[m][f][i];
+                        const double y = (double)xi;
+                        if constexpr (WHAT == 0) {
+                            s[f] += y;
+                        } else {
+                            acc[3 * f] += y;
+                            acc[3 * f + 1] = tfma(y, y, acc[3 * f + 1]);
+                            mx[f] = tmax(mx[f], tabs(xi));
+                        }
+                    }
         }
-    };
-
-    if (slot < rpp) {
-        int64_t r = (int64_t)b + (int64_t)slot * RB;
-        for (; r + rstep < nrows; r += 2 * rstep) {
-            // 32-bit row arithmetic (the launchers refuse 2^31 or more rows)
-            const uint32_t ra = (uint32_t)r, rb = (uint32_t)(r + rstep), jt = (uint32_t)d.jtot;
-            const int ja = 1 + (int)(ra % jt), ka = 1 + (int)(ra / jt);
-            const int jb = 1 + (int)(rb % jt), kb = 1 + (int)(rb / jt);
-            for (int c = c0; c < cpr; c += cstep) {
-                T xa[3][V], xb[3][V];
-                load(xa, at(d, 1 + c * V, ja, ka));
-                load(xb, at(d, 1 + c * V, jb, kb));
-                add(xa, ka);
-                add(xb, kb);
-            }
-        }
-        if (r < nrows) {
-            const uint32_t ru = (uint32_t)r, jt = (uint32_t)d.jtot;
-            const int j = 1 + (int)(ru % jt), k = 1 + (int)(ru / jt);
-            for (int c = c0; c < cpr; c += cstep) {
-                T x[3][V];
-                load(x, at(d, 1 + c * V, j, k));
-                add(x, k);
-            }
+        if constexpr (WHAT == 0) {
+            const double wz = 1.0 / (double)dzi[k], wzh = 1.0 / (double)dzhi[k];
+            acc[0] += s[0] * wz;
+            acc[1] += s[1] * wz;
+            if (k >= kw0) acc[2] += s[2] * wzh;
         }
     }
-    block_tree<RQ>(acc, is_max, partial + (int64_t)b * RQ);
-}
-
-template <typename T, int V>
-__global__ __launch_bounds__(RT) void reduce_pass1(Dims d, int what, int kw0, const T *f0, const T *f1,
-                                                  const T *f2, const T *dzi, const T *dzhi,
-                                                  double *partial)
-{
-    reduce_block<T, V>(d, what, kw0, f0, f1, f2, dzi, dzhi, (int)blockIdx.x, partial);
-}
-
-// Pass 2 over the RB partials at `partial` into out[0 .. nout-1].
-__device__ __forceinline__ void reduce_final(int what, const double *partial, double *out)
-{
-    double acc[RQ];
-    int is_max[RQ];
+    if constexpr (WHAT == 1) {
 #pragma unroll
-    for (int q = 0; q < RQ; ++q) {
-        acc[q] = 0.0;
-        is_max[q] = (what == 1 && q % 3 == 2);
+        for (int f = 0; f < 3; ++f) acc[3 * f + 2] = (double)mx[f];
     }
-    for (int b = threadIdx.x; b < RB; b += RT)
-#pragma unroll
-        for (int q = 0; q < RQ; ++q) acc[q] = comb(is_max[q], acc[q], partial[(int64_t)b * RQ + q]);
-    __shared__ double res[RQ];
-    block_tree<RQ>(acc, is_max, res);
-    __syncthreads();
-    const int nout = what == 0 ? 3 : 9;
-    if ((int)threadIdx.x < nout) out[threadIdx.x] = res[threadIdx.x];
+    block_tree<WHAT, RT>(acc, partial + b, pl.nb);
 }
 
-__global__ __launch_bounds__(RT) void reduce_pass2(int what, const double *partial, double *out)
+template <typename T, int V, int WHAT>
+__global__ __launch_bounds__(RT) void reduce_pass1(Dims d, RedPlan pl, int kw0, const T *f0, const T *f1,
+                                                  const T *f2, const T *dzi, const T *dzhi, double *partial)
 {
-    reduce_final(what, partial, out);
+    reduce_block<T, V, WHAT>(d, pl, kw0, f0, f1, f2, dzi, dzhi, (int)blockIdx.x, partial);
 }
 
-// Conservation sums (what = 0) of many grids in two launches: pass-1 block
-// blockIdx.x is block b of job g, (g, b) = blocks[blockIdx.x], into that
-// job's own RB partials; pass 2 reduces each slot's partials in one block.
-// Per grid the blocks, their rows and the trees are those of the single-grid
-// reduction, so each grid's sums are bitwise those of kl_reduce_fp64.  Only
-// blocks that own rows (b < jtot*ktot) are launched: a block without rows
-// gives the partial +0.0, which the partials hold from their allocation, and
-// adding +0.0 changes no sum that pass 2 forms (its sums start at +0.0).
+// Pass 2 over nb partials (value q of block b at partial[q * nb + b]).
+template <int WHAT>
+__device__ __forceinline__ void reduce_final(const double *partial, int nb, double *out)
+{
+    constexpr int NQ = RedShape<WHAT>::NQ;
+    double acc[NQ];
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) acc[q] = 0.0;
+#pragma unroll
+    for (int m = 0; m < RED_MAXB / RT2; ++m) {
+        const int b = m * RT2 + (int)threadIdx.x;
+        if (b < nb)
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) {
+                const double y = partial[(int64_t)q * nb + b];
+                acc[q] = RedShape<WHAT>::is_max(q) ? fmax(acc[q], y) : acc[q] + y;
+            }
+    }
+    block_tree<WHAT, RT2>(acc, out, 1);
+}
+
+template <int WHAT>
+__global__ __launch_bounds__(RT2) void reduce_pass2(const double *partial, int nb, double *out)
+{
+    reduce_final<WHAT>(partial, nb, out);
+}
+
+// Conservation sums of many grids in two launches: pass-1 block blockIdx.x is
+// block b of job g, (g, b) = blocks[blockIdx.x], into that job's own partials;
+// pass 2 reduces each grid's partials in one block.  Per grid the pieces,
+// blocks and trees are those of the single-grid reduction, so each grid's
+// sums are bitwise those of kl_reduce_fp64.
 struct SumJob {
     Dims d;
-    int kw0, slot;
+    RedPlan pl;
+    int kw0;
+    int64_t first;  // the job's first partial
     const void *f0, *f1, *f2, *dzi, *dzhi;
 };
 
@@ -418,14 +468,16 @@ __global__ __launch_bounds__(RT) void sums_batch_pass1(const SumJob *__restrict_
 {
     const int2 gb = blocks[blockIdx.x];
     const SumJob j = jobs[gb.x];
-    reduce_block<T, V>(j.d, 0, j.kw0, as_global((const T *)j.f0), as_global((const T *)j.f1),
-                       as_global((const T *)j.f2), as_global((const T *)j.dzi), as_global((const T *)j.dzhi),
-                       gb.y, partials + (int64_t)j.slot * RB * RQ);
+    reduce_block<T, V, 0>(j.d, j.pl, j.kw0, as_global((const T *)j.f0), as_global((const T *)j.f1),
+                          as_global((const T *)j.f2), as_global((const T *)j.dzi), as_global((const T *)j.dzhi),
+                          gb.y, partials + j.first);
 }
 
-__global__ __launch_bounds__(RT) void sums_batch_pass2(const double *partials, double *out)
+__global__ __launch_bounds__(RT2) void sums_batch_pass2(const longlong2 *__restrict__ slots, const double *partials,
+                                                       double *out)
 {
-    reduce_final(0, partials + (int64_t)blockIdx.x * RB * RQ, out + 3 * (int64_t)blockIdx.x);
+    const longlong2 sl = slots[blockIdx.x];  // first partial and number of blocks of this grid
+    reduce_final<0>(partials + sl.x, (int)sl.y, out + 3 * (int64_t)blockIdx.x);
 }
 
 // Bit hash: sum over interior cells (mod 2^64) of SplitMix64(bits ^ cell key).
@@ -583,48 +635,46 @@ hipError_t launch_zero_interior(const HostArgs &a, void *f, hipStream_t s)
     return hipGetLastError();
 }
 
-// Vector width of the reductions' loads: 4 floats or 2 doubles (16 bytes)
-// when every row start of the interior and every field pointer is aligned to
-// it (true), else 1 (false).
-bool reduce_vectorized(const HostArgs &a, const void *f0, const void *f1, const void *f2)
+namespace {
+template <typename T, int V>
+void launch_pass1(const HostArgs &a, const RedPlan &pl, int what, const void *f0, const void *f1, const void *f2,
+                  double *partial, hipStream_t s)
 {
-    const int vw = a.dtype == KL_F32 ? 4 : 2;
-    const size_t vb = (size_t)vw * (a.dtype == KL_F32 ? 4 : 8);
-    bool vec = a.itot % vw == 0 && (a.off + 1) % vw == 0 && a.js % vw == 0 && a.ks % vw == 0;
-    for (const void *p : {f0, f1, f2})
-        if (p && (uintptr_t)p % vb) vec = false;
-    return vec;
+    const Dims d = dims_of(a);
+    const T *p[3] = {(const T *)f0, (const T *)f1, (const T *)f2};
+    if (what == 0)
+        hipLaunchKernelGGL((reduce_pass1<T, V, 0>), dim3(pl.nb), dim3(RT), 0, s, d, pl, a.kw0, p[0], p[1], p[2],
+                           (const T *)a.dzi, (const T *)a.dzhi, partial);
+    else
+        hipLaunchKernelGGL((reduce_pass1<T, V, 1>), dim3(pl.nb), dim3(RT), 0, s, d, pl, a.kw0, p[0], p[1], p[2],
+                           (const T *)a.dzi, (const T *)a.dzhi, partial);
 }
+}  // namespace
 
 hipError_t launch_reduce(const HostArgs &a, int what, const void *f0, const void *f1, const void *f2,
                          double *out, void *scratch, hipStream_t s)
 {
-    const Dims d = dims_of(a);
     double *partial = (double *)scratch;
-    if ((int64_t)a.jtot * a.ktot >= ((int64_t)1 << 31)) return hipErrorInvalidValue;  // 32-bit row index
-    const bool vec = reduce_vectorized(a, f0, f1, f2);
+    if ((int64_t)a.jtot * a.ktot >= ((int64_t)1 << 31)) return hipErrorInvalidValue;  // 32-bit piece index
+    const RedPlan pl = red_plan(a);
+    const bool vec = row_chunk(a) > 1;
     if (a.dtype == KL_F32) {
         if (vec)
-            hipLaunchKernelGGL((reduce_pass1<float, 4>), dim3(RB), dim3(RT), 0, s, d, what, a.kw0,
-                               (const float *)f0, (const float *)f1, (const float *)f2, (const float *)a.dzi,
-                               (const float *)a.dzhi, partial);
+            launch_pass1<float, 4>(a, pl, what, f0, f1, f2, partial, s);
         else
-            hipLaunchKernelGGL((reduce_pass1<float, 1>), dim3(RB), dim3(RT), 0, s, d, what, a.kw0,
-                               (const float *)f0, (const float *)f1, (const float *)f2, (const float *)a.dzi,
-                               (const float *)a.dzhi, partial);
+            launch_pass1<float, 1>(a, pl, what, f0, f1, f2, partial, s);
     } else {
         if (vec)
-            hipLaunchKernelGGL((reduce_pass1<double, 2>), dim3(RB), dim3(RT), 0, s, d, what, a.kw0,
-                               (const double *)f0, (const double *)f1, (const double *)f2, (const double *)a.dzi,
-                               (const double *)a.dzhi, partial);
+            launch_pass1<double, 2>(a, pl, what, f0, f1, f2, partial, s);
         else
-            hipLaunchKernelGGL((reduce_pass1<double, 1>), dim3(RB), dim3(RT), 0, s, d, what, a.kw0,
-                               (const double *)f0, (const double *)f1, (const double *)f2, (const double *)a.dzi,
-                               (const double *)a.dzhi, partial);
+            launch_pass1<double, 1>(a, pl, what, f0, f1, f2, partial, s);
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(reduce_pass2, dim3(1), dim3(RT), 0, s, what, (const double *)partial, out);
+    if (what == 0)
+        hipLaunchKernelGGL(reduce_pass2<0>, dim3(1), dim3(RT2), 0, s, (const double *)partial, pl.nb, out);
+    else
+        hipLaunchKernelGGL(reduce_pass2<1>, dim3(1), dim3(RT2), 0, s, (const double *)partial, pl.nb, out);
     return hipGetLastError();
 }
 
@@ -675,23 +725,29 @@ hipError_t launch_fill_batch(int dtype, const void *jobs, const void *blocks, in
 
 size_t sum_job_bytes() { return sizeof(SumJob); }
 
-size_t sums_partial_bytes(int nslots) { return (size_t)nslots * RB * RQ * sizeof(double); }
+bool sums_vectorized(const HostArgs &a) { return row_chunk(a) > 1; }
 
-void append_sum_job(const HostArgs &a, const void *ut, const void *vt, const void *wt, int slot, std::vector<char> &jobs,
-                    std::vector<int2> &blocks)
+void append_sum_job(const HostArgs &a, const void *ut, const void *vt, const void *wt, std::vector<char> &jobs,
+                    std::vector<int2> &blocks, std::vector<longlong2> &slots, int64_t *npartials)
 {
     const int job = (int)(jobs.size() / sizeof(SumJob));
-    const int64_t nb = std::min<int64_t>(RB, (int64_t)a.jtot * a.ktot);
-    for (int b = 0; b < (int)nb; ++b) blocks.push_back(make_int2(job, b));
     SumJob j;
+    memset(&j, 0, sizeof j);
     j.d = dims_of(a);
+    j.pl = red_plan(a);
     j.kw0 = a.kw0;
-    j.slot = slot;
+    j.first = *npartials;
     j.f0 = ut;
     j.f1 = vt;
     j.f2 = wt;
     j.dzi = a.dzi;
     j.dzhi = a.dzhi;
+    for (int b = 0; b < j.pl.nb; ++b) blocks.push_back(make_int2(job, b));
+    longlong2 sl;
+    sl.x = j.first;
+    sl.y = j.pl.nb;
+    slots.push_back(sl);
+    *npartials += 3 * (int64_t)j.pl.nb;
     const char *p = (const char *)&j;
     jobs.insert(jobs.end(), p, p + sizeof j);
 }
@@ -717,10 +773,11 @@ hipError_t launch_sums_batch(int dtype, bool vec, const void *jobs, const void *
     return hipGetLastError();
 }
 
-hipError_t launch_sums_finish(const double *partials, int nslots, double *out, hipStream_t s)
+hipError_t launch_sums_finish(const void *slots, const double *partials, int nslots, double *out, hipStream_t s)
 {
     if (nslots <= 0) return hipSuccess;
-    hipLaunchKernelGGL(sums_batch_pass2, dim3((unsigned)nslots), dim3(RT), 0, s, partials, out);
+    hipLaunchKernelGGL(sums_batch_pass2, dim3((unsigned)nslots), dim3(RT2), 0, s, (const longlong2 *)slots, partials,
+                       out);
     return hipGetLastError();
 }
 

@@ -74,6 +74,7 @@ struct Batch {
     int nsjobs[2][2] = {{0, 0}, {0, 0}};
     int nsblocks[2][2] = {{0, 0}, {0, 0}};
     double *d_partials = nullptr;
+    void *d_sslots = nullptr;  // {first partial, blocks} per grid
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
     int64_t ntiles = 0;
@@ -110,6 +111,8 @@ struct Batch {
         }
         if (d_partials) (void)hipFree(d_partials);
         d_partials = nullptr;
+        if (d_sslots) (void)hipFree(d_sslots);
+        d_sslots = nullptr;
         groups.clear();
         ntiles = 0;
         nkernels = 0;
@@ -413,12 +416,14 @@ int build(Batch &b, void *const *fields)
     if (b.flags & KL_BATCH_SUMS) {
         std::vector<char> jobs[2][2];
         std::vector<int2> blocks[2][2];
+        std::vector<longlong2> slots;
+        int64_t npartials = 0;
         for (size_t n = 0; n < b.grids.size(); ++n) {
             const kl_grid_t *g = &b.grids[n];
             const HostArgs a = make_args(g);
             void *const *f = fields + 6 * n;
-            const int vec = reduce_vectorized(a, f[3], f[4], f[5]) ? 1 : 0;
-            append_sum_job(a, f[3], f[4], f[5], (int)n, jobs[g->dtype][vec], blocks[g->dtype][vec]);
+            const int vec = sums_vectorized(a) ? 1 : 0;
+            append_sum_job(a, f[3], f[4], f[5], jobs[g->dtype][vec], blocks[g->dtype][vec], slots, &npartials);
             ++b.nsjobs[g->dtype][vec];
         }
         for (int d = 0; d < 2; ++d)
@@ -430,12 +435,12 @@ int build(Batch &b, void *const *fields)
                     return hip_fail(e, "sum jobs");
                 b.nsblocks[d][v] = (int)blocks[d][v].size();
             }
-        // the partials of blocks that own no rows stay +0.0 (they are never launched)
-        const size_t pb = sums_partial_bytes((int)b.grids.size());
-        if ((e = hipMalloc((void **)&b.d_partials, pb)) != hipSuccess) return hip_fail(e, "sum partials");
-        if ((e = hipMemset(b.d_partials, 0, pb)) != hipSuccess) return hip_fail(e, "sum partials");
+        if ((e = hipMalloc((void **)&b.d_partials, (size_t)npartials * sizeof(double))) != hipSuccess)
+            return hip_fail(e, "sum partials");
+        if ((e = upload(&b.d_sslots, slots.data(), slots.size() * sizeof(longlong2))) != hipSuccess)
+            return hip_fail(e, "sum slots");
     }
-    // the queue and partial-buffer clears above ran on the null stream: let
+    // the queue clears above ran on the null stream: let
     // them finish before any replay can start on another stream
     if ((e = hipStreamSynchronize(nullptr)) != hipSuccess) return hip_fail(e, "batch set-up");
     // capture the graph on a private stream
@@ -473,7 +478,7 @@ int build(Batch &b, void *const *fields)
                 ++b.nkernels;
             }
         if (rc == KL_OK) {
-            e = launch_sums_finish(b.d_partials, (int)b.grids.size(), b.sums, cs);
+            e = launch_sums_finish(b.d_sslots, b.d_partials, (int)b.grids.size(), b.sums, cs);
             if (e != hipSuccess) rc = hip_fail(e, "sums finish");
             ++b.nkernels;
         }

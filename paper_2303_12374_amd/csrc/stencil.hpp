@@ -72,6 +72,8 @@ __device__ __forceinline__ float tfma(float a, float b, float c) { return __buil
 __device__ __forceinline__ double tfma(double a, double b, double c) { return __builtin_fma(a, b, c); }
 __device__ __forceinline__ float tabs(float a) { return __builtin_fabsf(a); }
 __device__ __forceinline__ double tabs(double a) { return __builtin_fabs(a); }
+__device__ __forceinline__ float tmax(float a, float b) { return __builtin_fmaxf(a, b); }
+__device__ __forceinline__ double tmax(double a, double b) { return __builtin_fmax(a, b); }
 
 // advec_u tendency at one u point.  Arguments are named by their offset from
 // the point: u at (i,j,k) and its six neighbours, v at (i-1..i, j..j+1, k),
@@ -164,6 +166,22 @@ __device__ __forceinline__ void vstore(T *p, const T (&s)[N])
 #pragma unroll
         for (int n = 0; n < N; ++n) x[n] = s[n];
         *reinterpret_cast<V *>(p) = x;
+    }
+}
+
+// Load N consecutive elements from an address aligned to one element only
+// (the hardware takes a global vector access at any 4-byte boundary; a wave's
+// row then spans at most one cache line more than an aligned one).
+template <typename T, int N>
+__device__ __forceinline__ void uload(T (&d)[N], const T *p)
+{
+    if constexpr (N == 1) {
+        d[0] = *p;
+    } else {
+        typedef typename VecOf<T, N>::type V __attribute__((aligned(sizeof(T))));
+        const V x = *reinterpret_cast<const V *>(p);
+#pragma unroll
+        for (int n = 0; n < N; ++n) d[n] = x[n];
     }
 }
 

@@ -249,3 +249,33 @@ def test_hash_detects_single_bit_change():
     xi[3, 4, 5] = torch.nextafter(xi[3, 4, 5], torch.tensor(10.0, device="cuda"))
     m.kl_hash_interior(g, x, h[1:2])
     assert h[0].item() != h[1].item()
+
+
+@pytest.mark.parametrize("layout", ["padded", "plain"])
+@pytest.mark.parametrize("shape", [(1, 5, 4), (4, 9, 5), (6, 2, 3), (301, 23, 7), (20, 700, 3), (9001, 2, 2), (64, 96, 400)],
+                         ids=lambda s: "x".join(map(str, s)))
+@pytest.mark.parametrize("dtype", [0, 1], ids=["f32", "f64"])
+def test_reduction_pieces_match_oracle(dtype, shape, layout):
+    """The reductions' row pieces where they can go wrong: rows of one point,
+    of one chunk, of a chunk and a masked tail, misaligned rows, levels that
+    end in a partial piece, rows wider than a piece, and more pieces than
+    blocks.  The sums accumulate in double, so each is within 1e-12 of the
+    sum of its terms' magnitudes; the maxima are exact."""
+    import torch
+    m = kl()
+    lay = inputs.plain_layout(*shape) if layout == "plain" else None
+    c = Case(*shape, dtype, bc=2 if shape[2] < 3 else 0, seed=14, layout=lay)
+    out = torch.zeros(9, dtype=torch.float64, device="cuda")
+    m.kl_reduce_fp64(c.g, 1, *c.dev, out)
+    got = out.cpu().numpy()
+    for n, h in enumerate(c.host):
+        ref = oracle.checksums(c.og, h)
+        x = c.interior_np(h)
+        assert abs(got[3 * n] - ref[0]) <= 1e-12 * np.sum(np.abs(x))
+        assert abs(got[3 * n + 1] - ref[1]) <= 1e-12 * ref[1]
+        assert got[3 * n + 2] == ref[2]
+    out3 = torch.zeros(3, dtype=torch.float64, device="cuda")
+    m.kl_reduce_fp64(c.g, 0, *c.dev, out3)
+    ref = oracle.conservation(c.og, *c.host)
+    scale = sum(np.sum(np.abs(c.interior_np(h))) for h in c.host) * np.max(1.0 / c.og.dzi)
+    assert np.max(np.abs(out3.cpu().numpy() - ref)) <= 1e-12 * scale
