@@ -347,9 +347,7 @@ int kl_euler(const kl_grid_t *g, double dt, void *u, void *v, void *w, const voi
     a.ut = (void *)ut;
     a.vt = (void *)vt;
     a.wt = (void *)wt;
-    hipError_t e = launch_euler(a, dt, u, v, w, (hipStream_t)stream);
-    // the fused refill covers one ghost layer; wider halos are refilled whole
-    if (e == hipSuccess && g->gc != 1) e = launch_fill_ghosts(a, u, v, w, (hipStream_t)stream);
+    const hipError_t e = launch_euler(a, dt, u, v, w, (hipStream_t)stream);
     return e == hipSuccess ? KL_OK : hip_fail(e, "euler");
 }
 
@@ -373,8 +371,7 @@ int kl_step(const kl_grid_t *g, double visc, double dt, void *u, void *v, void *
     a.ut = ut;
     a.vt = vt;
     a.wt = wt;
-    hipError_t e = launch_euler(a, dt, u, v, w, s);
-    if (e == hipSuccess && g->gc != 1) e = launch_fill_ghosts(a, u, v, w, s);
+    const hipError_t e = launch_euler(a, dt, u, v, w, s);
     return e == hipSuccess ? KL_OK : hip_fail(e, "euler");
 }
 

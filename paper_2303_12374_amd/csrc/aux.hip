@@ -148,68 +148,6 @@ __global__ __launch_bounds__(256) void fill_ghosts_batch_kernel(const FillJob *_
                  j.n3, (int64_t)b.y * 256 + threadIdx.x);
 }
 
-// Forward Euler at one interior point: the thread writes the updated cell
-// and every ghost cell whose source it is (the inverse of the fill map).
-template <typename T>
-__device__ __forceinline__ void euler_point(const Dims &d, T dt, int kw0, T *u, T *v, T *w, const T *ut,
-                                            const T *vt, const T *wt, int i, int j, int k)
-{
-    const int64_t c = at(d, i, j, k);
-    // x and y images of (i, j)
-    int xi[3], yj[3], nx = 1, ny = 1;
-    xi[0] = i;
-    yj[0] = j;
-    if (i == d.itot) xi[nx++] = 0;
-    if (i == 1) xi[nx++] = d.itot + 1;
-    if (j == d.jtot) yj[ny++] = 0;
-    if (j == 1) yj[ny++] = d.jtot + 1;
-    T *f3[3] = {u, v, w};
-    const T *t3[3] = {ut, vt, wt};
-#pragma unroll
-    for (int f = 0; f < 3; ++f) {
-        if (f == 2 && k < kw0) continue;
-        T *p = f3[f];
-        const T val = euler_value<T>(p[c], dt, t3[f][c]);
-        // z images with their factors
-        int zk[4], zs[4], nz = 1;
-        zk[0] = k;
-        zs[0] = 1;
-        const int kt = d.ktot;
-        if (d.bc == KL_BC_ZPERIODIC) {
-            if (k == kt) { zk[nz] = 0; zs[nz++] = 1; }
-            if (k == 1) { zk[nz] = kt + 1; zs[nz++] = 1; }
-        } else if (f < 2) {
-            if (k == 1) { zk[nz] = 0; zs[nz++] = 1; }
-            if (k == kt) { zk[nz] = kt + 1; zs[nz++] = 1; }
-        } else if (d.bc == KL_BC_ZWALL_ZEROGRAD) {
-            if (k == 2) { zk[nz] = 0; zs[nz++] = 1; zk[nz] = 1; zs[nz++] = 1; }
-            if (k == kt) { zk[nz] = kt + 1; zs[nz++] = 1; }
-        } else {
-            if (k == 2) { zk[nz] = 0; zs[nz++] = -1; zk[nz] = 1; zs[nz++] = 0; }
-            if (k == kt) { zk[nz] = kt + 1; zs[nz++] = 0; }
-        }
-        for (int a = 0; a < nz; ++a) {
-            const T zv = zs[a] == 0 ? T(0) : (zs[a] < 0 ? -val : val);
-            for (int y = 0; y < ny; ++y)
-                for (int x = 0; x < nx; ++x) p[at(d, xi[x], yj[y], zk[a])] = zv;
-        }
-    }
-}
-
-template <typename T>
-__global__ __launch_bounds__(256) void euler_kernel(Dims d, T dt, int kw0, T *u, T *v, T *w,
-                                                   const T *ut, const T *vt, const T *wt, int nbx)
-{
-    unsigned b = blockIdx.x;
-    const int bx = b % nbx;
-    b /= nbx;
-    const int j = 1 + (int)(b % d.jtot);
-    const int k = 1 + (int)(b / d.jtot);
-    const int i = 1 + bx * 256 + (int)threadIdx.x;
-    if (i > d.itot) return;
-    euler_point<T>(d, dt, kw0, u, v, w, ut, vt, wt, i, j, k);
-}
-
 template <typename T>
 __global__ __launch_bounds__(256) void zero_interior_kernel(Dims d, T *f, int nbx)
 {
@@ -262,17 +200,132 @@ inline int row_chunk(const HostArgs &a)
     return a.itot >= V ? V : 1;
 }
 
-// One chunk of a piece: its offset from the piece's first point, and the first
-// of its V points that counts (V: none, for a thread beyond the piece's end).
+// Chunk e of a piece of n chunks: its row and first column (0-based) in the
+// piece, and the first of its V points that counts (V: none, for a thread
+// beyond the piece's end).
 template <int V>
-__device__ __forceinline__ int64_t chunk_at(const RowPieces &rp, int64_t js, uint32_t e, uint32_t n, int &lo)
+struct Chunk {
+    int row, col, lo;
+    __device__ Chunk() {}
+    __device__ __forceinline__ Chunk(const RowPieces &rp, uint32_t e, uint32_t n)
+    {
+        const uint32_t ec = e < n ? e : n - 1;
+        const uint32_t r = rp.cpr == 1 ? ec : __umulhi(ec, rp.magic);
+        const uint32_t c = ec - r * rp.cpr;
+        const uint32_t ov = V > 1 && c == rp.cpr - 1 ? rp.ov : 0u;
+        row = (int)r;
+        col = (int)(c * (uint32_t)V - ov);
+        lo = e < n ? (int)ov : V;
+    }
+};
+
+// ---------------------------------------------------------------------------
+// Forward Euler, f += dt * ft, with the ghost refill: the thread that updates
+// a chunk also writes every ghost cell whose source is in it (the inverse of
+// the fill map; needs itot, jtot >= gc, so that every ghost cell is the image
+// of one interior cell by one shift).
+//
+// Bound by HBM: 6 values read and 3 written per point.  One chunk per thread
+// and 256 a piece: the blocks then sweep memory in order (pieces of 2048
+// chunks ran 10-20% slower).  The tendencies are read for the last time and
+// stream past the caches.  The images cost a branch that only the pieces and
+// chunks on a face take.  Against one point per thread (and a second kernel
+// for the outer layers of a three-layer halo): 256^3 FP32 158 -> 85 us, gc = 3
+// 176 -> 95; 512x512x256 FP32 592 -> 413 us (5.9 TB/s), FP64 1055 -> 825;
+// 301x203x151 FP32 137 -> 52 us.
+// ---------------------------------------------------------------------------
+// Store the points n >= lo of a chunk at (i0 .., j, k), and their x images.
+template <typename T, int V, int NT = 0>
+__device__ __forceinline__ void put_chunk(const Dims &d, T *p, int i0, int j, int k, int lo, const T (&val)[V])
 {
-    const uint32_t ec = e < n ? e : n - 1;
-    const uint32_t row = rp.cpr == 1 ? ec : __umulhi(ec, rp.magic);
-    const uint32_t c = ec - row * rp.cpr;
-    const uint32_t ov = V > 1 && c == rp.cpr - 1 ? rp.ov : 0u;
-    lo = e < n ? (int)ov : V;
-    return (int64_t)row * js + (int64_t)(c * (uint32_t)V - ov);
+    T *row = p + at(d, 0, j, k);
+    if (lo == 0) {
+        if constexpr (NT)
+            ustore_nt<T, V>(row + i0, val);
+        else
+            ustore<T, V>(row + i0, val);
+    } else {
+#pragma unroll
+        for (int n = 0; n < V; ++n)
+            if (n >= lo) row[i0 + n] = val[n];
+    }
+    if (i0 <= d.gc || i0 + V - 1 > d.itot - d.gc) {
+#pragma unroll
+        for (int n = 0; n < V; ++n) {
+            const int i = i0 + n;
+            if (n >= lo && i <= d.gc) row[d.itot + i] = val[n];
+            if (n >= lo && i > d.itot - d.gc) row[i - d.itot] = val[n];
+        }
+    }
+}
+
+template <typename T, int V, int NT>
+__device__ __forceinline__ void euler_chunk(const Dims &d, T *p, int f, int i0, int j, int k,
+                                            int lo, const T (&val)[V])
+{
+    put_chunk<T, V, NT>(d, p, i0, j, k, lo, val);
+    const int kt = d.ktot;
+    if (j > d.gc && j <= d.jtot - d.gc && k > 2 && k < kt) return;
+    // z images with their factors
+    int zk[4], zs[4], nz = 1;
+    zk[0] = k;
+    zs[0] = 1;
+    if (d.bc == KL_BC_ZPERIODIC) {
+        if (k == kt) { zk[nz] = 0; zs[nz++] = 1; }
+        if (k == 1) { zk[nz] = kt + 1; zs[nz++] = 1; }
+    } else if (f < 2) {
+        if (k == 1) { zk[nz] = 0; zs[nz++] = 1; }
+        if (k == kt) { zk[nz] = kt + 1; zs[nz++] = 1; }
+    } else if (d.bc == KL_BC_ZWALL_ZEROGRAD) {
+        if (k == 2) { zk[nz] = 0; zs[nz++] = 1; zk[nz] = 1; zs[nz++] = 1; }
+        if (k == kt) { zk[nz] = kt + 1; zs[nz++] = 1; }
+    } else {
+        if (k == 2) { zk[nz] = 0; zs[nz++] = -1; zk[nz] = 1; zs[nz++] = 0; }
+        if (k == kt) { zk[nz] = kt + 1; zs[nz++] = 0; }
+    }
+    for (int a = 0; a < nz; ++a) {
+        T v[V];
+#pragma unroll
+        for (int n = 0; n < V; ++n) v[n] = zs[a] == 0 ? T(0) : (zs[a] < 0 ? -val[n] : val[n]);
+        if (a > 0) put_chunk<T, V>(d, p, i0, j, zk[a], lo, v);
+        if (j <= d.gc) put_chunk<T, V>(d, p, i0, d.jtot + j, zk[a], lo, v);
+        if (j > d.jtot - d.gc) put_chunk<T, V>(d, p, i0, j - d.jtot, zk[a], lo, v);
+    }
+}
+
+template <typename T, int V, int NT>
+__global__ __launch_bounds__(256) void euler_kernel(Dims d, RowPieces rp, T dt, int kw0, T *u, T *v, T *w,
+                                                   const T *ut, const T *vt, const T *wt)
+{
+    const uint32_t pc = blockIdx.x;
+    const int k = 1 + (int)(pc / rp.ng);
+    const uint32_t j0 = (pc % rp.ng) * rp.R;
+    const uint32_t left = (uint32_t)d.jtot - j0;
+    const uint32_t n = (left < rp.R ? left : rp.R) * rp.cpr;
+    T *f3[3] = {u, v, w};
+    const T *t3[3] = {ut, vt, wt};
+    const int64_t base = at(d, 1, 1 + (int)j0, k);
+    for (uint32_t e = threadIdx.x; e < n; e += 256) {
+        const Chunk<V> c(rp, e, n);
+        const int64_t o = base + (int64_t)c.row * d.js + c.col;
+        T x[3][V], y[3][V];
+#pragma unroll
+        for (int f = 0; f < 3; ++f) {
+            if constexpr (NT)
+                uload_nt<T, V>(x[f], f3[f] + o);
+            else
+                uload<T, V>(x[f], f3[f] + o);
+            uload_nt<T, V>(y[f], t3[f] + o);
+        }
+#pragma unroll
+        for (int f = 0; f < 3; ++f) {
+            if (f == 2 && k < kw0) continue;
+            T val[V];
+#pragma unroll
+            for (int i = 0; i < V; ++i) val[i] = euler_value<T>(x[f][i], dt, y[f][i]);
+            euler_chunk<T, V, NT>(d, f3[f], f, 1 + c.col, 1 + (int)j0 + c.row, k, c.lo, val);
+        }
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -373,7 +426,9 @@ __device__ __forceinline__ void reduce_block(const Dims &d, const RedPlan &pl, i
             int lo[M];
 #pragma unroll
             for (int m = 0; m < M; ++m) {
-                const int64_t o = base + chunk_at<V>(rp, d.js, e0 + m * RT, n, lo[m]);
+                const Chunk<V> c(rp, e0 + m * RT, n);
+                const int64_t o = base + (int64_t)c.row * d.js + c.col;
+                lo[m] = c.lo;
 #pragma unroll
                 for (int f = 0; f < 3; ++f) {
                     if (WHAT == 1 && f3[f] == nullptr) {
@@ -607,20 +662,39 @@ hipError_t launch_fill_scalar(const HostArgs &a, void *f, hipStream_t s)
     return fill_launch(a, f, nullptr, nullptr, 0, 0, 0, false, s);
 }
 
+namespace {
+// Above this size of u, v and w together they are streamed past the caches:
+// the memory-side cache holds 256 MB, and fields that fit are still there
+// when the next kernel reads them (256^3 FP32, 201 MB: 86 us cached, 104
+// streamed; 512x512x256 FP32, 805 MB: 507 us cached, 397 streamed).
+constexpr double EULER_CACHED_BYTES = 256e6;
+
+template <typename T, int V, int NT>
+void euler_go(const HostArgs &a, const Dims &d, const RowPieces &rp, double dt, void *u, void *v, void *w, hipStream_t s)
+{
+    hipLaunchKernelGGL((euler_kernel<T, V, NT>), dim3(rp.np), dim3(256), 0, s, d, rp, (T)dt, a.kw0, (T *)u, (T *)v,
+                       (T *)w, (const T *)a.ut, (const T *)a.vt, (const T *)a.wt);
+}
+}  // namespace
+
 hipError_t launch_euler(const HostArgs &a, double dt, void *u, void *v, void *w, hipStream_t s)
 {
-    const Dims d = dims_of(a);
-    const int nbx = (int)cdiv(a.itot, 256);
-    const unsigned nb = (unsigned)nbx * a.jtot * a.ktot;
+    // grids narrower than their halo: update with one ghost layer, refill all of them after
+    const bool narrow = a.itot < a.gc || a.jtot < a.gc;
+    Dims d = dims_of(a);
+    if (narrow) d.gc = 1;
+    if ((int64_t)a.jtot * a.ktot >= ((int64_t)1 << 31)) return hipErrorInvalidValue;  // 32-bit piece index
+    const int V = row_chunk(a);
+    const RowPieces rp = row_pieces(a, V, 256);
+    const bool nt = 3.0 * a.itot * a.jtot * a.ktot * (a.dtype == KL_F32 ? 4 : 8) > EULER_CACHED_BYTES;
     if (a.dtype == KL_F32)
-        hipLaunchKernelGGL(euler_kernel<float>, dim3(nb), dim3(256), 0, s, d, (float)dt, a.kw0, (float *)u,
-                           (float *)v, (float *)w, (const float *)a.ut, (const float *)a.vt,
-                           (const float *)a.wt, nbx);
+        V == 4 ? (nt ? euler_go<float, 4, 1>(a, d, rp, dt, u, v, w, s) : euler_go<float, 4, 0>(a, d, rp, dt, u, v, w, s))
+               : euler_go<float, 1, 0>(a, d, rp, dt, u, v, w, s);
     else
-        hipLaunchKernelGGL(euler_kernel<double>, dim3(nb), dim3(256), 0, s, d, dt, a.kw0, (double *)u,
-                           (double *)v, (double *)w, (const double *)a.ut, (const double *)a.vt,
-                           (const double *)a.wt, nbx);
-    return hipGetLastError();
+        V == 2 ? (nt ? euler_go<double, 2, 1>(a, d, rp, dt, u, v, w, s) : euler_go<double, 2, 0>(a, d, rp, dt, u, v, w, s))
+               : euler_go<double, 1, 0>(a, d, rp, dt, u, v, w, s);
+    const hipError_t e = hipGetLastError();
+    return e == hipSuccess && narrow ? launch_fill_ghosts(a, u, v, w, s) : e;
 }
 
 hipError_t launch_zero_interior(const HostArgs &a, void *f, hipStream_t s)

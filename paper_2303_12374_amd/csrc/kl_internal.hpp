@@ -87,6 +87,7 @@ hipError_t launch_fill_scalar(const HostArgs &a, void *f, hipStream_t s);
 // without the x ghost columns of interior rows): after a step that stored
 // the new values and their x images only.
 hipError_t launch_fill_yz_images(const HostArgs &a, void *u, void *v, void *w, hipStream_t s);
+// f += dt * ft with the ghost cells refilled, all a.gc layers
 hipError_t launch_euler(const HostArgs &a, double dt, void *u, void *v, void *w, hipStream_t s);
 hipError_t launch_zero_interior(const HostArgs &a, void *f, hipStream_t s);
 hipError_t launch_reduce(const HostArgs &a, int what, const void *f0, const void *f1,

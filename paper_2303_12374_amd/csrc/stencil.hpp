@@ -185,6 +185,47 @@ __device__ __forceinline__ void uload(T (&d)[N], const T *p)
     }
 }
 
+template <typename T, int N>
+__device__ __forceinline__ void uload_nt(T (&d)[N], const T *p)
+{
+    if constexpr (N == 1) {
+        d[0] = __builtin_nontemporal_load(p);
+    } else {
+        typedef typename VecOf<T, N>::type V __attribute__((aligned(sizeof(T))));
+        const V x = __builtin_nontemporal_load(reinterpret_cast<const V *>(p));
+#pragma unroll
+        for (int n = 0; n < N; ++n) d[n] = x[n];
+    }
+}
+
+template <typename T, int N>
+__device__ __forceinline__ void ustore(T *p, const T (&s)[N])
+{
+    if constexpr (N == 1) {
+        *p = s[0];
+    } else {
+        typedef typename VecOf<T, N>::type V __attribute__((aligned(sizeof(T))));
+        V x;
+#pragma unroll
+        for (int n = 0; n < N; ++n) x[n] = s[n];
+        *reinterpret_cast<V *>(p) = x;
+    }
+}
+
+template <typename T, int N>
+__device__ __forceinline__ void ustore_nt(T *p, const T (&s)[N])
+{
+    if constexpr (N == 1) {
+        __builtin_nontemporal_store(s[0], p);
+    } else {
+        typedef typename VecOf<T, N>::type V __attribute__((aligned(sizeof(T))));
+        V x;
+#pragma unroll
+        for (int n = 0; n < N; ++n) x[n] = s[n];
+        __builtin_nontemporal_store(x, reinterpret_cast<V *>(p));
+    }
+}
+
 // Streaming (non-temporal) variants for data touched exactly once.
 template <typename T, int N>
 __device__ __forceinline__ void vload_nt(T (&d)[N], const T *p)

@@ -279,3 +279,36 @@ def test_reduction_pieces_match_oracle(dtype, shape, layout):
     ref = oracle.conservation(c.og, *c.host)
     scale = sum(np.sum(np.abs(c.interior_np(h))) for h in c.host) * np.max(1.0 / c.og.dzi)
     assert np.max(np.abs(out3.cpu().numpy() - ref)) <= 1e-12 * scale
+
+
+@pytest.mark.parametrize("gc", [1, 3])
+@pytest.mark.parametrize("bc", [0, 1, 2], ids=["zerograd", "nopen", "zperiodic"])
+@pytest.mark.parametrize("shape", [(1, 1, 2), (3, 3, 2), (5, 2, 3), (7, 5, 4), (16, 600, 3), (301, 13, 5), (4100, 3, 2)],
+                         ids=lambda s: "x".join(map(str, s)))
+@pytest.mark.parametrize("dtype", [0, 1], ids=["f32", "f64"])
+def test_euler_updates_and_refills_every_ghost(dtype, shape, bc, gc):
+    """f + dt * ft at each advanced point to one rounding of the product and
+    one of the sum, and every ghost cell of all gc layers the ghost fill's
+    value; rows shorter than a chunk, masked tails, rows wider than a piece,
+    grids narrower than their halo, the padded and the unpadded layout."""
+    import torch
+    m = kl()
+    eps = float(np.finfo(m.NP_DTYPE[dtype]).eps)
+    for lay in (None, inputs.plain_layout(*shape, gh=gc)):
+        g = m.Grid(*shape, dtype=dtype, bc=bc, gc=gc, layout=lay)
+        rng = np.random.RandomState(5)
+        f = [g.upload(rng.uniform(-1, 1, shape[::-1])) for _ in range(3)]
+        t = [g.upload(rng.uniform(-1, 1, shape[::-1])) for _ in range(3)]
+        m.kl_fill_ghosts(g, *f)
+        dt = 0.125 + 1e-3
+        dte = float(m.NP_DTYPE[dtype](dt))
+        want = [g.interior(x).double() + dte * g.interior(y).double() for x, y in zip(f, t)]
+        m.kl_euler(g, dt, *f, *t)
+        k0 = 0 if bc == 2 else 1  # w's first advanced level, 0-based
+        for n in range(3):
+            d = (g.interior(f[n]).double() - want[n])[k0 if n == 2 else 0:].abs()
+            assert d.numel() == 0 or float(d.max()) <= 2 * eps * 1.126
+        chk = [x.clone() for x in f]
+        m.kl_fill_ghosts(g, *chk)
+        for a, b in zip(f, chk):
+            assert torch.equal(torch.nan_to_num(a, nan=77.0), torch.nan_to_num(b, nan=77.0))
