@@ -42,18 +42,18 @@ KERNEL_SOURCES = {
 
 def kernel_of_symbol(sym):
     """Library kernel a rocprofv3 kernel symbol belongs to, or None.  The
-    step tile serves both the fused step (last template argument 0) and the
-    fused advec_u + diff_uvw pass (1)."""
+    step tile serves both the fused step (bit 0 of the last template argument
+    clear) and the fused advec_u + diff_uvw pass (set)."""
     import re
     m = re.search(r"kl::(\w+?)_(zl3|zlp|zl|zr|zc|plain)(_batch)?<([^>]*)>", sym)
     if not m:
         m = re.search(r"kl::(step)_zl(_batch)?<([^>]*)>", sym)
         if not m:
             return None
-        return "advec_diff" if m.group(3).split(",")[-1].strip() == "1" else "step"
+        return "advec_diff" if int(m.group(3).split(",")[-1]) & 1 else "step"
     name = m.group(1)
     if name == "step":
-        return "advec_diff" if m.group(4).split(",")[-1].strip() == "1" else "step"
+        return "advec_diff" if int(m.group(4).split(",")[-1]) & 1 else "step"
     return name if name in KERNEL_SOURCES else None
 
 

@@ -165,7 +165,7 @@ int select_variant(const kl_grid_t *g, int kernel)
 }
 
 int run_variant(const kl_grid_t *g, int kernel, int index, void *const *fields, double visc, hipStream_t s,
-                double dt)
+                double dt, bool fresh)
 {
     const auto &vs = variants(kernel, g->dtype);
     if (index < 0 || index >= (int)vs.size()) return fail(KL_ERR_NOTFOUND, "variant index %d", index);
@@ -185,7 +185,7 @@ int run_variant(const kl_grid_t *g, int kernel, int index, void *const *fields, 
     a.wt = fields[5];
     a.evisc = nptr > 6 ? fields[6] : nullptr;
     a.visc = visc;
-    const hipError_t e = v.launch(a, s);
+    const hipError_t e = fresh ? v.fresh(a, s) : v.launch(a, s);
     if (e != hipSuccess) return hip_fail(e, v.name);
     return KL_OK;
 }
@@ -206,7 +206,7 @@ int check_ptrs(const void *const *p, int n)
 // Launch `kernel` with the selected configuration, falling back to the
 // default when the selected one does not fit this call's alignment.
 int launch_selected(const kl_grid_t *g, int kernel, void *const *fields, double visc, hipStream_t s,
-                    double dt = 0.0)
+                    double dt = 0.0, bool fresh = false)
 {
     int index = select_variant(g, kernel);
     const auto &vs = variants(kernel, g->dtype);
@@ -215,9 +215,10 @@ int launch_selected(const kl_grid_t *g, int kernel, void *const *fields, double 
     if (!variant_eligible(vs[index], g, ptrs, nptr)) index = 0;
     if (!variant_eligible(vs[index], g, ptrs, nptr))
         return fail(KL_ERR_INVALID, "no configuration of %s fits this grid/alignment", kernel_name(kernel));
-    const int rc = maybe_capture(g, kernel, fields, visc, dt, s);
+    // a capture holds the tendencies a launch accumulates onto
+    const int rc = fresh ? KL_OK : maybe_capture(g, kernel, fields, visc, dt, s);
     if (rc) return rc;
-    return run_variant(g, kernel, index, fields, visc, s, dt);
+    return run_variant(g, kernel, index, fields, visc, s, dt, fresh);
 }
 
 bool kernel_ok(int32_t kernel) { return kernel >= 0 && kernel < KL_NUM_KERNELS; }
@@ -361,13 +362,20 @@ int kl_step(const kl_grid_t *g, double visc, double dt, void *u, void *v, void *
     if ((rc = check_ptrs(p, 6))) return rc;
     hipStream_t s = (hipStream_t)stream;
     HostArgs a = make_args(g);
-    for (void *t : {ut, vt, wt}) {
-        const hipError_t e = launch_zero_interior(a, t, s);
-        if (e != hipSuccess) return hip_fail(e, "zero tendencies");
-    }
     void *f[6] = {u, v, w, ut, vt, wt};
-    if ((rc = launch_selected(g, KL_KERNEL_ADVEC_U, f, visc, s))) return rc;
-    if ((rc = launch_selected(g, KL_KERNEL_DIFF_UVW, f, visc, s))) return rc;
+    if (capture_pending(g, KL_KERNEL_ADVEC_U) || capture_pending(g, KL_KERNEL_DIFF_UVW)) {
+        // the step's two tendency kernels are to be captured: launch them
+        for (void *t : {ut, vt, wt}) {
+            const hipError_t e = launch_zero_interior(a, t, s);
+            if (e != hipSuccess) return hip_fail(e, "zero tendencies");
+        }
+        if ((rc = launch_selected(g, KL_KERNEL_ADVEC_U, f, visc, s))) return rc;
+        if ((rc = launch_selected(g, KL_KERNEL_DIFF_UVW, f, visc, s))) return rc;
+    } else {
+        // one pass for the zeroing and both kernels, bitwise theirs: 6 values
+        // per point moved instead of 17
+        if ((rc = launch_selected(g, KL_KERNEL_ADVEC_DIFF, f, visc, s, 0.0, true))) return rc;
+    }
     a.ut = ut;
     a.vt = vt;
     a.wt = wt;

@@ -11,9 +11,11 @@
 // then takes every grid it can serve, the next one the rest it can serve, and
 // so on (all configurations give the same bits).  Grids are grouped by
 // (dtype, configuration); every group becomes one persistent kernel whose
-// blocks draw tiles from a work queue over the group's tile list, so the
-// graph holds: [zero tendencies] -> the fused groups (one launch when one
-// configuration serves every grid).
+// blocks draw tiles from a work queue over the group's tile list (one launch
+// when one configuration serves every grid).  Cleared tendencies
+// (KL_BATCH_ZERO_TENDENCIES) are not a step of the graph: the groups then run
+// the form of the pass that starts them at zero and does not read them
+// (FUSE_FRESH).
 //
 // A configuration that is fastest for one grid launched alone (where the
 // launch is short and latency decides) need not be fastest inside a batch
@@ -61,9 +63,6 @@ struct Batch {
     double *sums = nullptr;    // caller's device array of 3 doubles per grid (KL_BATCH_SUMS)
     int forced[2] = {-1, -1};  // configuration serving every grid it can, per dtype (-1: per-grid selection)
     void *d_desc[2] = {nullptr, nullptr};  // StencilArgs<float>[] and StencilArgs<double>[], indexed by grid
-    std::vector<int4> ztiles[2];
-    void *d_ztiles[2] = {nullptr, nullptr};
-    int zblocks[2] = {0, 0};
     std::vector<Group> groups;
     // ghost fill jobs and their blocks, per dtype
     void *d_fjobs[2] = {nullptr, nullptr}, *d_fblocks[2] = {nullptr, nullptr};
@@ -89,11 +88,7 @@ struct Batch {
         graph = nullptr;
         for (int d = 0; d < 2; ++d) {
             if (d_desc[d]) (void)hipFree(d_desc[d]);
-            if (d_ztiles[d]) (void)hipFree(d_ztiles[d]);
             d_desc[d] = nullptr;
-            d_ztiles[d] = nullptr;
-            ztiles[d].clear();
-            zblocks[d] = 0;
         }
         for (auto &g : groups) {
             if (g.d_tiles) (void)hipFree(g.d_tiles);
@@ -178,17 +173,6 @@ void merge_batch_groups(int kernel, const std::vector<kl_grid_t> &grids, void *c
             }
         }
     }
-}
-
-hipError_t launch_zero_batch(int dtype, const void *descs, const void *tiles, int ntiles, int nblocks, hipStream_t s)
-{
-    if (dtype == KL_F32)
-        hipLaunchKernelGGL(zero_tendencies_batch<float>, dim3(nblocks), dim3(256), 0, s,
-                           (const StencilArgs<float> *)descs, (const int4 *)tiles, ntiles);
-    else
-        hipLaunchKernelGGL(zero_tendencies_batch<double>, dim3(nblocks), dim3(256), 0, s,
-                           (const StencilArgs<double> *)descs, (const int4 *)tiles, ntiles);
-    return hipGetLastError();
 }
 
 namespace {
@@ -378,23 +362,8 @@ int build(Batch &b, void *const *fields)
         if ((e = hipMalloc((void **)&gr.d_queue, 2 * sizeof(int))) != hipSuccess) return hip_fail(e, "queue");
         if ((e = hipMemset(gr.d_queue, 0, 2 * sizeof(int))) != hipSuccess) return hip_fail(e, "queue");
         const Variant &v = variants(gr.kernel, gr.dtype)[gr.variant];
-        gr.nblocks = persistent_blocks((int64_t)gr.tiles.size(), ncu, v.occupancy());
+        gr.nblocks = persistent_blocks((int64_t)gr.tiles.size(), ncu, b.zero ? v.occupancy_fresh() : v.occupancy());
         b.ntiles += (int64_t)gr.tiles.size();
-    }
-    // zeroing tiles: 32 rows each
-    if (b.zero) {
-        for (size_t n = 0; n < b.grids.size(); ++n) {
-            const kl_grid_t *g = &b.grids[n];
-            const int rows = g->jtot * g->ktot;
-            for (int r0 = 0; r0 < rows; r0 += 32)
-                b.ztiles[g->dtype].push_back(make_int4((int)n, r0, std::min(rows, r0 + 32), 0));
-        }
-        for (int d = 0; d < 2; ++d) {
-            if (b.ztiles[d].empty()) continue;
-            if ((e = upload(&b.d_ztiles[d], b.ztiles[d].data(), b.ztiles[d].size() * sizeof(int4))) != hipSuccess)
-                return hip_fail(e, "zero tiles");
-            b.zblocks[d] = (int)std::min<int64_t>((int64_t)b.ztiles[d].size(), (int64_t)ncu * 8);
-        }
     }
     // ghost fill and conservation-sum jobs, one per grid
     if (b.flags & KL_BATCH_FILL_GHOSTS) {
@@ -455,16 +424,11 @@ int build(Batch &b, void *const *fields)
         if (e != hipSuccess) rc = hip_fail(e, "fill launch");
         ++b.nkernels;
     }
-    for (int d = 0; d < 2 && rc == KL_OK; ++d) {
-        if (!b.zero || b.ztiles[d].empty()) continue;
-        e = launch_zero_batch(d, b.d_desc[d], b.d_ztiles[d], (int)b.ztiles[d].size(), b.zblocks[d], cs);
-        if (e != hipSuccess) rc = hip_fail(e, "zero launch");
-        ++b.nkernels;
-    }
     for (Group &gr : b.groups) {
         if (rc != KL_OK) break;
         const Variant &v = variants(gr.kernel, gr.dtype)[gr.variant];
-        e = v.batch(b.d_desc[gr.dtype], gr.d_tiles, (int)gr.tiles.size(), gr.nblocks, gr.d_queue, cs);
+        e = (b.zero ? v.batch_fresh : v.batch)(b.d_desc[gr.dtype], gr.d_tiles, (int)gr.tiles.size(), gr.nblocks,
+                                               gr.d_queue, cs);
         if (e != hipSuccess) rc = hip_fail(e, v.name);
         ++b.nkernels;
     }

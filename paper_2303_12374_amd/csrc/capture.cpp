@@ -300,6 +300,15 @@ int maybe_capture(const kl_grid_t *g, int kernel, void *const *fields, double vi
     return write_capture(g, kernel, fields, visc, dt, s, c.dir + name);
 }
 
+bool capture_pending(const kl_grid_t *g, int kernel)
+{
+    CaptureState &c = cap_state();
+    std::lock_guard<std::mutex> lk(c.mu);
+    init_from_env(c);
+    if (c.kernels.empty() || !c.kernels.count(kernel_name(kernel))) return false;
+    return !c.done.count(std::make_tuple(kernel, (int)g->dtype, (int)g->itot, (int)g->jtot, (int)g->ktot));
+}
+
 }  // namespace kl
 
 using namespace kl;

@@ -60,6 +60,11 @@ struct Variant {
     LaunchFn launch;
     BatchFn batch;  // persistent tile-list form (LDS z-march family only), else null
     OccFn occupancy;
+    // advec_diff only: the same configuration onto tendencies that start at
+    // zero and are not read (FUSE_FRESH), and its persistent form
+    LaunchFn fresh = nullptr;
+    BatchFn batch_fresh = nullptr;
+    OccFn occupancy_fresh = nullptr;
 };
 
 // Registry (index 0 of every list is the default configuration).
@@ -115,9 +120,6 @@ void append_sum_job(const HostArgs &a, const void *ut, const void *vt, const voi
 hipError_t launch_sums_batch(int dtype, bool vec, const void *jobs, const void *blocks, int nblocks, double *partials,
                              hipStream_t s);
 hipError_t launch_sums_finish(const void *slots, const double *partials, int nslots, double *out, hipStream_t s);
-// Batched row-tile kernels: descs = StencilArgs<T>[], tiles = int4 {grid, row0, row1, 0}[].
-hipError_t launch_zero_batch(int dtype, const void *descs, const void *tiles, int ntiles, int nblocks,
-                             hipStream_t s);
 // Configuration of grid g for `kernel` in batched (persistent) form, or -1.
 int batch_variant(const kl_grid_t *g, int kernel, void *const f[6]);
 // Regroup grids (6 field pointers each) for fewer persistent kernels: see batch.hip.
@@ -141,11 +143,13 @@ std::string provenance_json(const DeviceIdent &dev);
 // Plan cache (api.cpp).
 int select_variant(const kl_grid_t *g, int kernel);
 int run_variant(const kl_grid_t *g, int kernel, int index, void *const *fields, double visc,
-                hipStream_t s, double dt = 0.0);
+                hipStream_t s, double dt = 0.0, bool fresh = false);
 void clear_plans();
 
 // Capture (capture.cpp): write the launch to a capture file if its kernel is
 // named in KL_CAPTURE / kl_set_capture and its problem size is new.
 int maybe_capture(const kl_grid_t *g, int kernel, void *const *fields, double visc, double dt, hipStream_t s);
+// Whether the next launch of `kernel` at this problem size would be captured.
+bool capture_pending(const kl_grid_t *g, int kernel);
 
 }  // namespace kl

@@ -458,25 +458,4 @@ __global__ __launch_bounds__(64 * BY, WPE) void advec_u_zl_batch(const StencilAr
     walk_done(queue);
 }
 
-// Batched zeroing of the tendencies: tile = (grid, first row, end row) over
-// the rows (j, k) of the interior, rows numbered j-1 + jtot*(k-1).
-template <typename T>
-__global__ __launch_bounds__(256) void zero_tendencies_batch(const StencilArgs<T> *__restrict__ grids,
-                                                            const int4 *__restrict__ tiles, int ntiles)
-{
-    for (int n = blockIdx.x; n < ntiles; n += gridDim.x) {
-        const int4 tl = tiles[n];
-        const StencilArgs<T> a = global_args(grids[tl.x]);
-        for (int r = tl.y; r < tl.z; ++r) {
-            const int j = 1 + r % a.jtot, k = 1 + r / a.jtot;
-            const int64_t base = a.off + (int64_t)j * a.js + (int64_t)k * a.ks;
-            for (int i = 1 + (int)threadIdx.x; i <= a.itot; i += 256) {
-                a.ut[base + i] = T(0);
-                a.vt[base + i] = T(0);
-                a.wt[base + i] = T(0);
-            }
-        }
-    }
-}
-
 }  // namespace kl

@@ -67,6 +67,20 @@ hipError_t launch_plain(const HostArgs &h, hipStream_t s)
     return hipGetLastError();
 }
 
+// The default configuration of the fused pass onto tendencies that start at zero.
+template <typename T>
+hipError_t launch_plain_fresh(const HostArgs &h, hipStream_t s)
+{
+    StencilArgs<T> a = device_args<T>(h);
+    a.nbx = (int)cdivu(h.itot, 256);
+    a.nby = h.jtot;
+    a.nbz = h.ktot;
+    const uint64_t nb = (uint64_t)a.nbx * a.nby * a.nbz;
+    if (!grid_fits(nb, 256)) return hipErrorInvalidConfiguration;
+    hipLaunchKernelGGL((advec_diff_plain<T, true>), dim3((unsigned)nb), dim3(256), 0, s, a);
+    return hipGetLastError();
+}
+
 template <typename T, int KERNEL, int VX, int BX, int BY, int KB, int XCD, int NT = 0, int WPE = 1>
 hipError_t launch_zc(const HostArgs &h, hipStream_t s)
 {
@@ -324,7 +338,10 @@ hipError_t launch_smag_zl(const HostArgs &h, hipStream_t s)
     Variant{"ad_v" KL_STR(VX) "_b64x" KL_STR(BY) "_k" KL_STR(KB) "_x" KL_STR(XCD) "_nt" KL_STR(NT),      \
             KL_KERNEL_ADVEC_DIFF, DT, FAMILY_ZL, VX, 64, BY, KB, XCD,                                    \
             &launch_step<T, VX, BY, KB, XCD, NT, 1, FUSE_PAIR>, &launch_step_batch<T, VX, BY, KB, NT, 1, FUSE_PAIR>, \
-            &step_batch_occupancy<T, VX, BY, KB, NT, 1, FUSE_PAIR>}
+            &step_batch_occupancy<T, VX, BY, KB, NT, 1, FUSE_PAIR>,                                       \
+            &launch_step<T, VX, BY, KB, XCD, NT, 1, FUSE_PAIR | FUSE_FRESH>,                              \
+            &launch_step_batch<T, VX, BY, KB, NT, 1, FUSE_PAIR | FUSE_FRESH>,                             \
+            &step_batch_occupancy<T, VX, BY, KB, NT, 1, FUSE_PAIR | FUSE_FRESH>}
 
 #define KL_ADW(T, DT, VX, BY, KB, XCD, NT, WPE, MODE, TAG)                                               \
     Variant{"ad_v" KL_STR(VX) "_b64x" KL_STR(BY) "_k" KL_STR(KB) "_x" KL_STR(XCD) "_nt" KL_STR(NT)       \
@@ -332,7 +349,10 @@ hipError_t launch_smag_zl(const HostArgs &h, hipStream_t s)
             KL_KERNEL_ADVEC_DIFF, DT, FAMILY_ZL, VX, 64, BY, KB, XCD,                                    \
             &launch_step<T, VX, BY, KB, XCD, NT, WPE, FUSE_PAIR | (MODE)>,                                \
             &launch_step_batch<T, VX, BY, KB, NT, WPE, FUSE_PAIR | (MODE)>,                               \
-            &step_batch_occupancy<T, VX, BY, KB, NT, WPE, FUSE_PAIR | (MODE)>}
+            &step_batch_occupancy<T, VX, BY, KB, NT, WPE, FUSE_PAIR | (MODE)>,                            \
+            &launch_step<T, VX, BY, KB, XCD, NT, WPE, FUSE_PAIR | FUSE_FRESH | (MODE)>,                   \
+            &launch_step_batch<T, VX, BY, KB, NT, WPE, FUSE_PAIR | FUSE_FRESH | (MODE)>,                  \
+            &step_batch_occupancy<T, VX, BY, KB, NT, WPE, FUSE_PAIR | FUSE_FRESH | (MODE)>}
 
 #define KL_AD_SET(T, DT, VX)                                                                             \
     KL_AD(T, DT, VX, 4, 8, 0, 0), KL_AD(T, DT, VX, 8, 8, 0, 0), KL_AD(T, DT, VX, 4, 32, 0, 0),           \

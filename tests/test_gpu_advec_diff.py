@@ -169,3 +169,47 @@ def test_full_size_selected_equals_separate(shape):
             del x
     finally:
         m.kl_set_wisdom_dir(None)
+
+
+@pytest.mark.parametrize("shape", [(256, 21, 19), (70, 9, 11)], ids=lambda s: "x".join(map(str, s)))
+@pytest.mark.parametrize("bc", [0, 1, 2], ids=["zerograd", "nopen", "zperiodic"])
+@pytest.mark.parametrize("dtype", [0, 1], ids=["f32", "f64"])
+def test_step_from_zero_bitwise_equals_the_separate_calls(dtype, bc, shape, tmp_path):
+    """kl_step starts its tendencies at zero inside the fused pass: for every
+    advec_diff configuration (forced by a wisdom record), with NaN in the
+    tendencies before the call, the state and the tendencies are bitwise
+    those of zeroed arrays, kl_advec_u, kl_diff_uvw and kl_euler, and nothing
+    outside the interior of a tendency is written."""
+    import json
+    m = kl()
+    g = m.Grid(*shape, dtype=dtype, bc=bc)
+    f = [g.full() for _ in range(3)]
+    m.kl_generate_fields(g, 8, *f)
+    m.kl_fill_ghosts(g, *f)
+    visc, dt = 1e-3, 2e-3
+    rf = [x.clone() for x in f]
+    rt = [g.zeros_interior(fill=-5.0) for _ in range(3)]
+    m.kl_advec_u(g, rt[0], *rf)
+    m.kl_diff_uvw(g, *rt, *rf, visc)
+    m.kl_euler(g, dt, *rf, *rt)
+    ran = 0
+    try:
+        for i in range(m.kl_num_variants(m.ADVEC_DIFF, dtype)):
+            rec = {"kernel": "advec_diff", "dtype": "f32" if dtype == 0 else "f64", "problem_size": list(shape),
+                   "variant": m.kl_variant_name(m.ADVEC_DIFF, dtype, i), "device": "forced", "arch": "gfx950",
+                   "time_ms": 1.0}
+            (tmp_path / "advec_diff.wisdom").write_text(json.dumps(rec) + "\n")
+            m.kl_set_wisdom_dir(str(tmp_path))
+            if m.kl_selected_variant(g, m.ADVEC_DIFF) != i:
+                continue
+            x = [a.clone() for a in f]
+            t = [g.full(-5.0) for _ in range(3)]
+            for a in t:
+                g.interior(a).fill_(float("nan"))
+            m.kl_step(g, visc, dt, *x, *t)
+            for a, b in zip(x + t, rf + rt):
+                assert np.array_equal(a.cpu().numpy(), b.cpu().numpy(), equal_nan=True), rec["variant"]
+            ran += 1
+    finally:
+        m.kl_set_wisdom_dir(None)
+    assert ran > 4
