@@ -315,7 +315,11 @@ int kl_launch_variant_dt(const kl_grid_t *g, int32_t kernel, int32_t index,
 
 /* Index of the configuration kl_advec_u / kl_diff_uvw would run for this
  * grid on the current device (consults the wisdom files on first use per
- * problem size and caches the choice). */
+ * problem size and caches the choice).  Where the heuristic of
+ * kl_wisdom_lookup finds only records of other problem sizes, the second-order
+ * kernels and the fused step run a configuration that sizes itself to the
+ * grid ("rf_t256") on grids of 2^19 points or more (the fused step on all)
+ * whose rows it takes, else the nearest record's. */
 int kl_selected_variant(const kl_grid_t *g, int32_t kernel);
 
 /* ---- tuning and wisdom (Sections "Kernel Tuning", "Wisdom Files",

@@ -88,6 +88,9 @@ HostArgs make_args(const kl_grid_t *g)
 
 bool variant_eligible(const Variant &v, const kl_grid_t *g, const void *const *ptrs, int nptr)
 {
+    if (v.family == FAMILY_RF)  // any alignment; rows that fit a block, 32-bit offsets inside a level
+        return rf_chunks(g->itot, v.vx) <= rf_max_chunks(v.bx) &&
+               g->jstride * ((int64_t)g->jtot + 2) * (g->dtype == KL_F32 ? 4 : 8) < ((int64_t)1 << 31);
     if (v.vx > 1) {
         const int64_t vx = v.vx;
         if (g->itot % vx || (g->off + 1) % vx || g->jstride % vx || g->kstride % vx) return false;
@@ -136,6 +139,26 @@ void clear_plans()
     g_plans.clear();
 }
 
+namespace {
+// The configuration of a problem size that no record names, where the nearest
+// record's is fixed for another size: the row-flattened tile with 256 threads
+// sizes itself to the grid.  Over 42 tuned sizes and four kernels, each left
+// out in turn, it is 0.9% from the fastest in the mean and 13% at worst, the
+// nearest record's 7% and 95%.  Below 2^19 points the launches count and the
+// one-thread-per-point default is as fast or faster (64^3 FP32 diff_uvw 6.8
+// against 7.6 us; 80^3 9.9 against 8.8), the fused step excepted, which has
+// none.  Longer rows (more than 80 chunks) take the nearest record's: with 512
+// threads the row-flattened tile is up to 48% from the fastest there.
+int unrecorded_variant(const kl_grid_t *g, int kernel)
+{
+    if (kernel != KL_KERNEL_STEP && (int64_t)g->itot * g->jtot * g->ktot < ((int64_t)1 << 19)) return -1;
+    const auto &vs = variants(kernel, g->dtype);
+    for (size_t n = 0; n < vs.size(); ++n)
+        if (vs[n].family == FAMILY_RF && vs[n].bx == 256 && variant_eligible(vs[n], g, nullptr, 0)) return (int)n;
+    return -1;
+}
+}  // namespace
+
 int select_variant(const kl_grid_t *g, int kernel)
 {
     int dev = 0;
@@ -151,12 +174,15 @@ int select_variant(const kl_grid_t *g, int kernel)
     if (current_device_ident(&id) == KL_OK) {
         std::string name;
         int level = 5;
-        if (wisdom_select(wisdom_dir(), kernel, g->dtype, id, g->itot, g->jtot, g->ktot, &name, &level) ==
+        bool same_size = false;
+        if (wisdom_select(wisdom_dir(), kernel, g->dtype, id, g->itot, g->jtot, g->ktot, &name, &level, &same_size) ==
                 KL_OK &&
             level < 5) {
             const auto &vs = variants(kernel, g->dtype);
             for (size_t n = 0; n < vs.size(); ++n)
                 if (name == vs[n].name) index = (int)n;
+            const int own = same_size ? -1 : unrecorded_variant(g, kernel);
+            if (own >= 0) index = own;
         }
     }
     std::lock_guard<std::mutex> lk(g_plan_mu);
@@ -203,8 +229,11 @@ int check_ptrs(const void *const *p, int n)
     return KL_OK;
 }
 
-// Launch `kernel` with the selected configuration, falling back to the
-// default when the selected one does not fit this call's alignment.
+// Launch `kernel` with the selected configuration.  When it does not fit this
+// call's rows or alignment, a row-flattened configuration takes its place,
+// which takes any (stencil_rf.hpp: 301x203x151 FP32 advec_u 65 us in the
+// default configuration, 32 row-flattened; FP64 diff_uvw 265 and 111), and
+// the default only on rows too long for one.
 int launch_selected(const kl_grid_t *g, int kernel, void *const *fields, double visc, hipStream_t s,
                     double dt = 0.0, bool fresh = false)
 {
@@ -212,7 +241,11 @@ int launch_selected(const kl_grid_t *g, int kernel, void *const *fields, double 
     const auto &vs = variants(kernel, g->dtype);
     const void *const *ptrs = (const void *const *)fields;
     const int nptr = kernel_nptr(kernel);
-    if (!variant_eligible(vs[index], g, ptrs, nptr)) index = 0;
+    if (!variant_eligible(vs[index], g, ptrs, nptr)) {
+        index = 0;
+        for (size_t n = vs.size(); n-- > 0;)  // the smallest block that fits (registered smallest first)
+            if (vs[n].family == FAMILY_RF && variant_eligible(vs[n], g, ptrs, nptr)) index = (int)n;
+    }
     if (!variant_eligible(vs[index], g, ptrs, nptr))
         return fail(KL_ERR_INVALID, "no configuration of %s fits this grid/alignment", kernel_name(kernel));
     // a capture holds the tendencies a launch accumulates onto

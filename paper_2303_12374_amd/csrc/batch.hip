@@ -118,6 +118,26 @@ struct Batch {
 
 }  // namespace
 
+bool batch_fits(const Variant &v, const kl_grid_t *g, const void *const *ptrs, int nptr)
+{
+    if (!v.batch || !variant_eligible(v, g, ptrs, nptr)) return false;
+    return v.family == FAMILY_RF || 64 * v.vx <= std::max(64, g->itot);
+}
+
+TileShape batch_tiles(const Variant &v, const kl_grid_t *g)
+{
+    TileShape t{64 * v.vx, v.by, v.kb, 1, 1, 1};
+    if (v.family == FAMILY_RF) {
+        t.tw = g->itot;
+        t.by = rf_rows(g->jtot, rf_chunks(g->itot, v.vx), v.bx);
+        t.kb = RF_BATCH_KB;
+    }
+    t.nbx = (int)cdivu(g->itot, t.tw);
+    t.nby = (int)cdivu(g->jtot, t.by);
+    t.nbz = (int)cdivu(g->ktot, t.kb);
+    return t;
+}
+
 // Configuration of grid g for `kernel` in batched form.
 int batch_variant(const kl_grid_t *g, int kernel, void *const f[6])
 {
@@ -126,10 +146,12 @@ int batch_variant(const kl_grid_t *g, int kernel, void *const f[6])
     const int nptr = kernel_nptr(kernel);
     const int sel = select_variant(g, kernel);
     // a selected configuration whose wave segment (64 * vx points) is wider
-    // than the grid's rows would leave most lanes idle: size one to the grid
-    if (vs[sel].batch && variant_eligible(vs[sel], g, ptrs, nptr) && 64 * vs[sel].vx <= std::max(64, g->itot))
-        return sel;
-    // fallback: widest vector that divides itot and does not exceed the row
+    // than the grid's rows would leave most lanes idle
+    if (batch_fits(vs[sel], g, ptrs, nptr)) return sel;
+    // fallback: whole rows, else the widest vector that divides itot and does
+    // not exceed the row
+    for (size_t n = 0; n < vs.size(); ++n)
+        if (vs[n].family == FAMILY_RF && batch_fits(vs[n], g, ptrs, nptr)) return (int)n;
     const int vmax = g->dtype == KL_F32 ? 4 : 2;
     for (int vx = vmax; vx >= 1; vx /= 2) {
         if (g->itot % vx || 64 * vx > std::max(64, g->itot)) continue;
@@ -166,8 +188,7 @@ void merge_batch_groups(int kernel, const std::vector<kl_grid_t> &grids, void *c
             if (placed[n] || g->dtype != dtype) continue;
             void *const *f = fields + 6 * n;
             const void *ptrs[6] = {f[0], f[1], f[2], f[3], f[4], f[5]};
-            if (sel[n] == vi ||
-                (v.batch && 64 * v.vx <= std::max(64, g->itot) && variant_eligible(v, g, ptrs, nptr))) {
+            if (sel[n] == vi || batch_fits(v, g, ptrs, nptr)) {
                 sel[n] = vi;
                 placed[n] = 1;
             }
@@ -177,8 +198,11 @@ void merge_batch_groups(int kernel, const std::vector<kl_grid_t> &grids, void *c
 
 namespace {
 
+// Descriptors of every grid (entries of grids of the other dtype are never
+// referenced); sel[n] is the configuration of grid n.
 template <typename T>
-std::vector<StencilArgs<T>> descriptors(const std::vector<kl_grid_t> &grids, void *const *fields, double visc)
+std::vector<StencilArgs<T>> descriptors(const std::vector<kl_grid_t> &grids, void *const *fields, double visc,
+                                        const std::vector<int> &sel)
 {
     std::vector<StencilArgs<T>> out(grids.size());
     for (size_t n = 0; n < grids.size(); ++n) {
@@ -192,6 +216,7 @@ std::vector<StencilArgs<T>> descriptors(const std::vector<kl_grid_t> &grids, voi
         a.wt = f[5];
         a.visc = visc;
         out[n] = device_args<T>(a);
+        batch_shape(variants(KL_KERNEL_ADVEC_DIFF, grids[n].dtype)[sel[n]], &grids[n], out[n]);
     }
     return out;
 }
@@ -204,13 +229,10 @@ hipError_t upload(void **dst, const void *src, size_t bytes)
     return hipMemcpy(*dst, src, bytes, hipMemcpyHostToDevice);
 }
 
-// Whether configuration v can run grid g in a persistent kernel: it has a
-// persistent form, fits the layout and pointers, and its wave segment (64 vx
-// points) is no wider than the grid's rows.
 bool serves(const Variant &v, const kl_grid_t *g, void *const *f)
 {
     const void *ptrs[6] = {f[0], f[1], f[2], f[3], f[4], f[5]};
-    return v.batch && 64 * v.vx <= std::max(64, g->itot) && variant_eligible(v, g, ptrs, 6);
+    return batch_fits(v, g, ptrs, 6);
 }
 
 // Signature of the grids of one dtype: FNV-1a over their sorted (itot, jtot,
@@ -297,13 +319,6 @@ int build(Batch &b, void *const *fields)
     if (e != hipSuccess) return hip_fail(e, "device properties");
     const int ncu = prop.multiProcessorCount;
 
-    // descriptor tables per dtype (entries of the other dtype are never referenced)
-    {
-        auto df = descriptors<float>(b.grids, fields, b.visc);
-        auto dd = descriptors<double>(b.grids, fields, b.visc);
-        if ((e = upload(&b.d_desc[0], df.data(), df.size() * sizeof(df[0]))) != hipSuccess) return hip_fail(e, "desc");
-        if ((e = upload(&b.d_desc[1], dd.data(), dd.size() * sizeof(dd[0]))) != hipSuccess) return hip_fail(e, "desc");
-    }
     // groups
     std::map<std::tuple<int, int, int>, size_t> gidx;
     {
@@ -320,6 +335,10 @@ int build(Batch &b, void *const *fields)
             if (sel[n] < 0) return fail(KL_ERR_INVALID, "grid %zu: no batched configuration fits", n);
         }
         merge_batch_groups(kernel, b.grids, fields, sel);
+        auto df = descriptors<float>(b.grids, fields, b.visc, sel);
+        auto dd = descriptors<double>(b.grids, fields, b.visc, sel);
+        if ((e = upload(&b.d_desc[0], df.data(), df.size() * sizeof(df[0]))) != hipSuccess) return hip_fail(e, "desc");
+        if ((e = upload(&b.d_desc[1], dd.data(), dd.size() * sizeof(dd[0]))) != hipSuccess) return hip_fail(e, "desc");
         for (size_t n = 0; n < b.grids.size(); ++n) {
             const kl_grid_t *g = &b.grids[n];
             const int vi = sel[n];
@@ -335,14 +354,13 @@ int build(Batch &b, void *const *fields)
             }
             Group &gr = b.groups[it->second];
             const Variant &v = variants(kernel, g->dtype)[vi];
-            const int tw = 64 * v.vx;
-            const int nbx = (int)cdivu(g->itot, tw), nby = (int)cdivu(g->jtot, v.by), nbz = (int)cdivu(g->ktot, v.kb);
-            for (int tz = 0; tz < nbz; ++tz)
-                for (int ty = 0; ty < nby; ++ty)
-                    for (int tx = 0; tx < nbx; ++tx) {
+            const TileShape t = batch_tiles(v, g);
+            for (int tz = 0; tz < t.nbz; ++tz)
+                for (int ty = 0; ty < t.nby; ++ty)
+                    for (int tx = 0; tx < t.nbx; ++tx) {
                         gr.tiles.push_back(make_int4((int)n, tx, ty, tz));
-                        gr.cost.push_back((int64_t)std::min(tw, g->itot - tx * tw) *
-                                          std::min(v.by, g->jtot - ty * v.by) * std::min(v.kb, g->ktot - tz * v.kb));
+                        gr.cost.push_back((int64_t)std::min(t.tw, g->itot - tx * t.tw) *
+                                          std::min(t.by, g->jtot - ty * t.by) * std::min(t.kb, g->ktot - tz * t.kb));
                     }
         }
     }

@@ -50,7 +50,7 @@ inline int persistent_blocks(int64_t ntiles, int ncu, int occ)
     return (int)(nb > 0 ? nb : 1);
 }
 
-enum { FAMILY_PLAIN = 0, FAMILY_ZC = 1, FAMILY_ZL = 2 };
+enum { FAMILY_PLAIN = 0, FAMILY_ZC = 1, FAMILY_ZL = 2, FAMILY_RF = 3 };
 
 // One ahead-of-time compiled configuration of a tendency kernel.
 struct Variant {
@@ -71,6 +71,26 @@ struct Variant {
 const std::vector<Variant> &variants(int kernel, int dtype);
 const std::vector<Variant> &variants_f32(int kernel);
 const std::vector<Variant> &variants_f64(int kernel);
+
+// Row-flattened tiles (stencil_rf.hpp): rows of cpr = ceil(itot / vx) chunks,
+// R whole rows per block of at most `threads` threads.  A block also needs a
+// thread for every chunk of its two halo rows, and LDS for RF_PLANES planes of
+// R + 2 rows and a spare chunk per lane: blocks of 256 threads take rows of up
+// to 80 chunks (three rows, 52 KB, three blocks on a CU), blocks of 512 up to
+// 256 (two rows, 122 KB).
+constexpr int RF_PLANES = 7;  // u: 2, v: 2, w: 3
+inline int rf_chunks(int itot, int vx) { return (int)(((int64_t)itot + vx - 1) / vx); }
+inline int rf_max_chunks(int threads) { return threads == 256 ? 80 : 256; }
+inline int rf_rows(int jtot, int cpr, int threads)
+{
+    const int most = threads / cpr < jtot ? threads / cpr : jtot;
+    const int blocks = (jtot + most - 1) / most;
+    return (jtot + blocks - 1) / blocks;  // row blocks of equal height
+}
+inline size_t rf_lds_bytes(int cpr, int R) { return (size_t)RF_PLANES * ((R + 2) * cpr + 64) * 16; }
+constexpr size_t RF_LDS_256 = (size_t)RF_PLANES * (5 * 80 + 64) * 16, RF_LDS_512 = (size_t)RF_PLANES * (4 * 256 + 64) * 16;
+// Levels per tile in the persistent forms, where many grids fill the GPU.
+constexpr int RF_BATCH_KB = 32;
 
 // Errors: record a message for kl_last_error() and return `code`.
 int fail(int code, const char *fmt, ...) __attribute__((format(printf, 2, 3)));
@@ -120,6 +140,16 @@ void append_sum_job(const HostArgs &a, const void *ut, const void *vt, const voi
 hipError_t launch_sums_batch(int dtype, bool vec, const void *jobs, const void *blocks, int nblocks, double *partials,
                              hipStream_t s);
 hipError_t launch_sums_finish(const void *slots, const double *partials, int nslots, double *out, hipStream_t s);
+// Whether configuration v can run grid g in a persistent kernel: it has a
+// persistent form, fits the layout and pointers, and does not leave most of
+// its lanes without a point.
+bool batch_fits(const Variant &v, const kl_grid_t *g, const void *const *ptrs, int nptr);
+// Tiles of grid g under configuration v in a persistent kernel, as
+// {tile width, rows, levels} and their counts per axis.
+struct TileShape {
+    int tw, by, kb, nbx, nby, nbz;
+};
+TileShape batch_tiles(const Variant &v, const kl_grid_t *g);
 // Configuration of grid g for `kernel` in batched (persistent) form, or -1.
 int batch_variant(const kl_grid_t *g, int kernel, void *const f[6]);
 // Regroup grids (6 field pointers each) for fewer persistent kernels: see batch.hip.
@@ -134,8 +164,9 @@ int current_device_ident(DeviceIdent *out);
 std::string wisdom_dir();
 std::string wisdom_path(const std::string &dir, int kernel);
 const char *kernel_name(int kernel);
+// *same_size (if not null): whether the chosen record is of this very problem size.
 int wisdom_select(const std::string &dir, int kernel, int dtype, const DeviceIdent &dev,
-                  int itot, int jtot, int ktot, std::string *variant, int *level);
+                  int itot, int jtot, int ktot, std::string *variant, int *level, bool *same_size = nullptr);
 int wisdom_append(const std::string &dir, int kernel, const std::string &json_line);
 int wisdom_append_file(const std::string &dir, const std::string &file, const std::string &json_line);
 std::string provenance_json(const DeviceIdent &dev);

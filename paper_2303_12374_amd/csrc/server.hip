@@ -264,14 +264,17 @@ struct GpuExec {
             const Req &q = *act[n];
             const int vi = sel[n];
             const Variant &v = variants(KL_KERNEL_STEP, q.g.dtype)[vi];
+            if (q.g.dtype == KL_F32)
+                batch_shape(v, &q.g, df[didx[n]]);
+            else
+                batch_shape(v, &q.g, dd[didx[n]]);
             auto &tl = sized[std::make_tuple(q.g.dtype, vi)];
-            const int tw = 64 * v.vx;
-            const int nbx = (int)cdivu(q.g.itot, tw), nby = (int)cdivu(q.g.jtot, v.by), nbz = (int)cdivu(q.g.ktot, v.kb);
-            for (int tz = 0; tz < nbz; ++tz)
-                for (int ty = 0; ty < nby; ++ty)
-                    for (int tx = 0; tx < nbx; ++tx)
-                        tl.emplace_back((int64_t)std::min(tw, q.g.itot - tx * tw) * std::min(v.by, q.g.jtot - ty * v.by) *
-                                            std::min(v.kb, q.g.ktot - tz * v.kb),
+            const TileShape t = batch_tiles(v, &q.g);
+            for (int tz = 0; tz < t.nbz; ++tz)
+                for (int ty = 0; ty < t.nby; ++ty)
+                    for (int tx = 0; tx < t.nbx; ++tx)
+                        tl.emplace_back((int64_t)std::min(t.tw, q.g.itot - tx * t.tw) *
+                                            std::min(t.by, q.g.jtot - ty * t.by) * std::min(t.kb, q.g.ktot - tz * t.kb),
                                         make_int4(didx[n], tx, ty, tz));
         }
         // the blocks draw tiles from a queue: largest first (stable, so the tiles

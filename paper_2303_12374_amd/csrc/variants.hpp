@@ -6,8 +6,11 @@
 #include "stencil.hpp"
 #include "stencil_zl.hpp"
 #include "stencil_step.hpp"
+#include "stencil_rf.hpp"
 #include "stencil_les.hpp"
 #include "stencil_les_zl.hpp"
+
+#include <algorithm>
 
 namespace kl {
 
@@ -39,6 +42,7 @@ StencilArgs<T> device_args(const HostArgs &h)
     a.w = (const T *)h.w;
     a.nbx = a.nby = a.nbz = 1;
     a.evisc = (const T *)h.evisc;
+    a.rf_cpr = a.rf_rows = a.rf_kb = 0;
     return a;
 }
 
@@ -168,6 +172,64 @@ int step_batch_occupancy()
     const hipError_t e =
         hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, step_zl_batch<T, VX, BY, KB, NT, WPE, MODE>, 64 * BY, 0);
     return e == hipSuccess && n > 0 ? n : 1;
+}
+
+// Row-flattened tiles.  Levels per tile: about 512 tiles (two per CU), at
+// least two levels each; longer marches read less twice, more tiles balance
+// better, and no other power of two was faster by more than 3% at the sizes
+// tried (64^3 .. 320x320x160, odd rows, both types).  Tendencies stream past
+// the caches when the arrays of a call exceed the memory-side cache (256 MB):
+// 301x203x151 FP32 diff_uvw (221 MB) 57 us cached, 60 streamed; 320x320x160
+// (393 MB) 115 cached, 95 streamed.
+template <typename T, int V, int MODE, int THREADS>
+hipError_t launch_rf(const HostArgs &h, hipStream_t s)
+{
+    StencilArgs<T> a = device_args<T>(h);
+    a.rf_cpr = rf_chunks(h.itot, V);
+    a.rf_rows = rf_rows(h.jtot, a.rf_cpr, THREADS);
+    a.nby = (int)cdivu(h.jtot, a.rf_rows);
+    a.rf_kb = std::max(2, (int)cdivu(h.ktot, std::max(1, 512 / a.nby)));
+    a.nbz = (int)cdivu(h.ktot, a.rf_kb);
+    const uint64_t nb = (uint64_t)a.nby * a.nbz;
+    a.nbx = a.nby % 8 == 0 ? a.nby : (int)nb;
+    const int threads = (std::max(a.rf_rows, 2) * a.rf_cpr + 63) / 64 * 64;
+    if (!grid_fits(nb, threads) || threads > THREADS) return hipErrorInvalidConfiguration;
+    const size_t lds = rf_lds_bytes(a.rf_cpr, a.rf_rows);
+    constexpr int arrays = (MODE & RF_DIFF) ? 6 : 4;
+    if ((double)arrays * h.itot * h.jtot * h.ktot * sizeof(T) > 256e6)
+        hipLaunchKernelGGL((rf_kernel<T, V, MODE, 1, THREADS>), dim3((unsigned)nb), dim3(threads), lds, s, a);
+    else
+        hipLaunchKernelGGL((rf_kernel<T, V, MODE, 0, THREADS>), dim3((unsigned)nb), dim3(threads), lds, s, a);
+    return hipGetLastError();
+}
+
+template <typename T, int V, int MODE, int THREADS>
+hipError_t launch_rf_batch(const void *descs, const void *tiles, int ntiles, int nblocks, int *queue, hipStream_t s)
+{
+    hipLaunchKernelGGL((rf_batch<T, V, MODE, 1, THREADS>), dim3(nblocks), dim3(THREADS),
+                       THREADS == 256 ? RF_LDS_256 : RF_LDS_512, s, (const StencilArgs<T> *)descs, (const int4 *)tiles,
+                       ntiles, queue);
+    return hipGetLastError();
+}
+
+template <typename T, int V, int MODE, int THREADS>
+int rf_batch_occupancy()
+{
+    int n = 0;
+    const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, rf_batch<T, V, MODE, 1, THREADS>, THREADS,
+                                                                      THREADS == 256 ? RF_LDS_256 : RF_LDS_512);
+    return e == hipSuccess && n > 0 ? n : 1;
+}
+
+// The row-flattened tile shape of a grid in a persistent kernel of configuration v.
+template <typename T>
+void batch_shape(const Variant &v, const kl_grid_t *g, StencilArgs<T> &a)
+{
+    if (v.family != FAMILY_RF) return;
+    const TileShape t = batch_tiles(v, g);
+    a.rf_cpr = rf_chunks(g->itot, v.vx);
+    a.rf_rows = t.by;
+    a.rf_kb = t.kb;
 }
 
 // diff_uvw as three single-component passes (u, then v, then w) of the LDS
@@ -426,3 +488,42 @@ hipError_t launch_smag_zl(const HostArgs &h, hipStream_t s)
     Variant{"zl3_v" KL_STR(VX) "_b64x" KL_STR(BY) "_k" KL_STR(KB) "_x" KL_STR(XCD) "_nt" KL_STR(NT),       \
             KL_KERNEL_DIFF_UVW, DT, FAMILY_ZL, VX, 64, BY, KB, XCD, &launch_zl_split<T, VX, BY, KB, XCD, NT>, \
             nullptr, nullptr}
+
+// Row-flattened configurations, named rf_t<block threads>; they size their
+// tiles to the grid themselves.
+#define KL_RF(T, DT, KERN, V, MODE, THREADS)                                                                \
+    Variant{"rf_t" KL_STR(THREADS), KERN, DT, FAMILY_RF, V, THREADS, 1, 0, 0, &launch_rf<T, V, MODE, THREADS>, nullptr, \
+            nullptr}
+
+#define KL_RFB(T, DT, KERN, V, MODE, THREADS)                                                               \
+    Variant{"rf_t" KL_STR(THREADS), KERN, DT, FAMILY_RF, V, THREADS, 1, 0, 0, &launch_rf<T, V, MODE, THREADS>, \
+            &launch_rf_batch<T, V, MODE, THREADS>, &rf_batch_occupancy<T, V, MODE, THREADS>,                \
+            &launch_rf<T, V, (MODE) | RF_FRESH, THREADS>, &launch_rf_batch<T, V, (MODE) | RF_FRESH, THREADS>, \
+            &rf_batch_occupancy<T, V, (MODE) | RF_FRESH, THREADS>}
+
+#define KL_RF_SET(T, DT, V)                                                                                 \
+    switch (kernel) {                                                                                       \
+    case KL_KERNEL_ADVEC_U:                                                                                 \
+        out.push_back(KL_RF(T, DT, KL_KERNEL_ADVEC_U, V, RF_ADVEC, 256));                                   \
+        out.push_back(KL_RF(T, DT, KL_KERNEL_ADVEC_U, V, RF_ADVEC, 512));                                   \
+        break;                                                                                              \
+    case KL_KERNEL_DIFF_UVW:                                                                                \
+        out.push_back(KL_RF(T, DT, KL_KERNEL_DIFF_UVW, V, RF_DIFF, 256));                                   \
+        out.push_back(KL_RF(T, DT, KL_KERNEL_DIFF_UVW, V, RF_DIFF, 512));                                   \
+        break;                                                                                              \
+    case KL_KERNEL_ADVEC_DIFF:                                                                              \
+        out.push_back(KL_RFB(T, DT, KL_KERNEL_ADVEC_DIFF, V, RF_ADVEC | RF_DIFF, 256));                     \
+        out.push_back(KL_RFB(T, DT, KL_KERNEL_ADVEC_DIFF, V, RF_ADVEC | RF_DIFF, 512));                     \
+        break;                                                                                              \
+    case KL_KERNEL_STEP:                                                                                    \
+        out.push_back(KL_RFS(T, DT, V, 256));                                                               \
+        out.push_back(KL_RFS(T, DT, V, 512));                                                               \
+        break;                                                                                              \
+    default: break;                                                                                         \
+    }
+
+#define KL_RFS(T, DT, V, THREADS)                                                                           \
+    Variant{"rf_t" KL_STR(THREADS), KL_KERNEL_STEP, DT, FAMILY_RF, V, THREADS, 1, 0, 0,                     \
+            &launch_rf<T, V, RF_ADVEC | RF_DIFF | RF_STEP, THREADS>,                                        \
+            &launch_rf_batch<T, V, RF_ADVEC | RF_DIFF | RF_STEP, THREADS>,                                  \
+            &rf_batch_occupancy<T, V, RF_ADVEC | RF_DIFF | RF_STEP, THREADS>}

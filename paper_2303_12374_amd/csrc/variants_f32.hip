@@ -15,16 +15,19 @@ void add_variants_f32_rev(int kernel, std::vector<Variant> &out);
 void add_variants_f32_les(int kernel, std::vector<Variant> &out);
 void add_variants_f32_split(std::vector<Variant> &out);
 void add_variants_f32_ad(std::vector<Variant> &out);
+void add_variants_f32_rf(int kernel, std::vector<Variant> &out);
 
 static std::vector<Variant> build_f32(int kernel)
 {
     std::vector<Variant> v;
     if (kernel == KL_KERNEL_STEP) {  // index 0: a fused step with scalar lanes (fits any itot)
         add_variants_f32_step(v);
+        add_variants_f32_rf(kernel, v);
         return v;
     }
     if (kernel == KL_KERNEL_ADVEC_DIFF) {
         add_variants_f32_ad(v);
+        add_variants_f32_rf(kernel, v);
         return v;
     }
     if (kernel == KL_KERNEL_ADVEC_U_2I5 || kernel == KL_KERNEL_DIFF_SMAG) {
@@ -48,6 +51,7 @@ static std::vector<Variant> build_f32(int kernel)
         add_variants_f32_small(kernel, v);
         add_variants_f32_rev(kernel, v);
         if (kernel == KL_KERNEL_DIFF_UVW) add_variants_f32_split(v);
+        add_variants_f32_rf(kernel, v);
     return v;
 }
 

@@ -14,16 +14,19 @@ void add_variants_f64_rev(int kernel, std::vector<Variant> &out);
 void add_variants_f64_les(int kernel, std::vector<Variant> &out);
 void add_variants_f64_split(std::vector<Variant> &out);
 void add_variants_f64_ad(std::vector<Variant> &out);
+void add_variants_f64_rf(int kernel, std::vector<Variant> &out);
 
 static std::vector<Variant> build_f64(int kernel)
 {
     std::vector<Variant> v;
     if (kernel == KL_KERNEL_STEP) {  // index 0: a fused step with scalar lanes (fits any itot)
         add_variants_f64_step(v);
+        add_variants_f64_rf(kernel, v);
         return v;
     }
     if (kernel == KL_KERNEL_ADVEC_DIFF) {
         add_variants_f64_ad(v);
+        add_variants_f64_rf(kernel, v);
         return v;
     }
     if (kernel == KL_KERNEL_ADVEC_U_2I5 || kernel == KL_KERNEL_DIFF_SMAG) {
@@ -46,6 +49,7 @@ static std::vector<Variant> build_f64(int kernel)
         add_variants_f64_small(kernel, v);
         add_variants_f64_rev(kernel, v);
         if (kernel == KL_KERNEL_DIFF_UVW) add_variants_f64_split(v);
+        add_variants_f64_rf(kernel, v);
     return v;
 }
 

@@ -124,8 +124,9 @@ int current_device_ident(DeviceIdent *out)
 }
 
 int wisdom_select(const std::string &dir, int kernel, int dtype, const DeviceIdent &dev, int itot, int jtot,
-                  int ktot, std::string *variant, int *level)
+                  int ktot, std::string *variant, int *level, bool *same_size)
 {
+    if (same_size) *same_size = false;
     *level = 5;
     *variant = "default";
     std::ifstream in(wisdom_path(dir, kernel));
@@ -159,6 +160,7 @@ int wisdom_select(const std::string &dir, int kernel, int dtype, const DeviceIde
         if (!choice[l].empty()) {
             *level = l;
             *variant = choice[l];
+            if (same_size) *same_size = best[l] == 0;
             return KL_OK;
         }
     }

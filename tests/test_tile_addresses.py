@@ -364,3 +364,66 @@ def test_model_catches_an_out_of_bounds_halo():
         sp.add(bad, g["k0"], g["k1"], ks)
     with pytest.raises(AssertionError):
         check(sp, alloc, "planted")
+
+
+def rf_spans(itot, jtot, ktot, v, threads, kb, off, js, ks, esize):
+    """Row-flattened tiles: every field access, and every LDS index against
+    its plane."""
+    sp = Span()
+    cpr = -(-itot // v)
+    R = max(1, min(jtot, threads // cpr))
+    plane = lambda R: ((R + 2) * cpr + 64) * v
+    while R > 1 and 7 * plane(R) * esize > 160 * 1024:
+        R -= 1
+    R = -(-jtot // -(-jtot // R))
+    nt = (max(R, 2) * cpr + 63) // 64 * 64
+    assert nt <= 512 and 2 * cpr <= nt and 7 * plane(R) * esize <= 160 * 1024
+    t = np.arange(nt)
+    row_t, c = t // cpr, t % cpr
+    S = v * cpr
+    for ty, tz in itertools.product(range(-(-jtot // R)), range(-(-ktot // kb))):
+        j0, k0 = 1 + ty * R, 1 + tz * kb
+        nv = min(R, jtot - j0 + 1)
+        k1 = min(k0 + kb, ktot + 1)
+        row = np.minimum(row_t, nv - 1)
+        side, halo = t >= cpr, t < 2 * cpr
+        hc = t - side * cpr
+        base = off + (j0 - 1) * js
+        o_own = (row + 1) * js + 1 + c * v
+        o_x = np.where(halo, np.where(side, (nv + 1) * js, 0) + 1 + hc * v, 1)
+        assert o_own.min() >= 0 and o_x.min() >= 0 and (max(o_own.max(), o_x.max()) + v) * esize < 2 ** 32
+        sp.add(base + o_own, k0 - 1, k1, ks, v)           # field ring
+        sp.add(base + o_own, k0, k1, ks, v)               # tendencies (stores: at most the same)
+        sp.add(base + o_x, k0, min(k1 + 1, ktot), ks, v)  # halo rows, never above ktot
+        own = row_t < nv
+        l_own = (row + 1) * S + c * v
+        l_x = np.where(halo, np.where(side, (nv + 1) * S, 0) + hc * v, (R + 2) * S + (t & 63) * v)
+        l_left = (row + 1) * S + np.where(c == 0, itot, c * v) - 1
+        l_right = (row + 1) * S + np.where(c == cpr - 1, 0, (c + 1) * v)
+        for lo, hi in ((l_own - S, l_own + S + v), (l_x, l_x + v), (l_left, l_left + S + 1), (l_right, l_right + 1)):
+            assert lo.min() >= 0 and hi.max() <= plane(R), "row-flattened LDS index outside its plane"
+        # every row the readers use is written: rows 0 and nv+1 by the halo threads, 1..nv by owners
+        assert set((l_own[own] // S).tolist()) == set(range(1, nv + 1))
+        assert set((l_x[halo] // S).tolist()) == {0, nv + 1}
+    return sp
+
+
+RF_SHAPES = SHAPES + [(3, 5, 4), (301, 11, 9), (127, 40, 5), (1023, 3, 3), (48, 300, 3)]
+
+
+@pytest.mark.parametrize("dtype", [0, 1], ids=["f32", "f64"])
+@pytest.mark.parametrize("shape", RF_SHAPES, ids=lambda s: "x".join(map(str, s)))
+def test_row_flattened_tiles_stay_inside_the_fields(shape, dtype):
+    itot, jtot, ktot = shape
+    ran = 0
+    for gc in (1, 3):
+        for off, js, ks, alloc in layouts(itot, jtot, ktot, dtype, gc):
+            for threads, kb in itertools.product((256, 512), (1, 2, 4, 8, 16, 64)):
+                v = 4 if dtype == 0 else 2
+                cpr = -(-itot // v)
+                if 2 * cpr > threads:
+                    continue
+                sp = rf_spans(itot, jtot, ktot, v, threads, kb, off, js, ks, 4 if dtype == 0 else 8)
+                check(sp, alloc, f"rf {shape} gc={gc} layout=({off},{js},{ks}) threads={threads} kb={kb}")
+                ran += 1
+    assert ran > 0 or itot > 512
