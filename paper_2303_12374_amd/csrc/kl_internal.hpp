@@ -92,6 +92,20 @@ constexpr size_t RF_LDS_256 = (size_t)RF_PLANES * (5 * 80 + 64) * 16, RF_LDS_512
 // Levels per tile in the persistent forms, where many grids fill the GPU.
 constexpr int RF_BATCH_KB = 32;
 
+// Row-flattened tiles of the paper's schemes (stencil_les_rf.hpp): rows cut into
+// the fewest segments of at most 64 (advec_u_2i5; 60 of two points) or 48
+// (diff_smag) chunks, W each, and R rows, so that the block's chunks, the
+// chunks around it (one per thread) and the LDS fit a block of 512 threads.
+struct LesRfShape {
+    int W, R, threads;
+    size_t lds;
+};
+LesRfShape les_rf_shape(int kernel, int itot, int jtot, int vx);
+// Levels per tile of `slab` tiles per level slab: the fewest rounds of 256
+// tiles (one block per CU) times levels, a tile costing about five levels
+// more than it computes (its prologue and its end).
+int les_rf_levels(int slab, int ktot);
+
 // Errors: record a message for kl_last_error() and return `code`.
 int fail(int code, const char *fmt, ...) __attribute__((format(printf, 2, 3)));
 int hip_fail(hipError_t e, const char *what);

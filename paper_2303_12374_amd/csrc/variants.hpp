@@ -9,6 +9,7 @@
 #include "stencil_rf.hpp"
 #include "stencil_les.hpp"
 #include "stencil_les_zl.hpp"
+#include "stencil_les_rf.hpp"
 
 #include <algorithm>
 
@@ -219,6 +220,38 @@ int rf_batch_occupancy()
     const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, rf_batch<T, V, MODE, 1, THREADS>, THREADS,
                                                                       THREADS == 256 ? RF_LDS_256 : RF_LDS_512);
     return e == hipSuccess && n > 0 ? n : 1;
+}
+
+// The paper's schemes; tendencies are streamed past the memory-side cache where
+// a call's arrays do not fit it (256 MB), as in launch_rf.
+template <typename T, int V, int KERNEL>
+hipError_t launch_les_rf(const HostArgs &h, hipStream_t s)
+{
+    StencilArgs<T> a = device_args<T>(h);
+    const LesRfShape sh = les_rf_shape(KERNEL, h.itot, h.jtot, V);
+    a.rf_cpr = sh.W;
+    a.rf_rows = sh.R;
+    a.nbx = (int)cdivu(rf_chunks(h.itot, V), sh.W);
+    a.nby = (int)cdivu(h.jtot, sh.R);
+    a.rf_kb = les_rf_levels(a.nbx * a.nby, h.ktot);
+    a.nbz = (int)cdivu(h.ktot, a.rf_kb);
+    const uint64_t nb = (uint64_t)a.nbx * a.nby * a.nbz;
+    if (!grid_fits(nb, sh.threads) || sh.threads > 512) return hipErrorInvalidConfiguration;
+    constexpr int arrays = KERNEL == KL_KERNEL_ADVEC_U_2I5 ? 4 : 7;
+    const bool nt = (double)arrays * h.itot * h.jtot * h.ktot * sizeof(T) > 256e6;
+    const dim3 grid((unsigned)nb), block(sh.threads);
+    if (KERNEL == KL_KERNEL_ADVEC_U_2I5) {
+        if (nt)
+            hipLaunchKernelGGL((advec_u_2i5_rf<T, V, 1>), grid, block, sh.lds, s, a);
+        else
+            hipLaunchKernelGGL((advec_u_2i5_rf<T, V, 0>), grid, block, sh.lds, s, a);
+    } else {
+        if (nt)
+            hipLaunchKernelGGL((diff_smag_rf<T, V, 1>), grid, block, sh.lds, s, a);
+        else
+            hipLaunchKernelGGL((diff_smag_rf<T, V, 0>), grid, block, sh.lds, s, a);
+    }
+    return hipGetLastError();
 }
 
 // The row-flattened tile shape of a grid in a persistent kernel of configuration v.
@@ -501,6 +534,9 @@ hipError_t launch_smag_zl(const HostArgs &h, hipStream_t s)
             &launch_rf<T, V, (MODE) | RF_FRESH, THREADS>, &launch_rf_batch<T, V, (MODE) | RF_FRESH, THREADS>, \
             &rf_batch_occupancy<T, V, (MODE) | RF_FRESH, THREADS>}
 
+#define KL_RFL(T, DT, KERN, V)                                                                              \
+    Variant{"rf_t512", KERN, DT, FAMILY_RF, V, 512, 1, 0, 0, &launch_les_rf<T, V, KERN>, nullptr, nullptr}
+
 #define KL_RF_SET(T, DT, V)                                                                                 \
     switch (kernel) {                                                                                       \
     case KL_KERNEL_ADVEC_U:                                                                                 \
@@ -519,6 +555,8 @@ hipError_t launch_smag_zl(const HostArgs &h, hipStream_t s)
         out.push_back(KL_RFS(T, DT, V, 256));                                                               \
         out.push_back(KL_RFS(T, DT, V, 512));                                                               \
         break;                                                                                              \
+    case KL_KERNEL_ADVEC_U_2I5: out.push_back(KL_RFL(T, DT, KL_KERNEL_ADVEC_U_2I5, V)); break;              \
+    case KL_KERNEL_DIFF_SMAG: out.push_back(KL_RFL(T, DT, KL_KERNEL_DIFF_SMAG, V)); break;                  \
     default: break;                                                                                         \
     }
 

@@ -36,6 +36,7 @@ static std::vector<Variant> build_f32(int kernel)
                                                             : &launch_plain<float, KL_KERNEL_DIFF_SMAG>,
                             nullptr, nullptr});
         add_variants_f32_les(kernel, v);
+        add_variants_f32_rf(kernel, v);
         return v;
     }
     v.push_back(Variant{"default", kernel, KL_F32, FAMILY_PLAIN, 1, 256, 1, 1, 0,

@@ -35,6 +35,7 @@ static std::vector<Variant> build_f64(int kernel)
                                                             : &launch_plain<double, KL_KERNEL_DIFF_SMAG>,
                             nullptr, nullptr});
         add_variants_f64_les(kernel, v);
+        add_variants_f64_rf(kernel, v);
         return v;
     }
     v.push_back(Variant{"default", kernel, KL_F64, FAMILY_PLAIN, 1, 256, 1, 1, 0,

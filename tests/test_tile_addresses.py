@@ -427,3 +427,117 @@ def test_row_flattened_tiles_stay_inside_the_fields(shape, dtype):
                 check(sp, alloc, f"rf {shape} gc={gc} layout=({off},{js},{ks}) threads={threads} kb={kb}")
                 ran += 1
     assert ran > 0 or itot > 512
+
+
+def les_rf_shape(itot, jtot, v, kernel, esize):
+    """Segment width (chunks), rows, threads and LDS bytes of the row-flattened
+    tiles of advec_u_2i5 (kernel "a5") and diff_smag ("s2")."""
+    cpr = -(-itot // v)
+    wmax = (64 if v == 4 else 60) if kernel == "a5" else 48
+    W = cpr
+    if cpr > wmax:
+        nsx = -(-cpr // wmax)
+        if -(-cpr // 32) * 32 - cpr <= cpr // 32:
+            W = 64 if wmax == 64 and cpr % 64 == 0 else 32
+        else:
+            W = -(-cpr // nsx)
+        if kernel != "a5" and nsx > 2:
+            W = -(-W // 8) * 8
+    hc = 4 // v
+    if kernel == "a5":
+        extra = lambda R: 6 * W + 2 * hc * (R + 6) + W + 2 * R + 1
+        lds = lambda R: 2 * ((R + 6) * (W * v + 8) + (2 * R + 1) * (W + 1) * v + 64 * v) * esize
+    else:
+        extra = lambda R: 8 * W + 8 * (R + 2)
+        lds = lambda R: 3 * (4 * (R + 2) * (W + 2) * v + 64 * v) * esize
+    R = min(jtot, 512 // W)
+    while R > 1 and (extra(R) > 512 or lds(R) > 160 * 1024):
+        R -= 1
+    R = -(-jtot // -(-jtot // R))
+    nt = (max(R * W, extra(R)) + 63) // 64 * 64
+    assert extra(R) <= nt <= 512 and lds(R) <= 160 * 1024
+    return W, R, nt
+
+
+def les_rf_spans(itot, jtot, ktot, v, kernel, kb, off, js, ks, esize, gc):
+    sp = Span()
+    W, R, nt = les_rf_shape(itot, jtot, v, kernel, esize)
+    cpr = -(-itot // v)
+    hc = 4 // v
+    t = np.arange(nt)
+    for sx, ty, tz in itertools.product(range(-(-cpr // W)), range(-(-jtot // R)), range(-(-ktot // kb))):
+        i0w = 1 + sx * W * v
+        width = min(W * v, itot - i0w + 1)
+        Wl = -(-width // v)
+        last = i0w + width > itot
+        j0, k0 = 1 + ty * R, 1 + tz * kb
+        nv, k1 = min(R, jtot - j0 + 1), min(k0 + kb, ktot + 1)
+        row_t, c_t = t // W, t % W
+        row, c = np.minimum(row_t, nv - 1), np.minimum(c_t, Wl - 1)
+        own = (row_t < nv) & (c_t < Wl)
+        assert len(set(zip(row[own].tolist(), c[own].tolist()))) == nv * Wl, "a chunk without a thread"
+        left = lambda n: (itot + 1 if i0w == 1 else i0w) - n
+        right = i0w + Wl * v - (itot if last else 0)
+        o_own = row * js + i0w + c * v
+        assert o_own.min() >= 0 and (o_own.max() + v) * esize < 2 ** 32
+        base = off + j0 * js
+        x = []  # (row, column, level shift, LDS index, kind)
+        if kernel == "a5":
+            SU, SV = W * v + 8, (W + 1) * v
+            oV, oW = (R + 6) * SU, (R + 6) * SU + (R + 1) * SV
+            PB = oW + R * SV + 64 * v
+            for h in range(6):
+                rho = h if h < 3 else nv + h
+                x += [(rho - 3, i0w + q * v, 0, rho * SU + 4 + q * v) for q in range(Wl)]
+            for rho in range(nv + 6):
+                for s in range(2 * hc):
+                    x.append((rho - 3, left(4) + s * v if s < hc else right + (s - hc) * v, 0,
+                              rho * SU + (s * v if s < hc else 4 + Wl * v + (s - hc) * v)))
+            x += [(nv, i0w + q * v, 0, oV + nv * SV + v + q * v) for q in range(Wl)]
+            x += [(r, left(v), 0, oV + r * SV) for r in range(nv + 1)]
+            x += [(r, left(v), 1, oW + r * SV) for r in range(nv)]
+            lu, lv = (row + 3) * SU + 4 + c * v, oV + row * SV + v + c * v
+            lo, hi = min((lu - 3 * SU).min(), (lu - 4).min(), (lv - 1).min()), max((lu + 3 * SU + v).max(),
+                                                                                   (lu + v + 4).max(),
+                                                                                   (lv + SV + v).max(),
+                                                                                   (lv + oW - oV + v).max())
+            sp.add(base + o_own, max(k0 - 3, 0), min(max(k1 + 4, k0 + 4), ktot + 1), ks, v)   # window
+            sp.add(base + o_own, k0, k1, ks, v)                                               # v, w, ut
+            sp.add(base + row * js + np.where(i0w + c * v == 1, itot, i0w + c * v - 1), k0, k0, ks)
+            for r, col, up, _ in x:
+                sp.add(base + r * js + col, k0 + up, k1 - 1 + up, ks, v)
+        else:
+            SW = (W + 2) * v
+            FP = (R + 2) * SW
+            PB = 4 * FP + 64 * v
+            for f in range(4):
+                for rho in (0, nv + 1):
+                    x += [(rho - 1, i0w + q * v, 0, f * FP + rho * SW + v + q * v) for q in range(Wl)]
+                for rho in range(nv + 2):
+                    x.append((rho - 1, left(v), 0, f * FP + rho * SW))
+                    x.append((rho - 1, right, 0, f * FP + rho * SW + v + Wl * v))
+            l = (row + 1) * SW + v + c * v
+            lo, hi = (l - SW - 1).min(), (l + 3 * FP + SW + v + 1).max()
+            sp.add(base + o_own, k0 - 1, max(k0 + 1, k1), ks, v)
+            for r, col, _, _ in x:
+                top = ktot if r == nv else ktot + 1
+                sp.add(base + r * js + col, k0 - 1, min(max(k0 + 1, k1), top), ks, v)
+        assert lo >= 0 and hi <= PB
+        assert len(x) <= nt
+        pos = [e[3] for e in x]
+        assert min(pos) >= 0 and max(pos) + v <= PB - 64 * v and len(set(pos)) == len(pos)
+    return sp
+
+
+@pytest.mark.parametrize("dtype", [0, 1], ids=["f32", "f64"])
+@pytest.mark.parametrize("shape", [(8, 3, 2), (9, 5, 4), (33, 7, 5), (65, 4, 7), (130, 5, 11), (192, 40, 9), (260, 6, 9),
+                                   (301, 70, 5), (32, 300, 4), (1000, 9, 3)], ids=lambda s: "x".join(map(str, s)))
+def test_row_flattened_les_tiles_stay_inside_the_fields(shape, dtype):
+    itot, jtot, ktot = shape
+    v, es = (4, 4) if dtype == 0 else (2, 8)
+    for kernel, gcs in (("a5", (3,)), ("s2", (1, 3))):
+        for gc in gcs:
+            for off, js, ks, alloc in layouts(itot, jtot, ktot, dtype, gc):
+                for kb in (2, 3, 8, 64):
+                    sp = les_rf_spans(itot, jtot, ktot, v, kernel, kb, off, js, ks, es, gc)
+                    check(sp, alloc, f"{kernel} rf {shape} gc={gc} layout=({off},{js},{ks}) kb={kb}")
