@@ -374,6 +374,22 @@ RedPlan red_plan(const HostArgs &a)
     return p;
 }
 
+// FP64 conservation sums: partials, vector width and threads per block (those
+// of the slots that own rows).
+bool sum_rows_aligned(const HostArgs &a, const void *f0, const void *f1, const void *f2)
+{
+    return a.itot % 2 == 0 && (a.off + 1) % 2 == 0 && a.js % 2 == 0 && a.ks % 2 == 0 &&
+           ((uintptr_t)f0 | (uintptr_t)f1 | (uintptr_t)f2) % 16 == 0;
+}
+int sum_rows_blocks(const HostArgs &a) { return (int)std::min<int64_t>(RB, (int64_t)a.jtot * a.ktot); }
+int sum_rows_threads(const HostArgs &a, int V)
+{
+    const int cpr = a.itot / V;
+    if (cpr >= RT) return RT;
+    const int64_t slots = ((int64_t)a.jtot * a.ktot + RB - 1) / RB;
+    return (int)(std::min<int64_t>(RT / cpr, slots) * cpr + 63) / 64 * 64;
+}
+
 // Reduce acc over the block's NT threads; thread q < NQ writes value q to
 // out[q * stride].
 template <int WHAT, int NT>
@@ -504,6 +520,136 @@ __global__ __launch_bounds__(RT2) void reduce_pass2(const double *partial, int n
     reduce_final<WHAT>(partial, nb, out);
 }
 
+// Conservation sums of FP64 fields.  Where they vanish exactly (momentum
+// tendencies of the flux-form schemes, z periodic) every digit of the result
+// is the rounding of this very order of additions, so the order is fixed: row
+// r = (j, k) pairs belongs to partial r % RB, a row's points in chunks of V
+// (2 where rows and fields are aligned to it, else 1) to the RT threads of that
+// partial, slot s of rpp = RT / cpr taking every rpp-th of its rows; each point
+// is weighted, then added; the threads' sums are combined by halving.  (FP32
+// tendencies differ from zero by their own rounding, far above this.)
+//
+// Bound by HBM at 256^3, by the two launches below.  Only threads and partials
+// that own rows are launched, four rows are in flight per thread, and the tree
+// is one exchange between waves and shuffles (before: 4096 blocks of 256, two
+// rows, nine values over LDS).
+constexpr int SUM_ROWS = 4;  // rows in flight
+
+__device__ __forceinline__ void sum_tree(double (&acc)[3], int nw, double *out, int64_t stride)
+{
+    __shared__ double sh[3][3][64];
+    const int lane = (int)threadIdx.x & 63, wave = (int)threadIdx.x >> 6;
+    if (wave > 0 && wave < 4)
+#pragma unroll
+        for (int q = 0; q < 3; ++q) sh[wave - 1][q][lane] = acc[q];
+    __syncthreads();
+    if (wave > 0) return;
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+        const double w1 = nw > 1 ? sh[0][q][lane] : 0.0, w2 = nw > 2 ? sh[1][q][lane] : 0.0,
+                     w3 = nw > 3 ? sh[2][q][lane] : 0.0;
+        acc[q] = (acc[q] + w2) + (w1 + w3);
+    }
+#pragma unroll
+    for (int s = 32; s > 0; s >>= 1)
+#pragma unroll
+        for (int q = 0; q < 3; ++q) acc[q] += __shfl_down(acc[q], (unsigned)s, 64);
+    if (lane == 0)
+#pragma unroll
+        for (int q = 0; q < 3; ++q) out[q * stride] = acc[q];
+}
+
+template <int V>
+__device__ __forceinline__ void sum_rows(const Dims &d, int kw0, const double *f0, const double *f1, const double *f2,
+                                         const double *dzi, const double *dzhi, int b, int nb, double *partial)
+{
+    const uint32_t nrows = (uint32_t)d.jtot * (uint32_t)d.ktot, jt = (uint32_t)d.jtot;  // below 2^31
+    const int cpr = d.itot / V;
+    const double *f3[3] = {f0, f1, f2};
+    double acc[3] = {0.0, 0.0, 0.0};
+    auto load = [&](double (&x)[3][V], uint32_t r, int c) {
+        const int64_t o = at(d, 1 + c * V, 1 + (int)(r % jt), 1 + (int)(r / jt));
+#pragma unroll
+        for (int f = 0; f < 3; ++f) vload<double, V>(x[f], f3[f] + o);
+    };
+    auto add = [&](const double (&x)[3][V], uint32_t r) {
+        const int k = 1 + (int)(r / jt);
+        const double wz = 1.0 / dzi[k], wzh = 1.0 / dzhi[k];
+#pragma unroll
+        for (int n = 0; n < V; ++n) {
+            acc[0] += x[0][n] * wz;
+            acc[1] += x[1][n] * wz;
+            if (k >= kw0) acc[2] += x[2][n] * wzh;
+        }
+    };
+    if (cpr < RT) {
+        const int rpp = RT / cpr, slot = (int)threadIdx.x / cpr, c = (int)threadIdx.x % cpr;
+        const uint32_t step = (uint32_t)rpp * RB;
+        if (slot < rpp)
+            for (uint32_t r = (uint32_t)b + (uint32_t)slot * RB; r < nrows; r += SUM_ROWS * step) {
+                double x[SUM_ROWS][3][V];
+#pragma unroll
+                for (int m = 0; m < SUM_ROWS; ++m) load(x[m], r + m * step < nrows ? r + m * step : r, c);
+#pragma unroll
+                for (int m = 0; m < SUM_ROWS; ++m)
+                    if (r + m * step < nrows) add(x[m], r + m * step);
+            }
+    } else {  // pairs of rows, chunk by chunk
+        uint32_t r = (uint32_t)b;
+        for (; r + RB < nrows; r += 2 * RB)
+            for (int c = (int)threadIdx.x; c < cpr; c += 2 * RT) {
+                const bool two = c + RT < cpr;
+                const int c2 = two ? c + RT : c;
+                double x[4][3][V];
+                load(x[0], r, c);
+                load(x[1], r + RB, c);
+                load(x[2], r, c2);
+                load(x[3], r + RB, c2);
+                add(x[0], r);
+                add(x[1], r + RB);
+                if (two) {
+                    add(x[2], r);
+                    add(x[3], r + RB);
+                }
+            }
+        if (r < nrows)
+            for (int c = (int)threadIdx.x; c < cpr; c += RT) {
+                double x[3][V];
+                load(x, r, c);
+                add(x, r);
+            }
+    }
+    sum_tree(acc, (int)blockDim.x >> 6, partial + b, nb);
+}
+
+template <int V>
+__global__ __launch_bounds__(RT) void sum_rows_pass1(Dims d, int kw0, const double *f0, const double *f1,
+                                                    const double *f2, const double *dzi, const double *dzhi,
+                                                    double *partial)
+{
+    sum_rows<V>(d, kw0, f0, f1, f2, dzi, dzhi, (int)blockIdx.x, (int)gridDim.x, partial);
+}
+
+// Pass 2 by the first RT threads: thread t sums partials t, t + RT, ...
+__device__ __forceinline__ void sum_rows_final(const double *partial, int nb, double *out)
+{
+    double acc[3] = {0.0, 0.0, 0.0};
+    if (threadIdx.x < RT) {
+#pragma unroll
+        for (int m = 0; m < RB / RT; ++m) {
+            const int b = m * RT + (int)threadIdx.x;
+#pragma unroll
+            for (int q = 0; q < 3; ++q) acc[q] += b < nb ? partial[(int64_t)q * nb + b] : 0.0;
+        }
+    }
+    sum_tree(acc, 4, out, 1);
+}
+
+__global__ __launch_bounds__(RT) void sum_rows_pass2(const double *partial, int nb, double *out)
+{
+    sum_rows_final(partial, nb, out);
+}
+
 // Conservation sums of many grids in two launches: pass-1 block blockIdx.x is
 // block b of job g, (g, b) = blocks[blockIdx.x], into that job's own partials;
 // pass 2 reduces each grid's partials in one block.  Per grid the pieces,
@@ -523,16 +669,24 @@ __global__ __launch_bounds__(RT) void sums_batch_pass1(const SumJob *__restrict_
 {
     const int2 gb = blocks[blockIdx.x];
     const SumJob j = jobs[gb.x];
-    reduce_block<T, V, 0>(j.d, j.pl, j.kw0, as_global((const T *)j.f0), as_global((const T *)j.f1),
-                          as_global((const T *)j.f2), as_global((const T *)j.dzi), as_global((const T *)j.dzhi),
-                          gb.y, partials + j.first);
+    if constexpr (sizeof(T) == 8)
+        sum_rows<V>(j.d, j.kw0, as_global((const T *)j.f0), as_global((const T *)j.f1), as_global((const T *)j.f2),
+                    as_global((const T *)j.dzi), as_global((const T *)j.dzhi), gb.y, j.pl.nb, partials + j.first);
+    else
+        reduce_block<T, V, 0>(j.d, j.pl, j.kw0, as_global((const T *)j.f0), as_global((const T *)j.f1),
+                              as_global((const T *)j.f2), as_global((const T *)j.dzi), as_global((const T *)j.dzhi),
+                              gb.y, partials + j.first);
 }
 
 __global__ __launch_bounds__(RT2) void sums_batch_pass2(const longlong2 *__restrict__ slots, const double *partials,
                                                        double *out)
 {
-    const longlong2 sl = slots[blockIdx.x];  // first partial and number of blocks of this grid
-    reduce_final<0>(partials + sl.x, (int)sl.y, out + 3 * (int64_t)blockIdx.x);
+    const longlong2 sl = slots[blockIdx.x];  // first partial and number of blocks of this grid, negative: FP64
+    double *o = out + 3 * (int64_t)blockIdx.x;
+    if (sl.y < 0)
+        sum_rows_final(partials + sl.x, (int)-sl.y, o);
+    else
+        reduce_final<0>(partials + sl.x, (int)sl.y, o);
 }
 
 // Bit hash: sum over interior cells (mod 2^64) of SplitMix64(bits ^ cell key).
@@ -716,12 +870,15 @@ void launch_pass1(const HostArgs &a, const RedPlan &pl, int what, const void *f0
 {
     const Dims d = dims_of(a);
     const T *p[3] = {(const T *)f0, (const T *)f1, (const T *)f2};
-    if (what == 0)
-        hipLaunchKernelGGL((reduce_pass1<T, V, 0>), dim3(pl.nb), dim3(RT), 0, s, d, pl, a.kw0, p[0], p[1], p[2],
-                           (const T *)a.dzi, (const T *)a.dzhi, partial);
-    else
-        hipLaunchKernelGGL((reduce_pass1<T, V, 1>), dim3(pl.nb), dim3(RT), 0, s, d, pl, a.kw0, p[0], p[1], p[2],
-                           (const T *)a.dzi, (const T *)a.dzhi, partial);
+    if constexpr (sizeof(T) == 4) {  // FP64: sum_rows_pass1
+        if (what == 0) {
+            hipLaunchKernelGGL((reduce_pass1<T, V, 0>), dim3(pl.nb), dim3(RT), 0, s, d, pl, a.kw0, p[0], p[1], p[2],
+                               (const T *)a.dzi, (const T *)a.dzhi, partial);
+            return;
+        }
+    }
+    hipLaunchKernelGGL((reduce_pass1<T, V, 1>), dim3(pl.nb), dim3(RT), 0, s, d, pl, a.kw0, p[0], p[1], p[2],
+                       (const T *)a.dzi, (const T *)a.dzhi, partial);
 }
 }  // namespace
 
@@ -730,6 +887,18 @@ hipError_t launch_reduce(const HostArgs &a, int what, const void *f0, const void
 {
     double *partial = (double *)scratch;
     if ((int64_t)a.jtot * a.ktot >= ((int64_t)1 << 31)) return hipErrorInvalidValue;  // 32-bit piece index
+    if (what == 0 && a.dtype == KL_F64) {
+        const Dims d = dims_of(a);
+        const int V = sum_rows_aligned(a, f0, f1, f2) ? 2 : 1, nb = sum_rows_blocks(a);
+        auto *k = V == 2 ? &sum_rows_pass1<2> : &sum_rows_pass1<1>;
+        hipLaunchKernelGGL(k, dim3(nb), dim3(sum_rows_threads(a, V)), 0, s, d, a.kw0, (const double *)f0,
+                           (const double *)f1, (const double *)f2, (const double *)a.dzi, (const double *)a.dzhi,
+                           partial);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(sum_rows_pass2, dim3(1), dim3(RT), 0, s, (const double *)partial, nb, out);
+        return hipGetLastError();
+    }
     const RedPlan pl = red_plan(a);
     const bool vec = row_chunk(a) > 1;
     if (a.dtype == KL_F32) {
@@ -799,7 +968,10 @@ hipError_t launch_fill_batch(int dtype, const void *jobs, const void *blocks, in
 
 size_t sum_job_bytes() { return sizeof(SumJob); }
 
-bool sums_vectorized(const HostArgs &a) { return row_chunk(a) > 1; }
+bool sums_vectorized(const HostArgs &a, const void *ut, const void *vt, const void *wt)
+{
+    return a.dtype == KL_F64 ? sum_rows_aligned(a, ut, vt, wt) : row_chunk(a) > 1;
+}
 
 void append_sum_job(const HostArgs &a, const void *ut, const void *vt, const void *wt, std::vector<char> &jobs,
                     std::vector<int2> &blocks, std::vector<longlong2> &slots, int64_t *npartials)
@@ -809,6 +981,7 @@ void append_sum_job(const HostArgs &a, const void *ut, const void *vt, const voi
     memset(&j, 0, sizeof j);
     j.d = dims_of(a);
     j.pl = red_plan(a);
+    if (a.dtype == KL_F64) j.pl.nb = sum_rows_blocks(a);
     j.kw0 = a.kw0;
     j.first = *npartials;
     j.f0 = ut;
@@ -819,7 +992,7 @@ void append_sum_job(const HostArgs &a, const void *ut, const void *vt, const voi
     for (int b = 0; b < j.pl.nb; ++b) blocks.push_back(make_int2(job, b));
     longlong2 sl;
     sl.x = j.first;
-    sl.y = j.pl.nb;
+    sl.y = a.dtype == KL_F64 ? -j.pl.nb : j.pl.nb;
     slots.push_back(sl);
     *npartials += 3 * (int64_t)j.pl.nb;
     const char *p = (const char *)&j;

@@ -409,7 +409,7 @@ int build(Batch &b, void *const *fields)
             const kl_grid_t *g = &b.grids[n];
             const HostArgs a = make_args(g);
             void *const *f = fields + 6 * n;
-            const int vec = sums_vectorized(a) ? 1 : 0;
+            const int vec = sums_vectorized(a, f[3], f[4], f[5]) ? 1 : 0;
             append_sum_job(a, f[3], f[4], f[5], jobs[g->dtype][vec], blocks[g->dtype][vec], slots, &npartials);
             ++b.nsjobs[g->dtype][vec];
         }

@@ -148,7 +148,7 @@ void append_fill_job(const HostArgs &a, void *u, void *v, void *w, std::vector<c
                      std::vector<int2> &blocks);
 hipError_t launch_fill_batch(int dtype, const void *jobs, const void *blocks, int nblocks, hipStream_t s);
 size_t sum_job_bytes();
-bool sums_vectorized(const HostArgs &a);
+bool sums_vectorized(const HostArgs &a, const void *ut, const void *vt, const void *wt);
 void append_sum_job(const HostArgs &a, const void *ut, const void *vt, const void *wt, std::vector<char> &jobs,
                     std::vector<int2> &blocks, std::vector<longlong2> &slots, int64_t *npartials);
 hipError_t launch_sums_batch(int dtype, bool vec, const void *jobs, const void *blocks, int nblocks, double *partials,

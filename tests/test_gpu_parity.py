@@ -281,6 +281,74 @@ def test_reduction_pieces_match_oracle(dtype, shape, layout):
     assert np.max(np.abs(out3.cpu().numpy() - ref)) <= 1e-12 * scale
 
 
+def sums_in_order(x, wz, wzh, kw0, v):
+    """The FP64 conservation sums, added in their fixed order: partial r % 4096
+    of row r, 256 threads per partial over chunks of v points (slots of rows
+    where a row has fewer than 256 chunks, pairs of rows where it has more),
+    the threads' sums combined by halving, and the same over the partials."""
+    ktot, jtot, itot = x[0].shape
+    nrows, cpr, rb, rt = jtot * ktot, itot // v, 4096, 256
+    acc = np.zeros((3, rb, rt))
+    rows = [f.reshape(nrows, itot) for f in x]
+    w = [np.repeat(wz, jtot), np.repeat(wz, jtot), np.repeat(np.where(np.arange(1, ktot + 1) >= kw0, wzh, 0.0), jtot)]
+
+    def add(r, t, c):
+        for q in range(3):
+            for n in range(v):
+                acc[q, r % rb, t] = acc[q, r % rb, t] + rows[q][r, c * v + n] * w[q][r]
+
+    if cpr < rt:
+        rpp = rt // cpr
+        c = np.arange(cpr)
+        for r in range(nrows):
+            add(r, r // rb % rpp * cpr + c, c)
+    else:
+        for b in range(min(rb, nrows)):
+            r = b
+            while r < nrows:
+                pair = [r, r + rb] if r + rb < nrows else [r]
+                for c0 in range(0, cpr, rt):
+                    c = np.arange(c0, min(cpr, c0 + rt))
+                    for rr in pair:
+                        add(rr, c - c0, c)
+                r += 2 * rb
+
+    def tree(a):
+        s = a.shape[-1] // 2
+        while s:
+            a = a[..., :s] + a[..., s:2 * s]
+            s //= 2
+        return a[..., 0]
+
+    part = tree(acc)
+    tot = np.zeros((3, rt))
+    for m in range(rb // rt):
+        tot = tot + part[:, m * rt:(m + 1) * rt]
+    return tree(tot)
+
+
+@pytest.mark.parametrize("layout", ["padded", "plain"])
+@pytest.mark.parametrize("shape", [(1, 1, 2), (48, 5, 7), (45, 90, 100), (516, 3, 4), (301, 70, 60)],
+                         ids=lambda s: "x".join(map(str, s)))
+def test_fp64_sums_keep_their_order(shape, layout):
+    """Sums that vanish exactly are their own rounding, so FP64 sums are held
+    to their order of additions bit for bit: one thread or several slots per
+    partial, more rows than partials, rows wider than the block, aligned rows
+    (two points per load) and unaligned ones."""
+    import torch
+    m = kl()
+    lay = inputs.plain_layout(*shape) if layout == "plain" else None
+    bc = 2 if shape[2] < 3 else 0
+    c = Case(*shape, 1, bc=bc, seed=15, layout=lay)
+    out = torch.zeros(3, dtype=torch.float64, device="cuda")
+    m.kl_reduce_fp64(c.g, 0, *c.dev, out)
+    og = c.og
+    v = 2 if shape[0] % 2 == 0 and (og.off + 1) % 2 == 0 and og.js % 2 == 0 and og.ks % 2 == 0 else 1
+    x = [c.interior_np(h) for h in c.host]
+    ref = sums_in_order(x, 1.0 / og.dzi[1:shape[2] + 1], 1.0 / og.dzhi[1:shape[2] + 1], 1 if bc == 2 else 2, v)
+    assert np.array_equal(out.cpu().numpy(), ref)
+
+
 @pytest.mark.parametrize("gc", [1, 3])
 @pytest.mark.parametrize("bc", [0, 1, 2], ids=["zerograd", "nopen", "zperiodic"])
 @pytest.mark.parametrize("shape", [(1, 1, 2), (3, 3, 2), (5, 2, 3), (7, 5, 4), (16, 600, 3), (301, 13, 5), (4100, 3, 2)],
