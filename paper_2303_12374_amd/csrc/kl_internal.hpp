@@ -89,8 +89,6 @@ inline int rf_rows(int jtot, int cpr, int threads)
 }
 inline size_t rf_lds_bytes(int cpr, int R) { return (size_t)RF_PLANES * ((R + 2) * cpr + 64) * 16; }
 constexpr size_t RF_LDS_256 = (size_t)RF_PLANES * (5 * 80 + 64) * 16, RF_LDS_512 = (size_t)RF_PLANES * (4 * 256 + 64) * 16;
-// Levels per tile in the persistent forms, where many grids fill the GPU.
-constexpr int RF_BATCH_KB = 32;
 
 // Row-flattened tiles of the paper's schemes (stencil_les_rf.hpp): rows cut into
 // the fewest segments of at most 64 (advec_u_2i5; 60 of two points) or 48
@@ -163,7 +161,11 @@ bool batch_fits(const Variant &v, const kl_grid_t *g, const void *const *ptrs, i
 struct TileShape {
     int tw, by, kb, nbx, nby, nbz;
 };
-TileShape batch_tiles(const Variant &v, const kl_grid_t *g);
+// (row-flattened tiles: rf_kb levels per tile, from rf_batch_levels).
+TileShape batch_tiles(const Variant &v, const kl_grid_t *g, int rf_kb);
+// Levels per row-flattened tile in a persistent kernel that advances the grids
+// n with sel[n] == vi together.
+int rf_batch_levels(const Variant &v, int vi, const std::vector<kl_grid_t> &grids, const std::vector<int> &sel, int ncu);
 // Configuration of grid g for `kernel` in batched (persistent) form, or -1.
 int batch_variant(const kl_grid_t *g, int kernel, void *const f[6]);
 // Regroup grids (6 field pointers each) for fewer persistent kernels: see batch.hip.

@@ -260,16 +260,24 @@ struct GpuExec {
         // as few groups (launches per tick) as the configurations allow; every
         // configuration gives the same bits, so a request may change group
         merge_batch_groups(KL_KERNEL_STEP, grids, fields.data(), sel);
+        std::map<std::pair<int, int>, int> levels;  // (dtype, configuration) -> levels per row-flattened tile
+        for (size_t n = 0; n < act.size(); ++n) {
+            const int dtype = grids[n].dtype;
+            if (!levels.count({dtype, sel[n]}))
+                levels[{dtype, sel[n]}] =
+                    rf_batch_levels(variants(KL_KERNEL_STEP, dtype)[sel[n]], sel[n], grids, sel, ncu);
+        }
         for (size_t n = 0; n < act.size(); ++n) {
             const Req &q = *act[n];
             const int vi = sel[n];
             const Variant &v = variants(KL_KERNEL_STEP, q.g.dtype)[vi];
+            const int kb = levels.at({q.g.dtype, vi});
             if (q.g.dtype == KL_F32)
-                batch_shape(v, &q.g, df[didx[n]]);
+                batch_shape(v, &q.g, kb, df[didx[n]]);
             else
-                batch_shape(v, &q.g, dd[didx[n]]);
+                batch_shape(v, &q.g, kb, dd[didx[n]]);
             auto &tl = sized[std::make_tuple(q.g.dtype, vi)];
-            const TileShape t = batch_tiles(v, &q.g);
+            const TileShape t = batch_tiles(v, &q.g, kb);
             for (int tz = 0; tz < t.nbz; ++tz)
                 for (int ty = 0; ty < t.nby; ++ty)
                     for (int tx = 0; tx < t.nbx; ++tx)

@@ -328,8 +328,12 @@ __global__ __launch_bounds__(64 * BY, WPE) void step_zl(StencilArgs<T> a)
     step_zl_tile<T, VX, BY, KB, NT, MODE>(a, tx, ty, tz);
 }
 
+// Persistent form.  At least two waves per SIMD: compiled for one, the FP64
+// tile of four rows took 264 registers and left its CU one block of four waves
+// (six FP64 grids of 128^3 to 512x512x128 in one launch: 516 us, with 251
+// registers and two blocks 455).
 template <typename T, int VX, int BY, int KB, int NT = 0, int WPE = 1, int MODE = FUSE_STEP>
-__global__ __launch_bounds__(64 * BY, WPE) void step_zl_batch(const StencilArgs<T> *__restrict__ grids,
+__global__ __launch_bounds__(64 * BY, WPE < 2 ? 2 : WPE) void step_zl_batch(const StencilArgs<T> *__restrict__ grids,
                                                              const int4 *__restrict__ tiles, int ntiles,
                                                              int *queue)
 {

@@ -265,10 +265,10 @@ hipError_t launch_les_rf(const HostArgs &h, hipStream_t s)
 
 // The row-flattened tile shape of a grid in a persistent kernel of configuration v.
 template <typename T>
-void batch_shape(const Variant &v, const kl_grid_t *g, StencilArgs<T> &a)
+void batch_shape(const Variant &v, const kl_grid_t *g, int rf_kb, StencilArgs<T> &a)
 {
     if (v.family != FAMILY_RF) return;
-    const TileShape t = batch_tiles(v, g);
+    const TileShape t = batch_tiles(v, g, rf_kb);
     a.rf_cpr = rf_chunks(g->itot, v.vx);
     a.rf_rows = t.by;
     a.rf_kb = t.kb;
