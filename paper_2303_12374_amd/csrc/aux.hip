@@ -934,7 +934,7 @@ int64_t fill_cell_count(const HostArgs &a)
            (a.bc != KL_BC_ZPERIODIC ? (int64_t)a.itot * a.jtot : 0);
 }
 
-void append_fill_job(const HostArgs &a, void *u, void *v, void *w, std::vector<char> &jobs,
+void append_fill_job(const HostArgs &a, void *u, void *v, void *w, bool x_columns, std::vector<char> &jobs,
                      std::vector<int2> &blocks)
 {
     const int64_t gc = a.gc;
@@ -946,7 +946,7 @@ void append_fill_job(const HostArgs &a, void *u, void *v, void *w, std::vector<c
     j.w = w;
     j.n0 = 2 * ic * jc;
     j.n1 = 2 * gc * ic * a.ktot;
-    j.n2 = 2 * gc * (int64_t)a.jtot * a.ktot;
+    j.n2 = x_columns ? 2 * gc * (int64_t)a.jtot * a.ktot : 0;
     j.n3 = a.bc != KL_BC_ZPERIODIC ? (int64_t)a.itot * a.jtot : 0;  // the velocity fill: w's wall faces
     const int job = (int)(jobs.size() / sizeof(FillJob));
     const char *p = (const char *)&j;

@@ -218,7 +218,8 @@ namespace {
 // referenced); sel[n] is the configuration of grid n.
 template <typename T>
 std::vector<StencilArgs<T>> descriptors(const std::vector<kl_grid_t> &grids, void *const *fields, double visc,
-                                        const std::vector<int> &sel, const std::map<std::pair<int, int>, int> &levels)
+                                        const std::vector<int> &sel, const std::map<std::pair<int, int>, int> &levels,
+                                        const std::vector<char> &x_fill)
 {
     std::vector<StencilArgs<T>> out(grids.size());
     for (size_t n = 0; n < grids.size(); ++n) {
@@ -234,6 +235,7 @@ std::vector<StencilArgs<T>> descriptors(const std::vector<kl_grid_t> &grids, voi
         out[n] = device_args<T>(a);
         batch_shape(variants(KL_KERNEL_ADVEC_DIFF, grids[n].dtype)[sel[n]], &grids[n],
                     levels.at({grids[n].dtype, sel[n]}), out[n]);
+        out[n].x_fill = x_fill[n];
     }
     return out;
 }
@@ -338,6 +340,7 @@ int build(Batch &b, void *const *fields)
 
     // groups
     std::map<std::tuple<int, int, int>, size_t> gidx;
+    std::vector<char> x_fill(b.grids.size(), 0);
     {
         const int kernel = KL_KERNEL_ADVEC_DIFF;
         std::vector<int> sel(b.grids.size()), recorded(b.grids.size(), -1);
@@ -360,8 +363,15 @@ int build(Batch &b, void *const *fields)
             if (!levels.count({dtype, sel[n]}))
                 levels[{dtype, sel[n]}] = rf_batch_levels(variants(kernel, dtype)[sel[n]], sel[n], b.grids, sel, ncu);
         }
-        auto df = descriptors<float>(b.grids, fields, b.visc, sel, levels);
-        auto dd = descriptors<double>(b.grids, fields, b.visc, sel, levels);
+        // the row-flattened pass writes one ghost column on each side itself
+        // where rows are whole chunks
+        for (size_t n = 0; n < b.grids.size(); ++n) {
+            const Variant &v = variants(kernel, b.grids[n].dtype)[sel[n]];
+            x_fill[n] = (b.flags & KL_BATCH_FILL_GHOSTS) && b.grids[n].gc == 1 && v.family == FAMILY_RF &&
+                        b.grids[n].itot % v.vx == 0;
+        }
+        auto df = descriptors<float>(b.grids, fields, b.visc, sel, levels, x_fill);
+        auto dd = descriptors<double>(b.grids, fields, b.visc, sel, levels, x_fill);
         if ((e = upload(&b.d_desc[0], df.data(), df.size() * sizeof(df[0]))) != hipSuccess) return hip_fail(e, "desc");
         if ((e = upload(&b.d_desc[1], dd.data(), dd.size() * sizeof(dd[0]))) != hipSuccess) return hip_fail(e, "desc");
         for (size_t n = 0; n < b.grids.size(); ++n) {
@@ -414,8 +424,8 @@ int build(Batch &b, void *const *fields)
         std::vector<int2> blocks[2];
         for (size_t n = 0; n < b.grids.size(); ++n) {
             const kl_grid_t *g = &b.grids[n];
-            append_fill_job(make_args(g), fields[6 * n], fields[6 * n + 1], fields[6 * n + 2], jobs[g->dtype],
-                            blocks[g->dtype]);
+            append_fill_job(make_args(g), fields[6 * n], fields[6 * n + 1], fields[6 * n + 2], !x_fill[n],
+                            jobs[g->dtype], blocks[g->dtype]);
         }
         for (int d = 0; d < 2; ++d) {
             if (blocks[d].empty()) continue;

@@ -142,7 +142,7 @@ size_t reduce_scratch_bytes();
 // partials need, every one of which is written by each launch).
 size_t fill_job_bytes();
 int64_t fill_cell_count(const HostArgs &a);  // ghost cells of the velocity fill (must be < 2^32)
-void append_fill_job(const HostArgs &a, void *u, void *v, void *w, std::vector<char> &jobs,
+void append_fill_job(const HostArgs &a, void *u, void *v, void *w, bool x_columns, std::vector<char> &jobs,
                      std::vector<int2> &blocks);
 hipError_t launch_fill_batch(int dtype, const void *jobs, const void *blocks, int nblocks, hipStream_t s);
 size_t sum_job_bytes();

@@ -52,6 +52,7 @@ StencilArgs<T> device_args(const HostArgs &h)
     a.nbx = a.nby = a.nbz = 1;
     a.evisc = (const T *)h.evisc;
     a.rf_cpr = a.rf_rows = a.rf_kb = 0;
+    a.x_fill = 0;
     a.x_nt = 3.0 * h.itot * h.jtot * h.ktot * sizeof(T) <= XIMAGE_CACHED_BYTES;
     return a;
 }

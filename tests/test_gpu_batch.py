@@ -234,3 +234,45 @@ def test_batch_graph_with_ghost_fill_zeroing_and_sums():
                 assert np.array_equal(s[3 * n:3 * n + 3], ref_s[n]), (rep, n, s[3 * n:3 * n + 3], ref_s[n])
     finally:
         m.kl_batch_destroy(b)
+
+
+@pytest.mark.parametrize("bc", [0, 1, 2], ids=["zerograd", "nopen", "zperiodic"])
+@pytest.mark.parametrize("zero", [False, True], ids=["accumulate", "cleared"])
+@pytest.mark.parametrize("dtype", [0, 1], ids=["f32", "f64"])
+def test_batch_fills_ghosts_of_every_row_form(dtype, zero, bc):
+    """The ghost columns that the row-flattened pass writes itself (rows of
+    whole chunks: one chunk, several, the widest) and those filled before it
+    (a partial last chunk, three ghost cells): fields and tendencies bitwise
+    those of the separate calls, whatever the ghosts held before."""
+    m = kl()
+    v = 4 if dtype == 0 else 2
+    grids, ref = [], []
+    for shape, gc in (((v, 3, 4), 1), ((8 * v, 9, 17), 1), ((8 * v + 1, 5, 9), 1), ((80 * v, 4, 5), 1), ((16 * v, 6, 3), 3)):
+        g = m.Grid(*shape, dtype=dtype, bc=bc, gc=gc)
+        f = [g.full(np.nan) for _ in range(3)]
+        m.kl_generate_fields(g, 61, *f)
+        for x in f:
+            keep = g.interior(x).clone()
+            g.box(x).fill_(np.nan)
+            g.interior(x).copy_(keep)
+        t = [g.full(-3.0) for _ in range(3)]
+        for x in t:
+            g.interior(x).fill_(0.25)
+        rf, rt = [x.clone() for x in f], [x.clone() for x in t]
+        for x in rt:
+            g.interior(x).fill_(0.0 if zero else 0.25)
+        m.kl_fill_ghosts(g, *rf)
+        m.kl_advec_u(g, rt[0], *rf)
+        m.kl_diff_uvw(g, *rt, *rf, 1e-5)
+        grids.append((g, f, t))
+        ref.append(rf + rt)
+    flags = m.BATCH_FILL_GHOSTS | (m.BATCH_ZERO_TENDENCIES if zero else 0)
+    b = m.kl_batch_create_ex([g for g, _, _ in grids], [f + t for _, f, t in grids], 1e-5, flags)
+    try:
+        m.kl_batch_run(b)
+        torch.cuda.synchronize()
+    finally:
+        m.kl_batch_destroy(b)
+    for n, (g, f, t) in enumerate(grids):
+        for q, (x, y) in enumerate(zip(f + t, ref[n])):
+            assert np.array_equal(x.cpu().numpy(), y.cpu().numpy(), equal_nan=True), (n, q)
