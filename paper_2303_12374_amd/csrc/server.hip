@@ -295,11 +295,6 @@ struct GpuExec {
             auto &tl = groups[kv.first];
             for (const auto &t : kv.second) tl.push_back(t.second);
         }
-        // one launch reads the inputs of all requests
-        double in = 0;
-        for (const kl_grid_t &g : grids) in += 3.0 * g.itot * g.jtot * g.ktot * (g.dtype == KL_F32 ? 4 : 8);
-        for (auto &a : df) a.x_nt = in <= XIMAGE_CACHED_BYTES;
-        for (auto &a : dd) a.x_nt = in <= XIMAGE_CACHED_BYTES;
         // pack tables: [desc f32][desc f64][group tiles...]
         size_t off = 0;
         auto place = [&](size_t bytes) {

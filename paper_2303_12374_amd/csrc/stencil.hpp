@@ -32,7 +32,6 @@ struct StencilArgs {
     const T *evisc;          // eddy viscosity at cell centers (diff_smag only)
     int rf_cpr, rf_rows, rf_kb;  // row-flattened tiles: chunks per row, rows and levels per tile
     int x_fill;              // batched pass: write the x ghost columns of u, v, w
-    int x_nt;                // fused step: stream the x images past the caches (XIMAGE_CACHED_BYTES)
 };
 
 // The batched kernels read their descriptors from memory, so the compiler

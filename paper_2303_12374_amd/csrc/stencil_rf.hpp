@@ -26,7 +26,7 @@
 // and 52 KB of LDS, two or three per CU.  Measured against the fastest of the
 // other tiles (us): advec_u 301x203x151 FP32 65 -> 32, FP64 133 -> 66;
 // diff_uvw 320x320x160 FP32 151 -> 94, 301x203x151 FP64 268 -> 113; fused pass
-// 128^3 FP64 32 -> 28; fused step 128^3 FP32 21 -> 16, 256^3 97 -> 75.  Rows of
+// 128^3 FP64 32 -> 28; fused step 128^3 FP32 21 -> 16, 256^3 97 -> 90.  Rows of
 // 640 points and more are left to the other tiles, which split them in x.
 //
 // The per-point functions are those of stencil.hpp: results are bitwise those
@@ -298,10 +298,9 @@ __device__ __forceinline__ void rf_tile(const StencilArgs<T> &a, int ty, int tz,
                     auto put = [&](T *f, int o, const T(&x)[V]) __attribute__((always_inline)) {
                         T *row0 = f + a.off + (int64_t)k * ks;
                         rf_store<NT, T, V>(boff(row0, (uint32_t)o * (uint32_t)sizeof(T)), x, n_own);
-                        if (c == 0) xstore<NT>(boff(row0, (uint32_t)(o + a.itot) * (uint32_t)sizeof(T)), x[0], a.x_nt);
+                        if (c == 0) *boff(row0, (uint32_t)(o + a.itot) * (uint32_t)sizeof(T)) = x[0];
                         if (c == cpr - 1)
-                            xstore<NT>(boff(row0, (uint32_t)(o - i0) * (uint32_t)sizeof(T)), rf_nth<T, V>(x, n_own),
-                                       a.x_nt);
+                            *boff(row0, (uint32_t)(o - i0) * (uint32_t)sizeof(T)) = rf_nth<T, V>(x, n_own);
                     };
 #pragma unroll
                     for (int f = 0; f < 3; ++f) {

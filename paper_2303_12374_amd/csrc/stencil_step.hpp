@@ -22,19 +22,6 @@
 
 namespace kl {
 
-// Store an x image of a streaming tile (see XIMAGE_CACHED_BYTES).
-template <int NT, typename T>
-__device__ __forceinline__ void xstore(T *p, T x, int x_nt)
-{
-    if (NT && x_nt) {
-        asm volatile("");  // without these the two stores become one, without the hint
-        __builtin_nontemporal_store(x, p);
-        asm volatile("");
-    } else {
-        *p = x;
-    }
-}
-
 // Store a VX-vector of new values at (i0.., j, k) and at its x images (the
 // ghost columns 0 and itot+1 of the same row, periodic x).
 template <typename T, int VX, int NT>
@@ -43,8 +30,8 @@ __device__ __forceinline__ void put_with_x_images(T *f, const StencilArgs<T> &a,
 {
     const int64_t base = a.off + (int64_t)j * a.js + (int64_t)k * a.ks;
     tstore<NT, T, VX>(f + base + i0, val);
-    if (i0 == 1) xstore<NT>(f + base + a.itot + 1, val[0], a.x_nt);
-    if (i0 + VX - 1 == a.itot) xstore<NT>(f + base, val[VX - 1], a.x_nt);
+    if (i0 == 1) f[base + a.itot + 1] = val[0];
+    if (i0 + VX - 1 == a.itot) f[base] = val[VX - 1];
 }
 
 // Store a VX-vector of new values at (i0.., j, k) of field `fld` and at all
@@ -62,8 +49,8 @@ __device__ __forceinline__ void put_with_images(T *f, const StencilArgs<T> &a, i
     {
         const int64_t base = a.off + (int64_t)j * a.js + (int64_t)k * a.ks;
         tstore<NT, T, VX>(f + base + i0, val);
-        if (x_lo) xstore<NT>(f + base + a.itot + 1, val[0], a.x_nt);
-        if (x_hi) xstore<NT>(f + base, val[VX - 1], a.x_nt);
+        if (x_lo) f[base + a.itot + 1] = val[0];
+        if (x_hi) f[base] = val[VX - 1];
     }
     if (!(j == 1 || j == a.jtot || k <= 2 || k == kt)) return;
     int zk[4], zs[4], nz = 1;

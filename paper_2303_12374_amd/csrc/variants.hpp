@@ -17,14 +17,6 @@ namespace kl {
 
 inline unsigned cdivu(int64_t a, int64_t b) { return (unsigned)((a + b - 1) / b); }
 
-// A streaming fused step leaves the memory-side cache (256 MB) to the fields it
-// reads.  Their x images, one value at each end of a row, are partial lines:
-// written through the caches they take the place of inputs that would fit, and
-// while the inputs do fit, streaming them too is faster (FP32 256^3 90 -> 74 us,
-// 320x320x160 91 -> 77, 384x384x128 130 -> 101; FP64 301x203x151 115 -> 108);
-// with larger inputs it is up to 2% slower (512x512x256 FP32 348 against 354).
-constexpr double XIMAGE_CACHED_BYTES = 256e6;
-
 template <typename T>
 StencilArgs<T> device_args(const HostArgs &h)
 {
@@ -53,7 +45,6 @@ StencilArgs<T> device_args(const HostArgs &h)
     a.evisc = (const T *)h.evisc;
     a.rf_cpr = a.rf_rows = a.rf_kb = 0;
     a.x_fill = 0;
-    a.x_nt = 3.0 * h.itot * h.jtot * h.ktot * sizeof(T) <= XIMAGE_CACHED_BYTES;
     return a;
 }
 
