@@ -329,35 +329,32 @@ __global__ __launch_bounds__(256) void euler_kernel(Dims d, RowPieces rp, T dt, 
 }
 
 // ---------------------------------------------------------------------------
-// FP64 reductions.  Pass 1: block b of nb sums pieces b, b + nb, ...; a thread
-// takes every RT-th chunk of a piece, M in flight at a time; partials are
-// combined by a fixed tree (lanes, then waves).  Pass 2 reduces the nb
-// partials in one block the same way.  No atomics, and the mapping depends
-// only on the grid, so the result is bitwise reproducible.  The conservation
-// sums weight a level's sum once per piece.
+// FP64 checksums (sum, sum of squares, largest magnitude of each field).  Pass
+// 1: block b of nb sums pieces b, b + nb, ...; a thread takes every RT-th chunk
+// of a piece, RM in flight at a time; partials are combined by a fixed tree
+// (lanes, then waves).  Pass 2 reduces the nb partials in one block the same
+// way.  No atomics, and the mapping depends only on the grid, so the result is
+// bitwise reproducible.
 //
 // Bound by HBM (one read of the fields) down to about 10^7 points, below that
-// by the two launches.  1024 chunks a piece keep 12 16-byte loads in flight
-// per thread (6 for the checksums, whose nine sums need the registers) and
-// still give a 128^3 grid 512 blocks; at most RED_MAXB blocks (8 per CU) keep
-// pass 2 to a few loads per thread.  Against 4096 blocks of scattered rows, a
-// division per point and row, and a nine-value tree over LDS for both kinds:
-// 512^3 FP32 sums 351 -> 266 us (6.06 TB/s), checksums 311 -> 281 us; 128^3
-// 27 -> 12 us; 301x203x151 (one point per load before) 102 -> 24 us.
+// by the two launches.  Two chunks of three fields keep 6 16-byte loads in
+// flight per thread (the nine sums need the registers: four chunks took 134 and
+// were slower), and 1024 chunks a piece still give a 128^3 grid 512 blocks; at
+// most RED_MAXB blocks (8 per CU) keep pass 2 to a few loads per thread.
+// Against 4096 blocks of scattered rows, a division per point and row, and a
+// tree over LDS (us): 512^3 FP32 311 -> 284, 128^3 26 -> 12, 301x203x151 FP32
+// (one point per load before) 102 -> 28.
 // ---------------------------------------------------------------------------
 constexpr int RB = 4096;   // pass-1 blocks of the hash, and the scratch's partial count
 constexpr int RT = 256;    // threads per block
-constexpr int RQ = 9;      // most values per partial
+constexpr int RQ = 9;      // values per partial
 constexpr int RED_MAXB = 2048;
+constexpr int SUM_P = 4;   // batched sums: partials per group of waves
 constexpr int RT2 = 512;   // threads of pass 2
 static_assert(RED_MAXB <= RB, "the reductions' partials fit the scratch");
 
-template <int WHAT>
-struct RedShape {
-    static constexpr int NQ = WHAT == 0 ? 3 : 9;
-    static constexpr int M = WHAT == 0 ? 4 : 2;  // chunks in flight per thread
-    __device__ static constexpr bool is_max(int q) { return WHAT == 1 && q % 3 == 2; }
-};
+constexpr int RM = 2;      // chunks in flight per thread
+__device__ constexpr bool is_max(int q) { return q % 3 == 2; }
 
 struct RedPlan {
     RowPieces rp;
@@ -374,35 +371,37 @@ RedPlan red_plan(const HostArgs &a)
     return p;
 }
 
-// FP64 conservation sums: partials, vector width and threads per block (those
-// of the slots that own rows).
-bool sum_rows_aligned(const HostArgs &a, const void *f0, const void *f1, const void *f2)
+// Conservation sums: points per load, partials, and waves per partial (those of
+// the slots that own rows; a block of RT threads takes 4 / waves groups of partials).
+int sum_rows_chunk(const HostArgs &a, const void *f0, const void *f1, const void *f2)
 {
-    return a.itot % 2 == 0 && (a.off + 1) % 2 == 0 && a.js % 2 == 0 && a.ks % 2 == 0 &&
-           ((uintptr_t)f0 | (uintptr_t)f1 | (uintptr_t)f2) % 16 == 0;
+    const int V = a.dtype == KL_F32 ? 4 : 2;
+    const bool aligned = a.itot % V == 0 && (a.off + 1) % V == 0 && a.js % V == 0 && a.ks % V == 0 &&
+                         ((uintptr_t)f0 | (uintptr_t)f1 | (uintptr_t)f2) % 16 == 0;
+    return aligned ? V : 1;
 }
 int sum_rows_blocks(const HostArgs &a) { return (int)std::min<int64_t>(RB, (int64_t)a.jtot * a.ktot); }
-int sum_rows_threads(const HostArgs &a, int V)
+int sum_rows_waves(const HostArgs &a, int V)
 {
     const int cpr = a.itot / V;
-    if (cpr >= RT) return RT;
-    const int64_t slots = ((int64_t)a.jtot * a.ktot + RB - 1) / RB;
-    return (int)(std::min<int64_t>(RT / cpr, slots) * cpr + 63) / 64 * 64;
+    if (cpr >= RT) return RT / 64;
+    const int64_t slots = ((int64_t)a.jtot * a.ktot + RB - 1) / RB, threads = std::min<int64_t>(RT / cpr, slots) * cpr;
+    return threads <= 64 ? 1 : threads <= 128 ? 2 : 4;
 }
 
-// Reduce acc over the block's NT threads; thread q < NQ writes value q to
+// Reduce acc over the block's NT threads; thread q < RQ writes value q to
 // out[q * stride].
-template <int WHAT, int NT>
-__device__ __forceinline__ void block_tree(double (&acc)[RedShape<WHAT>::NQ], double *out, int64_t stride)
+template <int NT>
+__device__ __forceinline__ void block_tree(double (&acc)[RQ], double *out, int64_t stride)
 {
-    constexpr int NQ = RedShape<WHAT>::NQ, NW = NT / 64;
+    constexpr int NQ = RQ, NW = NT / 64;
     __shared__ double sh[NW][NQ];
 #pragma unroll
     for (int s = 32; s > 0; s >>= 1)
 #pragma unroll
         for (int q = 0; q < NQ; ++q) {
             const double o = __shfl_down(acc[q], (unsigned)s, 64);
-            acc[q] = RedShape<WHAT>::is_max(q) ? fmax(acc[q], o) : acc[q] + o;
+            acc[q] = is_max(q) ? fmax(acc[q], o) : acc[q] + o;
         }
     const int lane = (int)threadIdx.x & 63, wave = (int)threadIdx.x >> 6;
     if (lane == 0)
@@ -412,42 +411,39 @@ __device__ __forceinline__ void block_tree(double (&acc)[RedShape<WHAT>::NQ], do
     if ((int)threadIdx.x < NQ) {
         const int q = (int)threadIdx.x;
         double r = sh[0][q];
-        for (int w = 1; w < NW; ++w) r = WHAT == 1 && q % 3 == 2 ? fmax(r, sh[w][q]) : r + sh[w][q];
+        for (int w = 1; w < NW; ++w) r = q % 3 == 2 ? fmax(r, sh[w][q]) : r + sh[w][q];
         out[q * stride] = r;
     }
 }
 
 // Pass-1 block b of nb; its partial value q goes to partial[q * nb + b].
-template <typename T, int V, int WHAT>
-__device__ __forceinline__ void reduce_block(const Dims &d, const RedPlan &pl, int kw0, const T *f0, const T *f1,
-                                             const T *f2, const T *dzi, const T *dzhi, int b, double *partial)
+template <typename T, int V>
+__global__ __launch_bounds__(RT) void reduce_pass1(Dims d, RedPlan pl, const T *f0, const T *f1, const T *f2,
+                                                  double *partial)
 {
-    constexpr int NQ = RedShape<WHAT>::NQ;
     const RowPieces &rp = pl.rp;
     const T *f3[3] = {f0, f1, f2};
-    constexpr int M = RedShape<WHAT>::M;
-    double acc[NQ];
-    T mx[3] = {T(0), T(0), T(0)};  // checksums: the largest |f| so far, exact in T
+    double acc[RQ];
+    T mx[3] = {T(0), T(0), T(0)};  // the largest |f| so far, exact in T
 #pragma unroll
-    for (int q = 0; q < NQ; ++q) acc[q] = 0.0;
-    for (uint32_t p = (uint32_t)b; p < rp.np; p += (uint32_t)pl.nb) {
+    for (int q = 0; q < RQ; ++q) acc[q] = 0.0;
+    for (uint32_t p = blockIdx.x; p < rp.np; p += (uint32_t)pl.nb) {
         const int k = 1 + (int)(p / rp.ng);
         const uint32_t j0 = (p % rp.ng) * rp.R;
         const uint32_t left = (uint32_t)d.jtot - j0;
         const uint32_t n = (left < rp.R ? left : rp.R) * rp.cpr;
         const int64_t base = at(d, 1, 1 + (int)j0, k);
-        double s[3] = {0.0, 0.0, 0.0};
-        for (uint32_t e0 = threadIdx.x; e0 < n; e0 += M * RT) {
-            T x[M][3][V];
-            int lo[M];
+        for (uint32_t e0 = threadIdx.x; e0 < n; e0 += RM * RT) {
+            T x[RM][3][V];
+            int lo[RM];
 #pragma unroll
-            for (int m = 0; m < M; ++m) {
+            for (int m = 0; m < RM; ++m) {
                 const Chunk<V> c(rp, e0 + m * RT, n);
                 const int64_t o = base + (int64_t)c.row * d.js + c.col;
                 lo[m] = c.lo;
 #pragma unroll
                 for (int f = 0; f < 3; ++f) {
-                    if (WHAT == 1 && f3[f] == nullptr) {
+                    if (f3[f] == nullptr) {
 #pragma unroll
                         for (int i = 0; i < V; ++i) x[m][f][i] = T(0);
                     } else {
@@ -456,194 +452,193 @@ __device__ __forceinline__ void reduce_block(const Dims &d, const RedPlan &pl, i
                 }
             }
 #pragma unroll
-            for (int m = 0; m < M; ++m)
+            for (int m = 0; m < RM; ++m)
 #pragma unroll
                 for (int f = 0; f < 3; ++f)
 #pragma unroll
                     for (int i = 0; i < V; ++i) {
                         const T xi = i < lo[m] ? T(0) : x[m][f][i];
                         const double y = (double)xi;
-                        if constexpr (WHAT == 0) {
-                            s[f] += y;
-                        } else {
-                            acc[3 * f] += y;
-                            acc[3 * f + 1] = tfma(y, y, acc[3 * f + 1]);
-                            mx[f] = tmax(mx[f], tabs(xi));
-                        }
+                        acc[3 * f] += y;
+                        acc[3 * f + 1] = tfma(y, y, acc[3 * f + 1]);
+                        mx[f] = tmax(mx[f], tabs(xi));
                     }
         }
-        if constexpr (WHAT == 0) {
-            const double wz = 1.0 / (double)dzi[k], wzh = 1.0 / (double)dzhi[k];
-            acc[0] += s[0] * wz;
-            acc[1] += s[1] * wz;
-            if (k >= kw0) acc[2] += s[2] * wzh;
-        }
     }
-    if constexpr (WHAT == 1) {
 #pragma unroll
-        for (int f = 0; f < 3; ++f) acc[3 * f + 2] = (double)mx[f];
-    }
-    block_tree<WHAT, RT>(acc, partial + b, pl.nb);
-}
-
-template <typename T, int V, int WHAT>
-__global__ __launch_bounds__(RT) void reduce_pass1(Dims d, RedPlan pl, int kw0, const T *f0, const T *f1,
-                                                  const T *f2, const T *dzi, const T *dzhi, double *partial)
-{
-    reduce_block<T, V, WHAT>(d, pl, kw0, f0, f1, f2, dzi, dzhi, (int)blockIdx.x, partial);
+    for (int f = 0; f < 3; ++f) acc[3 * f + 2] = (double)mx[f];
+    block_tree<RT>(acc, partial + blockIdx.x, pl.nb);
 }
 
 // Pass 2 over nb partials (value q of block b at partial[q * nb + b]).
-template <int WHAT>
-__device__ __forceinline__ void reduce_final(const double *partial, int nb, double *out)
+__global__ __launch_bounds__(RT2) void reduce_pass2(const double *partial, int nb, double *out)
 {
-    constexpr int NQ = RedShape<WHAT>::NQ;
-    double acc[NQ];
+    double acc[RQ];
 #pragma unroll
-    for (int q = 0; q < NQ; ++q) acc[q] = 0.0;
+    for (int q = 0; q < RQ; ++q) acc[q] = 0.0;
 #pragma unroll
     for (int m = 0; m < RED_MAXB / RT2; ++m) {
         const int b = m * RT2 + (int)threadIdx.x;
         if (b < nb)
 #pragma unroll
-            for (int q = 0; q < NQ; ++q) {
+            for (int q = 0; q < RQ; ++q) {
                 const double y = partial[(int64_t)q * nb + b];
-                acc[q] = RedShape<WHAT>::is_max(q) ? fmax(acc[q], y) : acc[q] + y;
+                acc[q] = is_max(q) ? fmax(acc[q], y) : acc[q] + y;
             }
     }
-    block_tree<WHAT, RT2>(acc, out, 1);
+    block_tree<RT2>(acc, out, 1);
 }
 
-template <int WHAT>
-__global__ __launch_bounds__(RT2) void reduce_pass2(const double *partial, int nb, double *out)
-{
-    reduce_final<WHAT>(partial, nb, out);
-}
-
-// Conservation sums of FP64 fields.  Where they vanish exactly (momentum
-// tendencies of the flux-form schemes, z periodic) every digit of the result
-// is the rounding of this very order of additions, so the order is fixed: row
-// r = (j, k) pairs belongs to partial r % RB, a row's points in chunks of V
-// (2 where rows and fields are aligned to it, else 1) to the RT threads of that
-// partial, slot s of rpp = RT / cpr taking every rpp-th of its rows; each point
-// is weighted, then added; the threads' sums are combined by halving.  (FP32
-// tendencies differ from zero by their own rounding, far above this.)
+// Conservation sums.  Where they vanish (momentum tendencies of the flux-form
+// schemes, z periodic) the digits of the result are the rounding of this very
+// order of additions, so the order is fixed: row r = (j, k) pairs belongs to
+// partial r % RB, a row's points in chunks of V (16 bytes where rows and fields
+// are aligned to it, else one point) to the RT threads of that partial, slot s
+// of rpp = RT / cpr taking every rpp-th of its rows; each point is weighted,
+// then added; the threads' sums are combined by halving.
 //
 // Bound by HBM at 256^3, by the two launches below.  Only threads and partials
-// that own rows are launched, four rows are in flight per thread, and the tree
-// is one exchange between waves and shuffles.  Against 4096 blocks of 256, two
-// rows in flight and nine values over LDS (us): 256^3 110 -> 77 (5.2 TB/s),
-// 128^3 29 -> 16, 64^3 25 -> 12, 301x203x151 69 -> 39.
-constexpr int SUM_ROWS = 4;  // rows in flight
-
-__device__ __forceinline__ void sum_tree(double (&acc)[3], int nw, double *out, int64_t stride)
+// that own rows are launched (partials of one or two waves share a block), four
+// rows are in flight per thread, and the tree is one exchange between waves and
+// shuffles.  Against 4096 blocks of 256, two rows in flight and nine values
+// over LDS (us): 512^3 FP32 351 -> 274 (5.9 TB/s), 128^3 27 -> 12,
+// 301x203x151 FP32 (one point per load) 102 -> 37; FP64 256^3 110 -> 76,
+// 301x203x151 69 -> 40.  In a batch the rows of a partial are few, so a group
+// of waves takes four partials at once: pass 1 of 56 grids FP32, 0.2 million
+// partials, 325 us with one, 165 with four.
+// Sums of NP values of acc over each group of gw waves (1, 2 or 4) of a block of
+// RT threads; partial p of the group goes to out + p if p < n.
+template <int NP>
+__device__ __forceinline__ void sum_tree(double (&acc)[NP][3], int gw, double *out, int n, int64_t stride)
 {
-    __shared__ double sh[3][3][64];
+    __shared__ double sh[RT / 64][3 * NP][64];
     const int lane = (int)threadIdx.x & 63, wave = (int)threadIdx.x >> 6;
-    if (wave > 0 && wave < 4)
+    if (gw > 1) {
 #pragma unroll
-        for (int q = 0; q < 3; ++q) sh[wave - 1][q][lane] = acc[q];
-    __syncthreads();
-    if (wave > 0) return;
+        for (int p = 0; p < NP; ++p)
 #pragma unroll
-    for (int q = 0; q < 3; ++q) {
-        const double w1 = nw > 1 ? sh[0][q][lane] : 0.0, w2 = nw > 2 ? sh[1][q][lane] : 0.0,
-                     w3 = nw > 3 ? sh[2][q][lane] : 0.0;
-        acc[q] = (acc[q] + w2) + (w1 + w3);
+            for (int q = 0; q < 3; ++q) sh[wave][3 * p + q][lane] = acc[p][q];
+        __syncthreads();
+        if (wave & (gw - 1)) return;
+#pragma unroll
+        for (int p = 0; p < NP; ++p)
+#pragma unroll
+            for (int q = 0; q < 3; ++q) {
+                const int e = 3 * p + q;
+                const double w1 = sh[wave + 1][e][lane], w2 = gw > 2 ? sh[(wave + 2) & 3][e][lane] : 0.0,
+                             w3 = gw > 2 ? sh[(wave + 3) & 3][e][lane] : 0.0;
+                acc[p][q] = (acc[p][q] + w2) + (w1 + w3);
+            }
     }
 #pragma unroll
     for (int s = 32; s > 0; s >>= 1)
 #pragma unroll
-        for (int q = 0; q < 3; ++q) acc[q] += __shfl_down(acc[q], (unsigned)s, 64);
+        for (int p = 0; p < NP; ++p)
+#pragma unroll
+            for (int q = 0; q < 3; ++q) acc[p][q] += __shfl_down(acc[p][q], (unsigned)s, 64);
     if (lane == 0)
 #pragma unroll
-        for (int q = 0; q < 3; ++q) out[q * stride] = acc[q];
+        for (int p = 0; p < NP; ++p)
+            if (p < n)
+#pragma unroll
+                for (int q = 0; q < 3; ++q) out[q * stride + p] = acc[p][q];
 }
 
-template <int V>
-__device__ __forceinline__ void sum_rows(const Dims &d, int kw0, const double *f0, const double *f1, const double *f2,
-                                         const double *dzi, const double *dzhi, int b, int nb, double *partial)
+// The block's partials, from b0: NP for each group of gw waves (one where a row
+// has RT chunks or more), four rows in flight.
+template <typename T, int V, int NP>
+__device__ __forceinline__ void sum_rows(const Dims &d, int kw0, const T *f0, const T *f1, const T *f2, const T *dzi,
+                                         const T *dzhi, int b0, int nb, int gw, double *partial)
 {
-    const uint32_t nrows = (uint32_t)d.jtot * (uint32_t)d.ktot, jt = (uint32_t)d.jtot;  // below 2^31
+    const int t = (int)threadIdx.x & (64 * gw - 1);
     const int cpr = d.itot / V;
-    const double *f3[3] = {f0, f1, f2};
-    double acc[3] = {0.0, 0.0, 0.0};
-    auto load = [&](double (&x)[3][V], uint32_t r, int c) {
+    const bool wide = cpr >= RT;  // one partial per block
+    const uint32_t b = (uint32_t)(b0 + (int)threadIdx.x / (64 * gw) * NP);
+    const uint32_t nrows = (uint32_t)d.jtot * (uint32_t)d.ktot, jt = (uint32_t)d.jtot;  // below 2^31
+    const T *f3[3] = {f0, f1, f2};
+    double acc[NP][3];
+#pragma unroll
+    for (int p = 0; p < NP; ++p)
+#pragma unroll
+        for (int q = 0; q < 3; ++q) acc[p][q] = 0.0;
+    auto load = [&](T (&x)[3][V], uint32_t r, int c) {
         const int64_t o = at(d, 1 + c * V, 1 + (int)(r % jt), 1 + (int)(r / jt));
 #pragma unroll
-        for (int f = 0; f < 3; ++f) vload<double, V>(x[f], f3[f] + o);
+        for (int f = 0; f < 3; ++f) vload<T, V>(x[f], f3[f] + o);
     };
-    auto add = [&](const double (&x)[3][V], uint32_t r) {
+    auto add = [&](double (&a)[3], const T (&x)[3][V], uint32_t r) {
         const int k = 1 + (int)(r / jt);
-        const double wz = 1.0 / dzi[k], wzh = 1.0 / dzhi[k];
+        const double wz = 1.0 / (double)dzi[k], wzh = 1.0 / (double)dzhi[k];
 #pragma unroll
         for (int n = 0; n < V; ++n) {
-            acc[0] += x[0][n] * wz;
-            acc[1] += x[1][n] * wz;
-            if (k >= kw0) acc[2] += x[2][n] * wzh;
+            a[0] += (double)x[0][n] * wz;
+            a[1] += (double)x[1][n] * wz;
+            if (k >= kw0) a[2] += (double)x[2][n] * wzh;
         }
     };
-    if (cpr < RT) {
-        const int rpp = RT / cpr, slot = (int)threadIdx.x / cpr, c = (int)threadIdx.x % cpr;
+    if (!wide) {
+        const int rpp = RT / cpr, slot = t / cpr, c = t % cpr;
         const uint32_t step = (uint32_t)rpp * RB;
+        constexpr int M = 4 / NP;
         if (slot < rpp)
-            for (uint32_t r = (uint32_t)b + (uint32_t)slot * RB; r < nrows; r += SUM_ROWS * step) {
-                double x[SUM_ROWS][3][V];
+            for (uint32_t r = b + (uint32_t)slot * RB; r < nrows; r += M * step) {
+                T x[M][NP][3][V];
 #pragma unroll
-                for (int m = 0; m < SUM_ROWS; ++m) load(x[m], r + m * step < nrows ? r + m * step : r, c);
+                for (int m = 0; m < M; ++m)
 #pragma unroll
-                for (int m = 0; m < SUM_ROWS; ++m)
-                    if (r + m * step < nrows) add(x[m], r + m * step);
+                    for (int p = 0; p < NP; ++p) load(x[m][p], min(r + m * step + p, nrows - 1), c);
+#pragma unroll
+                for (int m = 0; m < M; ++m)
+#pragma unroll
+                    for (int p = 0; p < NP; ++p)
+                        if (r + m * step + p < nrows) add(acc[p], x[m][p], r + m * step + p);
             }
     } else {  // pairs of rows, chunk by chunk
-        uint32_t r = (uint32_t)b;
+        uint32_t r = b;
         for (; r + RB < nrows; r += 2 * RB)
-            for (int c = (int)threadIdx.x; c < cpr; c += 2 * RT) {
+            for (int c = t; c < cpr; c += 2 * RT) {
                 const bool two = c + RT < cpr;
                 const int c2 = two ? c + RT : c;
-                double x[4][3][V];
+                T x[4][3][V];
                 load(x[0], r, c);
                 load(x[1], r + RB, c);
                 load(x[2], r, c2);
                 load(x[3], r + RB, c2);
-                add(x[0], r);
-                add(x[1], r + RB);
+                add(acc[0], x[0], r);
+                add(acc[0], x[1], r + RB);
                 if (two) {
-                    add(x[2], r);
-                    add(x[3], r + RB);
+                    add(acc[0], x[2], r);
+                    add(acc[0], x[3], r + RB);
                 }
             }
         if (r < nrows)
-            for (int c = (int)threadIdx.x; c < cpr; c += RT) {
-                double x[3][V];
+            for (int c = t; c < cpr; c += RT) {
+                T x[3][V];
                 load(x, r, c);
-                add(x, r);
+                add(acc[0], x, r);
             }
     }
-    sum_tree(acc, (int)blockDim.x >> 6, partial + b, nb);
+    sum_tree<NP>(acc, gw, partial + b, wide ? 1 : nb - (int)b, nb);
 }
 
-template <int V>
-__global__ __launch_bounds__(RT) void sum_rows_pass1(Dims d, int kw0, const double *f0, const double *f1,
-                                                    const double *f2, const double *dzi, const double *dzhi,
-                                                    double *partial)
+template <typename T, int V>
+__global__ __launch_bounds__(RT) void sum_rows_pass1(Dims d, int kw0, const T *f0, const T *f1, const T *f2,
+                                                    const T *dzi, const T *dzhi, int nb, int gw, double *partial)
 {
-    sum_rows<V>(d, kw0, f0, f1, f2, dzi, dzhi, (int)blockIdx.x, (int)gridDim.x, partial);
+    sum_rows<T, V, 1>(d, kw0, f0, f1, f2, dzi, dzhi, (int)blockIdx.x * (4 / gw), nb, gw, partial);
 }
 
-// Pass 2 by the first RT threads: thread t sums partials t, t + RT, ...
+// Pass 2 by one block: thread t sums partials t, t + RT, ...
 __device__ __forceinline__ void sum_rows_final(const double *partial, int nb, double *out)
 {
-    double acc[3] = {0.0, 0.0, 0.0};
-    if (threadIdx.x < RT) {
+    double acc[1][3] = {{0.0, 0.0, 0.0}};
 #pragma unroll
-        for (int m = 0; m < RB / RT; ++m) {
-            const int b = m * RT + (int)threadIdx.x;
+    for (int m = 0; m < RB / RT; ++m) {
+        const int b = m * RT + (int)threadIdx.x;
 #pragma unroll
-            for (int q = 0; q < 3; ++q) acc[q] += b < nb ? partial[(int64_t)q * nb + b] : 0.0;
-        }
+        for (int q = 0; q < 3; ++q) acc[0][q] += b < nb ? partial[(int64_t)q * nb + b] : 0.0;
     }
-    sum_tree(acc, 4, out, 1);
+    sum_tree<1>(acc, RT / 64, out, 1, 1);
 }
 
 __global__ __launch_bounds__(RT) void sum_rows_pass2(const double *partial, int nb, double *out)
@@ -653,13 +648,12 @@ __global__ __launch_bounds__(RT) void sum_rows_pass2(const double *partial, int 
 
 // Conservation sums of many grids in two launches: pass-1 block blockIdx.x is
 // block b of job g, (g, b) = blocks[blockIdx.x], into that job's own partials;
-// pass 2 reduces each grid's partials in one block.  Per grid the pieces,
+// pass 2 reduces each grid's partials in one block.  Per grid the rows,
 // blocks and trees are those of the single-grid reduction, so each grid's
 // sums are bitwise those of kl_reduce_fp64.
 struct SumJob {
     Dims d;
-    RedPlan pl;
-    int kw0;
+    int kw0, nb, gw;
     int64_t first;  // the job's first partial
     const void *f0, *f1, *f2, *dzi, *dzhi;
 };
@@ -670,24 +664,15 @@ __global__ __launch_bounds__(RT) void sums_batch_pass1(const SumJob *__restrict_
 {
     const int2 gb = blocks[blockIdx.x];
     const SumJob j = jobs[gb.x];
-    if constexpr (sizeof(T) == 8)
-        sum_rows<V>(j.d, j.kw0, as_global((const T *)j.f0), as_global((const T *)j.f1), as_global((const T *)j.f2),
-                    as_global((const T *)j.dzi), as_global((const T *)j.dzhi), gb.y, j.pl.nb, partials + j.first);
-    else
-        reduce_block<T, V, 0>(j.d, j.pl, j.kw0, as_global((const T *)j.f0), as_global((const T *)j.f1),
-                              as_global((const T *)j.f2), as_global((const T *)j.dzi), as_global((const T *)j.dzhi),
-                              gb.y, partials + j.first);
+    sum_rows<T, V, SUM_P>(j.d, j.kw0, as_global((const T *)j.f0), as_global((const T *)j.f1),
+                          as_global((const T *)j.f2), as_global((const T *)j.dzi), as_global((const T *)j.dzhi), gb.y, j.nb, j.gw, partials + j.first);
 }
 
-__global__ __launch_bounds__(RT2) void sums_batch_pass2(const longlong2 *__restrict__ slots, const double *partials,
+__global__ __launch_bounds__(RT) void sums_batch_pass2(const longlong2 *__restrict__ slots, const double *partials,
                                                        double *out)
 {
-    const longlong2 sl = slots[blockIdx.x];  // first partial and number of blocks of this grid, negative: FP64
-    double *o = out + 3 * (int64_t)blockIdx.x;
-    if (sl.y < 0)
-        sum_rows_final(partials + sl.x, (int)-sl.y, o);
-    else
-        reduce_final<0>(partials + sl.x, (int)sl.y, o);
+    const longlong2 sl = slots[blockIdx.x];  // first partial and number of blocks of this grid
+    sum_rows_final(partials + sl.x, (int)sl.y, out + 3 * (int64_t)blockIdx.x);
 }
 
 // Bit hash: sum over interior cells (mod 2^64) of SplitMix64(bits ^ cell key).
@@ -866,20 +851,21 @@ hipError_t launch_zero_interior(const HostArgs &a, void *f, hipStream_t s)
 
 namespace {
 template <typename T, int V>
-void launch_pass1(const HostArgs &a, const RedPlan &pl, int what, const void *f0, const void *f1, const void *f2,
+void sums_go(const HostArgs &a, int nb, const void *f0, const void *f1, const void *f2, double *partial,
+             hipStream_t s)
+{
+    const int gw = sum_rows_waves(a, V);
+    hipLaunchKernelGGL((sum_rows_pass1<T, V>), dim3(cdiv(nb, 4 / gw)), dim3(RT), 0, s, dims_of(a), a.kw0,
+                       (const T *)f0, (const T *)f1, (const T *)f2, (const T *)a.dzi, (const T *)a.dzhi, nb, gw,
+                       partial);
+}
+
+template <typename T, int V>
+void launch_pass1(const HostArgs &a, const RedPlan &pl, const void *f0, const void *f1, const void *f2,
                   double *partial, hipStream_t s)
 {
-    const Dims d = dims_of(a);
-    const T *p[3] = {(const T *)f0, (const T *)f1, (const T *)f2};
-    if constexpr (sizeof(T) == 4) {  // FP64: sum_rows_pass1
-        if (what == 0) {
-            hipLaunchKernelGGL((reduce_pass1<T, V, 0>), dim3(pl.nb), dim3(RT), 0, s, d, pl, a.kw0, p[0], p[1], p[2],
-                               (const T *)a.dzi, (const T *)a.dzhi, partial);
-            return;
-        }
-    }
-    hipLaunchKernelGGL((reduce_pass1<T, V, 1>), dim3(pl.nb), dim3(RT), 0, s, d, pl, a.kw0, p[0], p[1], p[2],
-                       (const T *)a.dzi, (const T *)a.dzhi, partial);
+    hipLaunchKernelGGL((reduce_pass1<T, V>), dim3(pl.nb), dim3(RT), 0, s, dims_of(a), pl, (const T *)f0,
+                       (const T *)f1, (const T *)f2, partial);
 }
 }  // namespace
 
@@ -888,13 +874,14 @@ hipError_t launch_reduce(const HostArgs &a, int what, const void *f0, const void
 {
     double *partial = (double *)scratch;
     if ((int64_t)a.jtot * a.ktot >= ((int64_t)1 << 31)) return hipErrorInvalidValue;  // 32-bit piece index
-    if (what == 0 && a.dtype == KL_F64) {
-        const Dims d = dims_of(a);
-        const int V = sum_rows_aligned(a, f0, f1, f2) ? 2 : 1, nb = sum_rows_blocks(a);
-        auto *k = V == 2 ? &sum_rows_pass1<2> : &sum_rows_pass1<1>;
-        hipLaunchKernelGGL(k, dim3(nb), dim3(sum_rows_threads(a, V)), 0, s, d, a.kw0, (const double *)f0,
-                           (const double *)f1, (const double *)f2, (const double *)a.dzi, (const double *)a.dzhi,
-                           partial);
+    if (what == 0) {
+        const int V = sum_rows_chunk(a, f0, f1, f2), nb = sum_rows_blocks(a);
+        if (a.dtype == KL_F32)
+            V == 4 ? sums_go<float, 4>(a, nb, f0, f1, f2, partial, s)
+                   : sums_go<float, 1>(a, nb, f0, f1, f2, partial, s);
+        else
+            V == 2 ? sums_go<double, 2>(a, nb, f0, f1, f2, partial, s)
+                   : sums_go<double, 1>(a, nb, f0, f1, f2, partial, s);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
         hipLaunchKernelGGL(sum_rows_pass2, dim3(1), dim3(RT), 0, s, (const double *)partial, nb, out);
@@ -904,21 +891,18 @@ hipError_t launch_reduce(const HostArgs &a, int what, const void *f0, const void
     const bool vec = row_chunk(a) > 1;
     if (a.dtype == KL_F32) {
         if (vec)
-            launch_pass1<float, 4>(a, pl, what, f0, f1, f2, partial, s);
+            launch_pass1<float, 4>(a, pl, f0, f1, f2, partial, s);
         else
-            launch_pass1<float, 1>(a, pl, what, f0, f1, f2, partial, s);
+            launch_pass1<float, 1>(a, pl, f0, f1, f2, partial, s);
     } else {
         if (vec)
-            launch_pass1<double, 2>(a, pl, what, f0, f1, f2, partial, s);
+            launch_pass1<double, 2>(a, pl, f0, f1, f2, partial, s);
         else
-            launch_pass1<double, 1>(a, pl, what, f0, f1, f2, partial, s);
+            launch_pass1<double, 1>(a, pl, f0, f1, f2, partial, s);
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    if (what == 0)
-        hipLaunchKernelGGL(reduce_pass2<0>, dim3(1), dim3(RT2), 0, s, (const double *)partial, pl.nb, out);
-    else
-        hipLaunchKernelGGL(reduce_pass2<1>, dim3(1), dim3(RT2), 0, s, (const double *)partial, pl.nb, out);
+    hipLaunchKernelGGL(reduce_pass2, dim3(1), dim3(RT2), 0, s, (const double *)partial, pl.nb, out);
     return hipGetLastError();
 }
 
@@ -971,7 +955,7 @@ size_t sum_job_bytes() { return sizeof(SumJob); }
 
 bool sums_vectorized(const HostArgs &a, const void *ut, const void *vt, const void *wt)
 {
-    return a.dtype == KL_F64 ? sum_rows_aligned(a, ut, vt, wt) : row_chunk(a) > 1;
+    return sum_rows_chunk(a, ut, vt, wt) > 1;
 }
 
 void append_sum_job(const HostArgs &a, const void *ut, const void *vt, const void *wt, std::vector<char> &jobs,
@@ -981,8 +965,9 @@ void append_sum_job(const HostArgs &a, const void *ut, const void *vt, const voi
     SumJob j;
     memset(&j, 0, sizeof j);
     j.d = dims_of(a);
-    j.pl = red_plan(a);
-    if (a.dtype == KL_F64) j.pl.nb = sum_rows_blocks(a);
+    j.nb = sum_rows_blocks(a);
+    const int V = sum_rows_chunk(a, ut, vt, wt), per = a.itot / V >= RT ? 1 : 4 / sum_rows_waves(a, V) * SUM_P;
+    j.gw = sum_rows_waves(a, V);
     j.kw0 = a.kw0;
     j.first = *npartials;
     j.f0 = ut;
@@ -990,12 +975,12 @@ void append_sum_job(const HostArgs &a, const void *ut, const void *vt, const voi
     j.f2 = wt;
     j.dzi = a.dzi;
     j.dzhi = a.dzhi;
-    for (int b = 0; b < j.pl.nb; ++b) blocks.push_back(make_int2(job, b));
+    for (int b = 0; b < j.nb; b += per) blocks.push_back(make_int2(job, b));
     longlong2 sl;
     sl.x = j.first;
-    sl.y = a.dtype == KL_F64 ? -j.pl.nb : j.pl.nb;
+    sl.y = j.nb;
     slots.push_back(sl);
-    *npartials += 3 * (int64_t)j.pl.nb;
+    *npartials += 3 * (int64_t)j.nb;
     const char *p = (const char *)&j;
     jobs.insert(jobs.end(), p, p + sizeof j);
 }
@@ -1024,7 +1009,7 @@ hipError_t launch_sums_batch(int dtype, bool vec, const void *jobs, const void *
 hipError_t launch_sums_finish(const void *slots, const double *partials, int nslots, double *out, hipStream_t s)
 {
     if (nslots <= 0) return hipSuccess;
-    hipLaunchKernelGGL(sums_batch_pass2, dim3((unsigned)nslots), dim3(RT2), 0, s, (const longlong2 *)slots, partials,
+    hipLaunchKernelGGL(sums_batch_pass2, dim3((unsigned)nslots), dim3(RT), 0, s, (const longlong2 *)slots, partials,
                        out);
     return hipGetLastError();
 }

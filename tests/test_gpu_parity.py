@@ -282,7 +282,7 @@ def test_reduction_pieces_match_oracle(dtype, shape, layout):
 
 
 def sums_in_order(x, wz, wzh, kw0, v):
-    """The FP64 conservation sums, added in their fixed order: partial r % 4096
+    """The conservation sums, added in their fixed order: partial r % 4096
     of row r, 256 threads per partial over chunks of v points (slots of rows
     where a row has fewer than 256 chunks, pairs of rows where it has more),
     the threads' sums combined by halving, and the same over the partials."""
@@ -328,22 +328,25 @@ def sums_in_order(x, wz, wzh, kw0, v):
 
 
 @pytest.mark.parametrize("layout", ["padded", "plain"])
-@pytest.mark.parametrize("shape", [(1, 1, 2), (48, 5, 7), (45, 90, 100), (516, 3, 4), (301, 70, 60)],
+@pytest.mark.parametrize("shape", [(1, 1, 2), (48, 5, 7), (45, 90, 100), (96, 50, 82), (516, 3, 4), (301, 70, 60)],
                          ids=lambda s: "x".join(map(str, s)))
-def test_fp64_sums_keep_their_order(shape, layout):
-    """Sums that vanish exactly are their own rounding, so FP64 sums are held
-    to their order of additions bit for bit: one thread or several slots per
-    partial, more rows than partials, rows wider than the block, aligned rows
-    (two points per load) and unaligned ones."""
+@pytest.mark.parametrize("dtype", [0, 1], ids=["f32", "f64"])
+def test_conservation_sums_keep_their_order(dtype, shape, layout):
+    """Sums that vanish are their own rounding, so the sums are held to their
+    order of additions bit for bit: one wave, two and four waves per partial,
+    one slot and several, more rows than partials, rows wider than the block, aligned rows
+    (16 bytes per load) and unaligned ones."""
     import torch
     m = kl()
     lay = inputs.plain_layout(*shape) if layout == "plain" else None
     bc = 2 if shape[2] < 3 else 0
-    c = Case(*shape, 1, bc=bc, seed=15, layout=lay)
+    c = Case(*shape, dtype, bc=bc, seed=15, layout=lay)
     out = torch.zeros(3, dtype=torch.float64, device="cuda")
     m.kl_reduce_fp64(c.g, 0, *c.dev, out)
     og = c.og
-    v = 2 if shape[0] % 2 == 0 and (og.off + 1) % 2 == 0 and og.js % 2 == 0 and og.ks % 2 == 0 else 1
+    v = 4 if dtype == 0 else 2
+    if shape[0] % v or (og.off + 1) % v or og.js % v or og.ks % v:
+        v = 1
     x = [c.interior_np(h) for h in c.host]
     ref = sums_in_order(x, 1.0 / og.dzi[1:shape[2] + 1], 1.0 / og.dzhi[1:shape[2] + 1], 1 if bc == 2 else 2, v)
     assert np.array_equal(out.cpu().numpy(), ref)
