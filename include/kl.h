@@ -318,7 +318,7 @@ int kl_launch_variant_dt(const kl_grid_t *g, int32_t kernel, int32_t index,
  * problem size and caches the choice).  Where the heuristic of
  * kl_wisdom_lookup finds only records of other problem sizes, the second-order
  * kernels and the fused step run a configuration that sizes itself to the
- * grid ("rf_t256") on grids of 2^19 points or more (the fused step on all)
+ * grid ("rf_t256", "rf_t512") on grids of 2^19 points or more (the fused step on all)
  * whose rows it takes, else the nearest record's; advec_u_2i5 and diff_smag
  * run theirs ("rf_t512") from 2^19 points, the default below. */
 int kl_selected_variant(const kl_grid_t *g, int32_t kernel);

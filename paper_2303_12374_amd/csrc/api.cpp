@@ -197,8 +197,16 @@ namespace {
 // nearest record's 7% and 95%.  Below 2^19 points the launches count and the
 // one-thread-per-point default is as fast or faster (64^3 FP32 diff_uvw 6.8
 // against 7.6 us; 80^3 9.9 against 8.8), the fused step excepted, which has
-// none.  Longer rows (more than 80 chunks) take the nearest record's: with 512
-// threads the row-flattened tile is up to 48% from the fastest there.
+// none.
+// Longer rows (81 to 256 chunks) take the form with 512 threads where its rows
+// fill the block (13/16 of the threads; rows of 192 chunks, two to a block, are
+// up to 48% slower): diff_uvw and the fused pass always (300x300x150 FP64 184
+// and 183 us, the nearest records' 238 and 222; 400x100x50 FP32 diff_uvw 19
+// against 38), the fused step (two buffers in turn) below 6e6 points
+// (200x150x150 FP64 56 us, the fastest other 63; 400x100x50 FP32 18 against 25;
+// 320x223x100 FP64, above, 100 against 90) or where rows leave a fifth of the
+// wave-per-row tiles' lanes idle (192^3 FP64 95 against 112; 330x330x200 FP64,
+// an eighth idle, 284 against 256).
 // The paper's schemes have one row-flattened tile, fastest or within 2% of it
 // at every size tried from 2^19 points up (200^3 FP32 advec_u_2i5 34 against
 // 61 us for the nearest record's); below, the default (100x37x61 9.4 against
@@ -209,7 +217,15 @@ int unrecorded_variant(const kl_grid_t *g, int kernel)
     const bool small = (int64_t)g->itot * g->jtot * g->ktot < ((int64_t)1 << 19);
     if (small && les) return 0;
     if (small && kernel != KL_KERNEL_STEP) return -1;
-    const int threads = les ? 512 : 256;
+    const int V = g->dtype == KL_F32 ? 4 : 2, cpr = rf_chunks(g->itot, V);
+    int threads = les ? 512 : 256;
+    if (!les && cpr > rf_max_chunks(256)) {
+        if (kernel == KL_KERNEL_ADVEC_U || cpr > rf_max_chunks(512) || 512 / cpr * cpr < 416) return -1;
+        const bool few = (double)g->itot * g->jtot * g->ktot < 6e6;
+        const bool idle = g->itot < 0.8 * ((cpr + 63) / 64) * 64 * V;
+        if (kernel == KL_KERNEL_STEP && !few && !idle) return -1;
+        threads = 512;
+    }
     const auto &vs = variants(kernel, g->dtype);
     for (size_t n = 0; n < vs.size(); ++n)
         if (vs[n].family == FAMILY_RF && vs[n].bx == threads && variant_eligible(vs[n], g, nullptr, 0)) return (int)n;
