@@ -28,23 +28,31 @@ METRIC = "grid-points/s & HBM GB/s (% peak), advec_u+diff_uvw 512^3 FP32; p99 la
 PEAK_HBM_GBPS = 8000.0  # MI355X HBM3E, published
 _CSRC = "paper_2303_12374_amd/csrc/"
 # device sources whose change invalidates a kernel's recorded counters
+_SECOND = [_CSRC + f for f in ("stencil.hpp", "stencil_zl.hpp", "stencil_rf.hpp")]
+_LES = _SECOND + [_CSRC + f for f in ("stencil_les.hpp", "stencil_les_zl.hpp", "stencil_les_rf.hpp")]
 KERNEL_SOURCES = {
-    "advec_u": [_CSRC + "stencil.hpp", _CSRC + "stencil_zl.hpp"],
-    "diff_uvw": [_CSRC + "stencil.hpp", _CSRC + "stencil_zl.hpp"],
-    "advec_u_2i5": [_CSRC + "stencil.hpp", _CSRC + "stencil_zl.hpp", _CSRC + "stencil_les.hpp",
-                    _CSRC + "stencil_les_zl.hpp"],
-    "diff_smag": [_CSRC + "stencil.hpp", _CSRC + "stencil_zl.hpp", _CSRC + "stencil_les.hpp",
-                  _CSRC + "stencil_les_zl.hpp"],
-    "step": [_CSRC + "stencil.hpp", _CSRC + "stencil_zl.hpp", _CSRC + "stencil_step.hpp"],
-    "advec_diff": [_CSRC + "stencil.hpp", _CSRC + "stencil_zl.hpp", _CSRC + "stencil_step.hpp"],
+    "advec_u": _SECOND,
+    "diff_uvw": _SECOND,
+    "advec_u_2i5": _LES,
+    "diff_smag": _LES,
+    "step": _SECOND + [_CSRC + "stencil_step.hpp"],
+    "advec_diff": _SECOND + [_CSRC + "stencil_step.hpp"],
 }
 
 
 def kernel_of_symbol(sym):
     """Library kernel a rocprofv3 kernel symbol belongs to, or None.  The
     step tile serves both the fused step (bit 0 of the last template argument
-    clear) and the fused advec_u + diff_uvw pass (set)."""
+    clear) and the fused advec_u + diff_uvw pass (set); the row-flattened tile
+    has the parts it computes in its third argument."""
     import re
+    m = re.search(r"kl::rf_(kernel|batch)<\w+, \d+, (\d+)", sym)
+    if m:
+        mode = int(m.group(2))
+        return "step" if mode & 8 else {1: "advec_u", 2: "diff_uvw", 3: "advec_diff"}[mode & 3]
+    m = re.search(r"kl::(advec_u_2i5|diff_smag)_rf<", sym)
+    if m:
+        return m.group(1)
     m = re.search(r"kl::(\w+?)_(zl3|zlp|zl|zr|zc|plain)(_batch)?<([^>]*)>", sym)
     if not m:
         m = re.search(r"kl::(step)_zl(_batch)?<([^>]*)>", sym)
@@ -224,7 +232,7 @@ def batched_leg(kl, inputs, torch, steps=10, warmup=3, tune_dir=None):
             "bytes_note": "the graph runs the fused pass: 9 values per point (u, v, w, ut, vt, wt read; "
                           "ut, vt, wt written); the two separate kernels move 14",
             "hbm_gbps_14_value_equivalent": 14 * 4 * npts / (batched_ms * 1e6),
-            "full_graph": {"steps": "ghost fill -> tendencies := 0 -> fused pass -> FP64 conservation sums",
+            "full_graph": {"steps": "ghost fill -> fused pass onto cleared tendencies (x ghosts written by it) -> FP64 conservation sums",
                            "graph_kernels": nkf, "ms": full_ms,
                            "grid_points_per_s": npts / (full_ms * 1e-3)}}
 
@@ -1127,7 +1135,7 @@ def main():
                       "fused_configuration": kl.kl_variant_name(kl.STEP, dtype, kl.kl_selected_variant(g, kl.STEP)),
                       "fused_grid_points_per_s": npts / (fused_ms * 1e-3),
                       "fused_hbm_gbps_6_values": 6 * s * npts / (fused_ms * 1e6),
-                      "separate_hbm_gbps_26_values": 26 * s * npts / (sep_ms * 1e6)}
+                      "separate_hbm_gbps_15_values": 15 * s * npts / (sep_ms * 1e6)}
     # FP64 reductions over the same grid: conservation sums of the tendencies
     # and checksums of the fields (3 fields read each, accumulated in double)
     log("FP64 reductions: conservation sums and checksums")
