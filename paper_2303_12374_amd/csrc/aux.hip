@@ -504,9 +504,10 @@ __global__ __launch_bounds__(RT2) void reduce_pass2(const double *partial, int n
 // over LDS (us): 512^3 FP32 351 -> 274 (5.9 TB/s), 128^3 27 -> 12,
 // 301x203x151 FP32 (one point per load) 102 -> 37; FP64 256^3 110 -> 76,
 // 301x203x151 69 -> 40.  In a batch the rows of a partial are few, so a group
-// of waves takes four partials at once: 56 grids FP32,
-// 0.2 million partials, the whole graph 807 us with one per block, 715 with one
-// per group, 646 with four.
+// of waves takes four partials at once: 56 grids FP32, 0.2 million partials,
+// the whole graph 807 us with one per block, 715 with one per group, 646 with
+// four.
+
 // Sums of NP values of acc over each group of gw waves (1, 2 or 4) of a block of
 // RT threads; partial p of the group goes to out + p if p < n.
 template <int NP>
