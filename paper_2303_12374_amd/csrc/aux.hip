@@ -193,6 +193,29 @@ RowPieces row_pieces(const HostArgs &a, int V, int64_t chunks_per_piece)
     return r;
 }
 
+// Pieces for blocks of 256 threads, a chunk each: rows that fit one, or, of longer
+// rows, as few as fill a whole number of blocks to 1 part in 32, else the up to 16
+// that fill them best.  Of long rows, one block with its chunks in a loop leaves
+// CUs idle on small grids, and blocks cut out of single rows end with one
+// nearly empty (Euler update, us; point per thread, block per row, now):
+// 2048x4x64 FP64 10.2, 15.1, 8.0; 1500x200x100 FP64 unpadded 398, 465, 411;
+// 1024x500x64 FP64 450, 417, 402; 560x300x100 FP64 238, 211, 200 (cut rows 240).
+RowPieces block_pieces(const HostArgs &a, int V)
+{
+    const int64_t cpr = (a.itot + V - 1) / V;
+    int64_t rows = 256 / cpr;
+    double unused = 1e300;
+    for (int64_t r = 1; cpr > 256 && r <= std::min(16, a.jtot) && (r == 1 || r * cpr <= 1 << 14); ++r) {
+        const double u = (double)((r * cpr + 255) / 256 * 256 - r * cpr) / (double)(r * cpr);
+        if (u < unused) {
+            unused = u;
+            rows = r;
+        }
+        if (u * 32 <= 1) break;
+    }
+    return row_pieces(a, V, rows * cpr);
+}
+
 // Points per 16-byte chunk, or 1 for rows narrower than that.
 inline int row_chunk(const HostArgs &a)
 {
@@ -293,38 +316,38 @@ __device__ __forceinline__ void euler_chunk(const Dims &d, T *p, int f, int i0, 
     }
 }
 
+// Block b: the 256 chunks of segment b % nseg of piece b / nseg.
 template <typename T, int V, int NT>
-__global__ __launch_bounds__(256) void euler_kernel(Dims d, RowPieces rp, T dt, int kw0, T *u, T *v, T *w,
-                                                   const T *ut, const T *vt, const T *wt)
+__global__ __launch_bounds__(256) void euler_kernel(Dims d, RowPieces rp, uint32_t nseg, T dt, int kw0, T *u, T *v,
+                                                   T *w, const T *ut, const T *vt, const T *wt)
 {
-    const uint32_t pc = blockIdx.x;
+    const uint32_t pc = blockIdx.x / nseg, e = (blockIdx.x % nseg) * 256 + threadIdx.x;
     const int k = 1 + (int)(pc / rp.ng);
     const uint32_t j0 = (pc % rp.ng) * rp.R;
     const uint32_t left = (uint32_t)d.jtot - j0;
     const uint32_t n = (left < rp.R ? left : rp.R) * rp.cpr;
+    if (e >= n) return;
     T *f3[3] = {u, v, w};
     const T *t3[3] = {ut, vt, wt};
     const int64_t base = at(d, 1, 1 + (int)j0, k);
-    for (uint32_t e = threadIdx.x; e < n; e += 256) {
-        const Chunk<V> c(rp, e, n);
-        const int64_t o = base + (int64_t)c.row * d.js + c.col;
-        T x[3][V], y[3][V];
+    const Chunk<V> c(rp, e, n);
+    const int64_t o = base + (int64_t)c.row * d.js + c.col;
+    T x[3][V], y[3][V];
 #pragma unroll
-        for (int f = 0; f < 3; ++f) {
-            if constexpr (NT)
-                uload_nt<T, V>(x[f], f3[f] + o);
-            else
-                uload<T, V>(x[f], f3[f] + o);
-            uload_nt<T, V>(y[f], t3[f] + o);
-        }
+    for (int f = 0; f < 3; ++f) {
+        if constexpr (NT)
+            uload_nt<T, V>(x[f], f3[f] + o);
+        else
+            uload<T, V>(x[f], f3[f] + o);
+        uload_nt<T, V>(y[f], t3[f] + o);
+    }
 #pragma unroll
-        for (int f = 0; f < 3; ++f) {
-            if (f == 2 && k < kw0) continue;
-            T val[V];
+    for (int f = 0; f < 3; ++f) {
+        if (f == 2 && k < kw0) continue;
+        T val[V];
 #pragma unroll
-            for (int i = 0; i < V; ++i) val[i] = euler_value<T>(x[f][i], dt, y[f][i]);
-            euler_chunk<T, V, NT>(d, f3[f], f, 1 + c.col, 1 + (int)j0 + c.row, k, c.lo, val);
-        }
+        for (int i = 0; i < V; ++i) val[i] = euler_value<T>(x[f][i], dt, y[f][i]);
+        euler_chunk<T, V, NT>(d, f3[f], f, 1 + c.col, 1 + (int)j0 + c.row, k, c.lo, val);
     }
 }
 
@@ -814,8 +837,9 @@ constexpr double EULER_CACHED_BYTES = 256e6;
 template <typename T, int V, int NT>
 void euler_go(const HostArgs &a, const Dims &d, const RowPieces &rp, double dt, void *u, void *v, void *w, hipStream_t s)
 {
-    hipLaunchKernelGGL((euler_kernel<T, V, NT>), dim3(rp.np), dim3(256), 0, s, d, rp, (T)dt, a.kw0, (T *)u, (T *)v,
-                       (T *)w, (const T *)a.ut, (const T *)a.vt, (const T *)a.wt);
+    const uint32_t nseg = (rp.R * rp.cpr + 255) / 256;  // above 1 where rows have more than 256 chunks
+    hipLaunchKernelGGL((euler_kernel<T, V, NT>), dim3(rp.np * nseg), dim3(256), 0, s, d, rp, nseg, (T)dt, a.kw0,
+                       (T *)u, (T *)v, (T *)w, (const T *)a.ut, (const T *)a.vt, (const T *)a.wt);
 }
 }  // namespace
 
@@ -827,7 +851,7 @@ hipError_t launch_euler(const HostArgs &a, double dt, void *u, void *v, void *w,
     if (narrow) d.gc = 1;
     if ((int64_t)a.jtot * a.ktot >= ((int64_t)1 << 31)) return hipErrorInvalidValue;  // 32-bit piece index
     const int V = row_chunk(a);
-    const RowPieces rp = row_pieces(a, V, 256);
+    const RowPieces rp = block_pieces(a, V);
     const bool nt = 3.0 * a.itot * a.jtot * a.ktot * (a.dtype == KL_F32 ? 4 : 8) > EULER_CACHED_BYTES;
     if (a.dtype == KL_F32)
         V == 4 ? (nt ? euler_go<float, 4, 1>(a, d, rp, dt, u, v, w, s) : euler_go<float, 4, 0>(a, d, rp, dt, u, v, w, s))
