@@ -87,53 +87,6 @@ HostArgs make_args(const kl_grid_t *g)
     return a;
 }
 
-// Segment width.  Where the rows divide into 32 chunks (512 bytes; padding of
-// less than 1/32 counts as dividing) a segment's lines are its own, and that is
-// fastest; 64 for advec_u_2i5 at V = 4 (512x512x128 FP32, us by width: 64 115,
-// 32 120, 43 150, 48 142; diff_smag 32 237, 43 313, 48 274).  Other rows: the
-// fewest segments whose taller halo still fits (301x203x151 FP32, 76 chunks:
-// 38 38.7, 26 44.9, 64 57.3); for three and more of diff_smag their width is
-// rounded up to a cache line (151 chunks: 40 148, 38 165, 51 does not fit).
-LesRfShape les_rf_shape(int kernel, int itot, int jtot, int vx)
-{
-    const bool a5 = kernel == KL_KERNEL_ADVEC_U_2I5;
-    const int cpr = rf_chunks(itot, vx), wmax = a5 ? (vx == 4 ? 64 : 60) : 48, hc = 4 / vx;
-    int W = cpr;
-    if (cpr > wmax) {
-        const int nsx = (cpr + wmax - 1) / wmax;
-        if ((cpr + 31) / 32 * 32 - cpr <= cpr / 32)
-            W = wmax == 64 && cpr % 64 == 0 ? 64 : 32;
-        else
-            W = (cpr + nsx - 1) / nsx;
-        if (!a5 && nsx > 2) W = (W + 7) / 8 * 8;
-    }
-    auto extra = [&](int R) { return a5 ? 6 * W + 2 * hc * (R + 6) + W + 2 * R + 1 : 8 * W + 8 * (R + 2); };
-    auto lds = [&](int R) {  // a chunk is 16 bytes
-        return a5 ? (size_t)2 * ((R + 6) * (W + 2 * hc) + (2 * R + 1) * (W + 1) + 64) * 16
-                  : (size_t)3 * (4 * (R + 2) * (W + 2) + 64) * 16;
-    };
-    int R = std::min(jtot, 512 / W);
-    while (R > 1 && (extra(R) > 512 || lds(R) > 160 * 1024)) --R;
-    const int blocks = (jtot + R - 1) / R;
-    R = (jtot + blocks - 1) / blocks;
-    return {W, R, (std::max(R * W, extra(R)) + 63) / 64 * 64, lds(R)};
-}
-
-int les_rf_levels(int slab, int ktot)
-{
-    int best = ktot;
-    double least = 1e300;
-    for (int nbz = 1; nbz <= 64 && (nbz == 1 || 2 * nbz <= ktot); ++nbz) {
-        const int kb = (ktot + nbz - 1) / nbz;
-        const double cost = (double)(((int64_t)slab * nbz + 255) / 256) * (kb + 5);
-        if (cost < least) {
-            least = cost;
-            best = kb;
-        }
-    }
-    return best;
-}
-
 bool variant_eligible(const Variant &v, const kl_grid_t *g, const void *const *ptrs, int nptr)
 {
     if (v.family == FAMILY_RF && (v.kernel == KL_KERNEL_ADVEC_U_2I5 || v.kernel == KL_KERNEL_DIFF_SMAG))

@@ -8,6 +8,7 @@
 #include <vector>
 
 #include "kl.h"
+#include "tile_shape.hpp"
 
 namespace kl {
 
@@ -71,38 +72,6 @@ struct Variant {
 const std::vector<Variant> &variants(int kernel, int dtype);
 const std::vector<Variant> &variants_f32(int kernel);
 const std::vector<Variant> &variants_f64(int kernel);
-
-// Row-flattened tiles (stencil_rf.hpp): rows of cpr = ceil(itot / vx) chunks,
-// R whole rows per block of at most `threads` threads.  A block also needs a
-// thread for every chunk of its two halo rows, and LDS for RF_PLANES planes of
-// R + 2 rows and a spare chunk per lane: blocks of 256 threads take rows of up
-// to 80 chunks (three rows, 52 KB, three blocks on a CU), blocks of 512 up to
-// 256 (two rows, 122 KB).
-constexpr int RF_PLANES = 7;  // u: 2, v: 2, w: 3
-inline int rf_chunks(int itot, int vx) { return (int)(((int64_t)itot + vx - 1) / vx); }
-inline int rf_max_chunks(int threads) { return threads == 256 ? 80 : 256; }
-inline int rf_rows(int jtot, int cpr, int threads)
-{
-    const int most = threads / cpr < jtot ? threads / cpr : jtot;
-    const int blocks = (jtot + most - 1) / most;
-    return (jtot + blocks - 1) / blocks;  // row blocks of equal height
-}
-inline size_t rf_lds_bytes(int cpr, int R) { return (size_t)RF_PLANES * ((R + 2) * cpr + 64) * 16; }
-constexpr size_t RF_LDS_256 = (size_t)RF_PLANES * (5 * 80 + 64) * 16, RF_LDS_512 = (size_t)RF_PLANES * (4 * 256 + 64) * 16;
-
-// Row-flattened tiles of the paper's schemes (stencil_les_rf.hpp): rows cut into
-// the fewest segments of at most 64 (advec_u_2i5; 60 of two points) or 48
-// (diff_smag) chunks, W each, and R rows, so that the block's chunks, the
-// chunks around it (one per thread) and the LDS fit a block of 512 threads.
-struct LesRfShape {
-    int W, R, threads;
-    size_t lds;
-};
-LesRfShape les_rf_shape(int kernel, int itot, int jtot, int vx);
-// Levels per tile of `slab` tiles per level slab: the fewest rounds of 256
-// tiles (one block per CU) times levels, a tile costing about five levels
-// more than it computes (its prologue and its end).
-int les_rf_levels(int slab, int ktot);
 
 // Errors: record a message for kl_last_error() and return `code`.
 int fail(int code, const char *fmt, ...) __attribute__((format(printf, 2, 3)));

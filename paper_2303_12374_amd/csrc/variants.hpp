@@ -176,13 +176,9 @@ int step_batch_occupancy()
     return e == hipSuccess && n > 0 ? n : 1;
 }
 
-// Row-flattened tiles.  Levels per tile: about 512 tiles (two per CU), at
-// least two levels each; longer marches read less twice, more tiles balance
-// better, and no other power of two was faster by more than 3% at the sizes
-// tried (64^3 .. 320x320x160, odd rows, both types).  Tendencies stream past
-// the caches when the arrays of a call exceed the memory-side cache (256 MB):
-// 301x203x151 FP32 diff_uvw (221 MB) 57 us cached, 60 streamed; 320x320x160
-// (393 MB) 115 cached, 95 streamed.
+// Row-flattened tiles.  Tendencies stream past the caches when the arrays of a
+// call exceed the memory-side cache (256 MB): 301x203x151 FP32 diff_uvw (221 MB)
+// 57 us cached, 60 streamed; 320x320x160 (393 MB) 115 cached, 95 streamed.
 template <typename T, int V, int MODE, int THREADS>
 hipError_t launch_rf(const HostArgs &h, hipStream_t s)
 {
@@ -190,7 +186,7 @@ hipError_t launch_rf(const HostArgs &h, hipStream_t s)
     a.rf_cpr = rf_chunks(h.itot, V);
     a.rf_rows = rf_rows(h.jtot, a.rf_cpr, THREADS);
     a.nby = (int)cdivu(h.jtot, a.rf_rows);
-    a.rf_kb = std::max(2, (int)cdivu(h.ktot, std::max(1, 512 / a.nby)));
+    a.rf_kb = rf_levels(a.nby, h.ktot);
     a.nbz = (int)cdivu(h.ktot, a.rf_kb);
     const uint64_t nb = (uint64_t)a.nby * a.nbz;
     a.nbx = a.nby % 8 == 0 ? a.nby : (int)nb;
