@@ -33,11 +33,29 @@ constexpr size_t RF_LDS_256 = (size_t)RF_PLANES * (5 * 80 + 64) * 16, RF_LDS_512
 // Levels per tile in a launch of nby row blocks: about 512 tiles (two per CU),
 // at least two levels each; longer marches read less twice, more tiles balance
 // better, and no other power of two was faster by more than 3% at the sizes
-// tried (64^3 .. 320x320x160, odd rows, both types).
-inline int rf_levels(int nby, int ktot)
+// tried (64^3 .. 320x320x160, odd rows, both types).  A block of 512 threads has
+// its CU to itself, so those tiles run in rounds of 256, and 300 of them leave
+// the second round nearly empty.  Where a march that fills the chip (240 tiles; the
+// fused pass at 384x380x64 FP32 took 63 us with 228, 57 with 456) needs a tenth
+// less, a tile costing five levels more than it computes, that one is taken:
+// 832x600x64 FP32 diff_uvw 304 -> 246 us, fused step 316 -> 233; 492x635x214 FP64
+// 1121 -> 940 and 1032 -> 762; 384x380x380 FP64 825 -> 739 and 856 -> 688.
+inline int rf_levels(int nby, int ktot, int threads)
 {
-    const int per = std::max(1, 512 / nby);
-    return std::max(2, (ktot + per - 1) / per);
+    const int per = std::max(1, 512 / nby), kb0 = std::max(2, (ktot + per - 1) / per);
+    if (threads != 512) return kb0;
+    auto tiles = [&](int kb) { return (int64_t)nby * ((ktot + kb - 1) / kb); };
+    auto cost = [&](int kb) { return (double)((tiles(kb) + 255) / 256) * (kb + 5); };
+    int best = kb0;
+    double least = 0.9 * cost(kb0);
+    for (int n = 1; n <= 16 && 8 * n <= ktot; ++n) {
+        const int kb = (ktot + n - 1) / n;
+        if (tiles(kb) >= 240 && cost(kb) < least) {
+            least = cost(kb);
+            best = kb;
+        }
+    }
+    return best;
 }
 
 // Row-flattened tiles of the paper's schemes (stencil_les_rf.hpp): rows cut into

@@ -186,7 +186,7 @@ hipError_t launch_rf(const HostArgs &h, hipStream_t s)
     a.rf_cpr = rf_chunks(h.itot, V);
     a.rf_rows = rf_rows(h.jtot, a.rf_cpr, THREADS);
     a.nby = (int)cdivu(h.jtot, a.rf_rows);
-    a.rf_kb = rf_levels(a.nby, h.ktot);
+    a.rf_kb = rf_levels(a.nby, h.ktot, THREADS);
     a.nbz = (int)cdivu(h.ktot, a.rf_kb);
     const uint64_t nb = (uint64_t)a.nby * a.nbz;
     a.nbx = a.nby % 8 == 0 ? a.nby : (int)nb;

@@ -1,7 +1,7 @@
 """Shapes of the row-flattened tiles, from the library's own functions
 (csrc/tile_shape.hpp compiled for the host): the fixed LDS that the persistent
 kernels reserve holds every grid's tile, a block has a thread for every chunk
-that it loads, and the levels per tile fill the CUs."""
+that it loads, and the levels per tile fill the CUs in rounds."""
 import ctypes
 import os
 import subprocess
@@ -16,6 +16,7 @@ int max_chunks(int t) { return kl::rf_max_chunks(t); }
 int rows(int j, int c, int t) { return kl::rf_rows(j, c, t); }
 long lds(int c, int r) { return (long)kl::rf_lds_bytes(c, r); }
 long lds_fixed(int t) { return (long)(t == 256 ? kl::RF_LDS_256 : kl::RF_LDS_512); }
+int levels(int nby, int k, int t) { return kl::rf_levels(nby, k, t); }
 int les_levels(int slab, int k) { return kl::les_rf_levels(slab, k); }
 void les_shape(int kernel, int i, int j, int vx, long *o)
 {
@@ -49,6 +50,27 @@ def test_tiles_fit_the_block_and_the_reserved_lds(lib, threads):
             assert 1 <= R <= j and R * cpr <= threads
             assert -(-j // R) == -(-j // min(threads // cpr, j))  # equal heights, as few blocks
             assert lib.lds(cpr, R) <= lib.lds_fixed(threads) <= 160 * 1024
+
+
+def cost(nby, ktot, kb):
+    return -(-nby * -(-ktot // kb) // 256) * (kb + 5)
+
+
+@pytest.mark.parametrize("nby", [1, 2, 3, 16, 25, 50, 64, 100, 107, 125, 128, 149, 185, 190, 200, 250, 256, 257, 300, 318,
+                                 353, 400, 512, 513, 1000])
+def test_levels_leave_no_round_nearly_empty(lib, nby):
+    """Blocks of 512 threads run 256 at a time: no march of whole slabs that fills
+    the chip needs a tenth less (levels and five more a tile, times rounds)."""
+    for ktot in (1, 2, 7, 8, 9, 17, 32, 50, 64, 80, 100, 137, 151, 214, 264, 380, 512, 1000):
+        kb = lib.levels(nby, ktot, 512)
+        assert kb >= 2
+        for n in range(1, min(16, ktot // 8) + 1):
+            k = -(-ktot // n)
+            if nby * -(-ktot // k) >= 240:
+                assert cost(nby, ktot, kb) <= cost(nby, ktot, k) / 0.9 + 1e-9, (ktot, kb, k)
+        # two blocks of 256 threads share a CU: about 512 tiles
+        kb = lib.levels(nby, ktot, 256)
+        assert kb == max(2, -(-ktot // max(1, 512 // nby)))
 
 
 def test_thin_grids_of_the_papers_schemes_fill_the_cus(lib):
