@@ -364,7 +364,10 @@ int kl_wisdom_lookup(const char *wisdom_dir, int32_t kernel, int32_t dtype, cons
  * wisdom_dir (NULL = current wisdom directory), and the selection cache is
  * cleared.  fields = {u, v, w, ut, vt, wt} (plus evisc as a seventh entry
  * when diff_smag is tuned): u, v, w (and evisc) must be ghost-filled;
- * ut, vt, wt are clobbered.  Synchronous (returns after the file is written).
+ * ut, vt, wt are clobbered.  The fused step is timed from one field set into
+ * another and back, as a program steps (ut, vt, wt and three fields allocated
+ * for the call; repeated on u, v, w where there is no memory for those).
+ * Synchronous (returns after the file is written).
  * If timings_out is not NULL it receives up to max_timings entries of
  * (configuration index, median ms) for kernel_mask's lowest kernel, or -1 ms
  * for a configuration that failed the bitwise check; *n_timings = count. */
