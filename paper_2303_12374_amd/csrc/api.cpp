@@ -1,6 +1,7 @@
 // C-ABI entry points: argument checks, layout, the selection cache and
 // dispatch of the tendency kernels, ghost fill, Euler step and reductions.
 #include <hip/hip_runtime.h>
+#include <math.h>
 #include <stdarg.h>
 #include <stdio.h>
 #include <string.h>
@@ -143,6 +144,42 @@ void clear_plans()
 }
 
 namespace {
+int variant_index(int kernel, int dtype, const std::string &name)
+{
+    const auto &vs = variants(kernel, dtype);
+    for (size_t n = 0; n < vs.size(); ++n)
+        if (name == vs[n].name) return (int)n;
+    return -1;
+}
+
+// Whether v takes rows of g's length at all; the layout and the pointers of a
+// call decide the rest (variant_eligible).
+bool takes_row_length(const Variant &v, const kl_grid_t *g)
+{
+    if (v.family != FAMILY_RF) return g->itot % v.vx == 0;
+    if (v.kernel == KL_KERNEL_ADVEC_U_2I5 || v.kernel == KL_KERNEL_DIFF_SMAG) return g->itot >= 8;
+    return rf_chunks(g->itot, v.vx) <= rf_max_chunks(v.bx);
+}
+
+// The nearest record whose configuration takes rows of g's length, or the default.
+int nearest_usable(const kl_grid_t *g, int kernel, const std::vector<SizeRecord> &records)
+{
+    const double want[3] = {(double)g->itot, (double)g->jtot, (double)g->ktot};
+    int index = 0;
+    double best = INFINITY;
+    for (const SizeRecord &r : records) {
+        const int n = variant_index(kernel, g->dtype, r.variant);
+        if (n < 0 || !takes_row_length(variants(kernel, g->dtype)[n], g)) continue;
+        double d2 = 0;
+        for (int a = 0; a < 3; ++a) d2 += (r.size[a] - want[a]) * (r.size[a] - want[a]);
+        if (d2 <= best) {
+            best = d2;
+            index = n;
+        }
+    }
+    return index;
+}
+
 // The configuration of a problem size that no record names, where the nearest
 // record's is fixed for another size: the row-flattened tile with 256 threads
 // sizes itself to the grid.  Over 42 tuned sizes and four kernels, each left
@@ -202,14 +239,12 @@ int select_variant(const kl_grid_t *g, int kernel)
         std::string name;
         int level = 5;
         bool same_size = false;
-        if (wisdom_select(wisdom_dir(), kernel, g->dtype, id, g->itot, g->jtot, g->ktot, &name, &level, &same_size) ==
-                KL_OK &&
+        std::vector<SizeRecord> records;
+        if (wisdom_select(wisdom_dir(), kernel, g->dtype, id, g->itot, g->jtot, g->ktot, &name, &level, &same_size,
+                          &records) == KL_OK &&
             level < 5) {
-            const auto &vs = variants(kernel, g->dtype);
-            for (size_t n = 0; n < vs.size(); ++n)
-                if (name == vs[n].name) index = (int)n;
-            const int own = same_size ? -1 : unrecorded_variant(g, kernel);
-            if (own >= 0) index = own;
+            index = same_size ? std::max(0, variant_index(kernel, g->dtype, name)) : unrecorded_variant(g, kernel);
+            if (index < 0) index = nearest_usable(g, kernel, records);
         }
     }
     std::lock_guard<std::mutex> lk(g_plan_mu);

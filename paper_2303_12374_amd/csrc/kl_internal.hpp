@@ -149,9 +149,15 @@ int current_device_ident(DeviceIdent *out);
 std::string wisdom_dir();
 std::string wisdom_path(const std::string &dir, int kernel);
 const char *kernel_name(int kernel);
-// *same_size (if not null): whether the chosen record is of this very problem size.
-int wisdom_select(const std::string &dir, int kernel, int dtype, const DeviceIdent &dev,
-                  int itot, int jtot, int ktot, std::string *variant, int *level, bool *same_size = nullptr);
+// *same_size (if not null): whether the chosen record is of this very problem
+// size; *records (if not null): the records the choice was made from, in file order.
+struct SizeRecord {
+    double size[3];
+    std::string variant;
+};
+int wisdom_select(const std::string &dir, int kernel, int dtype, const DeviceIdent &dev, int itot, int jtot, int ktot,
+                  std::string *variant, int *level, bool *same_size = nullptr,
+                  std::vector<SizeRecord> *records = nullptr);
 int wisdom_append(const std::string &dir, int kernel, const std::string &json_line);
 int wisdom_append_file(const std::string &dir, const std::string &file, const std::string &json_line);
 std::string provenance_json(const DeviceIdent &dev);

@@ -124,9 +124,10 @@ int current_device_ident(DeviceIdent *out)
 }
 
 int wisdom_select(const std::string &dir, int kernel, int dtype, const DeviceIdent &dev, int itot, int jtot,
-                  int ktot, std::string *variant, int *level, bool *same_size)
+                  int ktot, std::string *variant, int *level, bool *same_size, std::vector<SizeRecord> *records)
 {
     if (same_size) *same_size = false;
+    std::vector<std::pair<int, SizeRecord>> seen;  // with the lowest level each counts at
     *level = 5;
     *variant = "default";
     std::ifstream in(wisdom_path(dir, kernel));
@@ -148,6 +149,7 @@ int wisdom_select(const std::string &dir, int kernel, int dtype, const DeviceIde
         const bool same_arch = r.arch == dev.arch;
         // level 1: same GPU, exact size; 2: same GPU; 3: same arch; 4: any
         const int lvl = (same_gpu && d2 == 0) ? 1 : same_gpu ? 2 : same_arch ? 3 : 4;
+        if (records) seen.push_back({lvl, SizeRecord{{r.size[0], r.size[1], r.size[2]}, r.variant}});
         for (int l = lvl; l <= 4; ++l) {
             if (l == 1 && lvl != 1) continue;
             if (d2 <= best[l]) {  // "<=": a later record wins ties
@@ -161,6 +163,8 @@ int wisdom_select(const std::string &dir, int kernel, int dtype, const DeviceIde
             *level = l;
             *variant = choice[l];
             if (same_size) *same_size = best[l] == 0;
+            for (auto &r : seen)
+                if (r.first <= l) records->push_back(r.second);
             return KL_OK;
         }
     }
