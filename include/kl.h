@@ -316,11 +316,13 @@ int kl_launch_variant_dt(const kl_grid_t *g, int32_t kernel, int32_t index,
 /* Index of the configuration kl_advec_u / kl_diff_uvw would run for this
  * grid on the current device (consults the wisdom files on first use per
  * problem size and caches the choice).  Where the heuristic of
- * kl_wisdom_lookup finds only records of other problem sizes, the second-order
- * kernels and the fused step run a configuration that sizes itself to the
- * grid ("rf_t256", "rf_t512") on grids of 2^19 points or more (the fused step on all)
- * whose rows it takes, else the nearest record's; advec_u_2i5 and diff_smag
- * run theirs ("rf_t512") from 2^19 points, the default below. */
+ * kl_wisdom_lookup finds only records of other problem sizes, the choice is by
+ * rules on the sizes: a record that is nearly of this size, else mostly the
+ * configurations that size themselves to the grid ("rf_t256", "rf_t512"), on
+ * longer rows than those take a tile fixed for long rows, on grids of fewer than
+ * 2^19 points the default or the record of the same shape.  It always takes
+ * rows of this length; a call whose layout or pointers it does not fit runs
+ * another. */
 int kl_selected_variant(const kl_grid_t *g, int32_t kernel);
 
 /* ---- tuning and wisdom (Sections "Kernel Tuning", "Wisdom Files",

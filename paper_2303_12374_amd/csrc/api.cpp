@@ -161,65 +161,115 @@ bool takes_row_length(const Variant &v, const kl_grid_t *g)
     return rf_chunks(g->itot, v.vx) <= rf_max_chunks(v.bx);
 }
 
-// The nearest record whose configuration takes rows of g's length, or the default.
-int nearest_usable(const kl_grid_t *g, int kernel, const std::vector<SizeRecord> &records)
+// The tile for rows that the row-flattened ones do not take or lose on: one whose
+// march is short enough to fill the chip and that stays near the fastest over
+// 16 to 19 such sizes of 5e6 points and more (552x97x77 to 2048x256x64; mean
+// against the fastest of each size: FP64 advec_u 1.05, diff_uvw 1.07, fused pass
+// 1.03, fused step 1.02; FP32 1.06, 1.08, 1.09, 1.04).  The step's march is the longer
+// the more points there are.
+const char *wide_rows_tile(int kernel, int dtype, double points)
 {
-    const double want[3] = {(double)g->itot, (double)g->jtot, (double)g->ktot};
-    int index = 0;
-    double best = INFINITY;
-    for (const SizeRecord &r : records) {
-        const int n = variant_index(kernel, g->dtype, r.variant);
-        if (n < 0 || !takes_row_length(variants(kernel, g->dtype)[n], g)) continue;
-        double d2 = 0;
-        for (int a = 0; a < 3; ++a) d2 += (r.size[a] - want[a]) * (r.size[a] - want[a]);
-        if (d2 <= best) {
-            best = d2;
-            index = n;
-        }
+    const bool f32 = dtype == KL_F32;
+    switch (kernel) {
+    case KL_KERNEL_ADVEC_U: return f32 ? "zc_v4_b64x4_k16_x2_nt1_w1" : "zl_v2_b64x8_k32_x0_nt1_w1";
+    case KL_KERNEL_DIFF_UVW: return f32 ? "zl_v4_b64x8_k16_x0_nt1_w1" : "zl_v2_b64x8_k32_x0_nt1_w1";
+    case KL_KERNEL_ADVEC_DIFF: return f32 ? "ad_v4_b64x4_k64_x2_nt1" : "ad_v2_b64x8_k32_x2_nt1";
+    default: break;  // the fused step
     }
-    return index;
+    if (!f32) return points < 6e7 ? "step_v2_b64x4_k32_x2_nt1_w1_h3y" : "step_v2_b64x8_k64_x2_nt1_w1_h3y";
+    return points < 2.4e7 ? "step_v4_b64x4_k16_x2_nt1_w1_h3y"
+                          : points < 6e7 ? "step_v4_b64x4_k32_x2_nt1_w1_h3y" : "step_v4_b64x8_k64_x2_nt1_w1_h3y";
 }
 
-// The configuration of a problem size that no record names, where the nearest
-// record's is fixed for another size: the row-flattened tile with 256 threads
-// sizes itself to the grid.  Over 42 tuned sizes and four kernels, each left
-// out in turn, it is 0.9% from the fastest in the mean and 13% at worst, the
-// nearest record's 7% and 95%.  Below 2^19 points the launches count and the
-// one-thread-per-point default is as fast or faster (64^3 FP32 diff_uvw 6.8
-// against 7.6 us; 80^3 9.9 against 8.8), the fused step excepted, which has
-// none.
-// Longer rows (81 to 256 chunks) take the form with 512 threads where its rows
-// fill the block (13/16 of the threads; rows of 192 chunks, two to a block, are
-// up to 48% slower): diff_uvw and the fused pass always (300x300x150 FP64 184
-// and 183 us, the nearest records' 238 and 222; 400x100x50 FP32 diff_uvw 19
-// against 38), the fused step (two buffers in turn) below 6e6 points
-// (200x150x150 FP64 56 us, the fastest other 63; 400x100x50 FP32 18 against 25;
-// 320x223x100 FP64, above, 100 against 90) or where rows leave a fifth of the
-// wave-per-row tiles' lanes idle (192^3 FP64 95 against 112; 330x330x200 FP64,
-// an eighth idle, 284 against 256).
-// The paper's schemes have one row-flattened tile, fastest or within 2% of it
-// at every size tried from 2^19 points up (200^3 FP32 advec_u_2i5 34 against
-// 61 us for the nearest record's); below, the default (100x37x61 9.4 against
-// 10 us, the nearest record's 55).
-int unrecorded_variant(const kl_grid_t *g, int kernel)
+// The configuration of a problem size that no record names.  A record's tile is
+// fixed for its own size: over 111 sizes of every length, height and aspect
+// (16^3 .. 1024x1020x128, both types), every configuration of the second-order
+// kernels and the step timed, the nearest record is 1.3 to 2.7 times the fastest
+// in the mean of a kernel and up to 47 times; this rule is 1.01 to 1.04 times.  Its lines, in us (rule, other):
+//  - A record whose sizes are within 1.25% in all keeps its word; on fields of
+//    400 MB and more within 10%, where longer marches pay (500x500x500 FP32
+//    diff_uvw, nearest to 512^3, 785, row-flattened 873).
+//  - Rows of up to 80 chunks take the row-flattened tile of 256 threads, rows of up
+//    to 256 the one of 512 (300x300x150 FP32 diff_uvw 79, nearest record 152;
+//    768x300x100 161, 181).
+//  - Grids of fewer than 2^19 points are short launches: a record of about the
+//    same shape (within 0.3 in the logarithms of the sizes), else the default up to
+//    512 KB a field (48^3 FP32 diff_uvw 6.6, row-flattened 7.3), else the row-flattened
+//    tile (32x128x128 FP64 advec_u 7.1, default 10.3; 500x20x30 8, the nearest
+//    record 33).  Rows too long for it: the default (1000x16x16 FP64 advec_u 8, the
+//    nearest record 19).
+//  - The fused step's row-flattened tile writes its images itself and falls behind
+//    on long rows of large grids.  Rows of more than 80 chunks take it where they
+//    fill its block to 400 of 512 threads and either the fields are small (FP32
+//    50 MB, FP64 70: 400x300x100 FP32 80, long-row tile 91; above, 512x64x508 98,
+//    105 row-flattened; 208x200x200 FP64 114, 129; above, 400x300x100 167, 172) or
+//    the rows leave a fifth of the other tiles' lanes without a point (264x187x264
+//    FP64 176, 182), up to 192 chunks; and where no vector divides the rows
+//    (510x300x100 FP32 104, 138).
+//  - FP32 advec_u on rows of more than 128 chunks from 1.5e7 points: four arrays,
+//    where whole rows gain nothing (832x600x64 133, row-flattened 150;
+//    748x216x221 142, 158; 120 chunks, 480x400x100, 82, 65 row-flattened).
+//  - Longer rows: wide_rows_tile (FP64 704x400x80 diff_uvw 313, nearest record 449);
+//    below 5e6 points the nearest fixed tile of the same shape, whose march follows
+//    the height.
+//  - The paper's schemes have one row-flattened tile, fastest or within 2% of it
+//    at every size tried from 2^19 points up; below, the default (100x37x61 9.4,
+//    nearest record 55).  It does not take rows of fewer than 8 points: their 1-wide
+//    tile of 16 levels, from 2^17 points (4x256x256 FP32 advec_u_2i5 22, default 39;
+//    1x512x512 diff_smag 99, 217).
+int unrecorded_variant(const kl_grid_t *g, int kernel, const std::vector<SizeRecord> &records)
 {
-    const bool les = kernel == KL_KERNEL_ADVEC_U_2I5 || kernel == KL_KERNEL_DIFF_SMAG;
-    const bool small = (int64_t)g->itot * g->jtot * g->ktot < ((int64_t)1 << 19);
-    if (small && les) return 0;
-    if (small && kernel != KL_KERNEL_STEP) return -1;
-    const int V = g->dtype == KL_F32 ? 4 : 2, cpr = rf_chunks(g->itot, V);
-    int threads = les ? 512 : 256;
-    if (!les && cpr > rf_max_chunks(256)) {
-        if (kernel == KL_KERNEL_ADVEC_U || cpr > rf_max_chunks(512) || 512 / cpr * cpr < 416) return -1;
-        const bool few = (double)g->itot * g->jtot * g->ktot < 6e6;
-        const bool idle = g->itot < 0.8 * ((cpr + 63) / 64) * 64 * V;
-        if (kernel == KL_KERNEL_STEP && !few && !idle) return -1;
-        threads = 512;
-    }
     const auto &vs = variants(kernel, g->dtype);
-    for (size_t n = 0; n < vs.size(); ++n)
-        if (vs[n].family == FAMILY_RF && vs[n].bx == threads && variant_eligible(vs[n], g, nullptr, 0)) return (int)n;
-    return -1;
+    const bool f32 = g->dtype == KL_F32, step = kernel == KL_KERNEL_STEP;
+    const double points = (double)g->itot * g->jtot * g->ktot, bytes = points * (f32 ? 4 : 8);
+    const double sizes[3] = {(double)g->itot, (double)g->jtot, (double)g->ktot};
+    const int V = f32 ? 4 : 2, cpr = rf_chunks(g->itot, V);
+    const bool few = points < (double)(1 << 19);
+
+    // nearest record by the ratios of the sizes, and nearest with a fixed tile
+    int near = 0, near_fixed = 0;
+    double dist = INFINITY, dist_fixed = INFINITY;
+    for (const SizeRecord &r : records) {
+        const int n = variant_index(kernel, g->dtype, r.variant);
+        if (n < 0 || !takes_row_length(vs[n], g) || !(r.size[0] > 0 && r.size[1] > 0 && r.size[2] > 0)) continue;
+        double d = 0;
+        for (int a = 0; a < 3; ++a) d += log(r.size[a] / sizes[a]) * log(r.size[a] / sizes[a]);
+        d = sqrt(d);
+        if (d <= dist) {
+            dist = d;
+            near = n;
+        }
+        if (vs[n].family != FAMILY_RF && d <= dist_fixed) {
+            dist_fixed = d;
+            near_fixed = n;
+        }
+    }
+    auto named = [&](const char *name, int otherwise) {
+        const int n = variant_index(kernel, g->dtype, name);
+        return n >= 0 && takes_row_length(vs[n], g) ? n : otherwise;
+    };
+    if (kernel == KL_KERNEL_ADVEC_U_2I5 || kernel == KL_KERNEL_DIFF_SMAG) {
+        if (points < (double)(1 << (g->itot < 8 ? 17 : 19))) return 0;
+        if (g->itot >= 8) return named("rf_t512", 0);
+        return named(kernel == KL_KERNEL_DIFF_SMAG ? "s2_v1_b64x8_k16_x0_nt0" : "a5_v1_b64x8_k16_x0_nt0", 0);
+    }
+    const bool big = bytes >= 4e8;
+    if (dist <= (big ? 0.1 : 0.0125)) return near;
+    const bool rows_fit = cpr <= rf_max_chunks(512), short_rows = cpr <= rf_max_chunks(256);
+    const int flat = !rows_fit ? 0 : named(short_rows ? "rf_t256" : "rf_t512", 0);
+    const int wide = points < 5e6 ? near_fixed
+                                  : named(wide_rows_tile(kernel, g->dtype, points), rows_fit ? flat : near_fixed);
+    if (step) {
+        if (short_rows) return flat;
+        const bool idle = cpr <= 192 && g->itot < 0.8 * ((cpr + 63) / 64) * 64 * V;
+        const bool takes = rows_fit && 512 / cpr * cpr >= 400 && (bytes < (f32 ? 50e6 : 70e6) || idle);
+        return takes || (rows_fit && g->itot % V) ? flat : wide;
+    }
+    if (few) return dist <= 0.3 ? near : bytes < (double)(1 << 19) ? 0 : flat;
+    if (!rows_fit) return wide;
+    if (kernel == KL_KERNEL_ADVEC_U && f32 && cpr > 128 && points > 1.5e7 && g->itot % V == 0)
+        return points < 6e7 ? wide : near_fixed;
+    return flat;
 }
 }  // namespace
 
@@ -242,10 +292,8 @@ int select_variant(const kl_grid_t *g, int kernel)
         std::vector<SizeRecord> records;
         if (wisdom_select(wisdom_dir(), kernel, g->dtype, id, g->itot, g->jtot, g->ktot, &name, &level, &same_size,
                           &records) == KL_OK &&
-            level < 5) {
-            index = same_size ? std::max(0, variant_index(kernel, g->dtype, name)) : unrecorded_variant(g, kernel);
-            if (index < 0) index = nearest_usable(g, kernel, records);
-        }
+            level < 5)
+            index = same_size ? std::max(0, variant_index(kernel, g->dtype, name)) : unrecorded_variant(g, kernel, records);
     }
     std::lock_guard<std::mutex> lk(g_plan_mu);
     g_plans[key] = index;

@@ -1,9 +1,14 @@
-"""Which configuration an unrecorded problem size runs: one that takes its rows."""
+"""Which configuration an unrecorded problem size runs: one that takes its rows,
+the record of nearly the same size where there is one, and no record of a
+size far away; and all configurations that the rules can name exist."""
 import json
 import os
+import re
 
 import pytest
 import torch
+
+from paper_2303_12374_amd import inputs
 
 pytestmark = pytest.mark.gpu
 
@@ -59,3 +64,43 @@ def test_unusable_nearest_record_is_passed_over(m, tmp_path):
     """FP64 rows of 768 points are 384 chunks; the nearest record's tile takes 256."""
     write(m, tmp_path, {"step": [(1, (768, 700, 100), "step_v2_b64x4_k32_x2_nt1_w1_h3"), (1, (760, 300, 100), "rf_t512")]})
     assert selected(m, "step", 1, (768, 300, 100))[0] not in ("rf_t512", m.kl_variant_name(m.STEP, 1, 0))
+
+
+@pytest.mark.parametrize("kernel,dtype,name", [("diff_uvw", 0, "zl3_v4_b64x8_k256_x3_nt1"),
+                                               ("advec_diff", 1, "ad_v2_b64x4_k64_x2_nt1"),
+                                               ("step", 0, "step_v4_b64x8_k64_x2_nt1_w1_h3y")])
+def test_record_of_nearly_the_same_size_decides(m, tmp_path, kernel, dtype, name):
+    write(m, tmp_path, {kernel: [(dtype, (256, 256, 256), name), (dtype, (248, 256, 250), "default")]})
+    assert selected(m, kernel, dtype, (256, 254, 256))[0] == name  # 0.8%
+    assert selected(m, kernel, dtype, (256, 192, 256))[0] != name  # a quarter off
+
+
+@pytest.mark.parametrize("kernel", ["advec_u", "diff_uvw"])
+@pytest.mark.parametrize("dtype", [0, 1], ids=["f32", "f64"])
+def test_small_grid_does_not_take_a_far_records_tile(m, tmp_path, kernel, dtype):
+    """500x20x30: a march of 32 levels on one tile column leaves the chip idle."""
+    v = 4 if dtype == 0 else 2
+    far = f"zl_v{v}_b64x8_k32_x2_nt1_w1"
+    write(m, tmp_path, {kernel: [(dtype, (512, 128, 128), far)]})
+    assert selected(m, kernel, dtype, (500, 20, 30))[0] != far
+
+
+def test_every_configuration_the_rules_name_exists(m):
+    """A misspelt name would quietly fall to the nearest record."""
+    src = open(os.path.join(ROOT, "paper_2303_12374_amd", "csrc", "api.cpp")).read()
+    rule = src[src.index("const char *wide_rows_tile"):src.index("int select_variant")]
+    names = set(re.findall(r'"((?:zc|zl|ad|step|a5|s2|rf)_[a-z0-9_]+)"', rule))
+    assert len(names) >= 12
+    known = {m.kl_variant_name(k, d, i) for k in range(6) for d in (0, 1) for i in range(m.kl_num_variants(k, d))}
+    assert names <= known
+
+
+def test_selection_follows_the_rows_not_the_layout(m):
+    """The choice is by size; a layout that it does not fit is handled at the call."""
+    m.kl_set_wisdom_dir(os.path.join(ROOT, "wisdom"))
+    for size in ((300, 40, 40), (64, 64, 64), (516, 130, 130)):
+        for kernel in SECOND:
+            k = kernel_id(m, kernel)
+            a = m.kl_selected_variant(m.Grid(*size, dtype=1), k)
+            m.kl_clear_plan_cache()
+            assert a == m.kl_selected_variant(m.Grid(*size, dtype=1, layout=inputs.plain_layout(*size)), k)
