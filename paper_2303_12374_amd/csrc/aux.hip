@@ -193,27 +193,30 @@ RowPieces row_pieces(const HostArgs &a, int V, int64_t chunks_per_piece)
     return r;
 }
 
-// Pieces for blocks of 256 threads, a chunk each: rows that fit one, or, of longer
-// rows, as few as fill a whole number of blocks to 1 part in 32, else the up to 16
-// that fill them best.  Of long rows, one block with its chunks in a loop leaves
-// CUs idle on small grids, and blocks cut out of single rows end with one
-// nearly empty (Euler update, us; point per thread, block per row, now):
-// 2048x4x64 FP64 10.2, 15.1, 8.0; 1500x200x100 FP64 unpadded 398, 465, 411;
-// 1024x500x64 FP64 450, 417, 402; 560x300x100 FP64 238, 211, 200 (cut rows 240).
-RowPieces block_pieces(const HostArgs &a, int V)
+// The Euler update's blocks, a chunk per thread: the rows that fit 256 threads,
+// or one row of up to 512 chunks, or an equal part of a longer one.  Whole waves,
+// so that those of a row that starts on a cache line store whole lines.  (Longer
+// rows in 256 threads, us; one point per thread, chunks in a loop, now:
+// 2048x4x64 FP64 10.2, 15.1, 7.9; 1500x200x100 FP64 unpadded 398, 465, 411;
+// 1024x500x64 FP64 450, 426, 400; 560x300x100 FP64 238, 209, 201.  Blocks of
+// 256 cut out of one row, or out of several in a run: 560x300x100 240, 207;
+// 526x359x388 FP64, now 898, 926 in a loop, 1000 in a run.)
+struct EulerBlocks {
+    RowPieces rp;
+    uint32_t threads, nseg;  // per block; blocks per piece
+};
+
+EulerBlocks euler_blocks(const HostArgs &a, int V)
 {
-    const int64_t cpr = (a.itot + V - 1) / V;
-    int64_t rows = 256 / cpr;
-    double unused = 1e300;
-    for (int64_t r = 1; cpr > 256 && r <= std::min(16, a.jtot) && (r == 1 || r * cpr <= 1 << 14); ++r) {
-        const double u = (double)((r * cpr + 255) / 256 * 256 - r * cpr) / (double)(r * cpr);
-        if (u < unused) {
-            unused = u;
-            rows = r;
-        }
-        if (u * 32 <= 1) break;
+    EulerBlocks b;
+    b.rp = row_pieces(a, V, 256);
+    b.threads = 256;
+    b.nseg = 1;
+    if (b.rp.cpr > 256) {
+        b.nseg = (b.rp.cpr + 511) / 512;
+        b.threads = ((b.rp.cpr + b.nseg - 1) / b.nseg + 63) / 64 * 64;
     }
-    return row_pieces(a, V, rows * cpr);
+    return b;
 }
 
 // Points per 16-byte chunk, or 1 for rows narrower than that.
@@ -316,12 +319,13 @@ __device__ __forceinline__ void euler_chunk(const Dims &d, T *p, int f, int i0, 
     }
 }
 
-// Block b: the 256 chunks of segment b % nseg of piece b / nseg.
-template <typename T, int V, int NT>
-__global__ __launch_bounds__(256) void euler_kernel(Dims d, RowPieces rp, uint32_t nseg, T dt, int kw0, T *u, T *v,
+// Block b: part b % nseg of piece b / nseg (256 threads: a whole piece).
+template <typename T, int V, int NT, int THREADS>
+__global__ __launch_bounds__(THREADS) void euler_kernel(Dims d, RowPieces rp, uint32_t nseg, T dt, int kw0, T *u, T *v,
                                                    T *w, const T *ut, const T *vt, const T *wt)
 {
-    const uint32_t pc = blockIdx.x / nseg, e = (blockIdx.x % nseg) * 256 + threadIdx.x;
+    const uint32_t pc = THREADS == 256 ? blockIdx.x : blockIdx.x / nseg;
+    const uint32_t e = THREADS == 256 ? threadIdx.x : (blockIdx.x - pc * nseg) * blockDim.x + threadIdx.x;
     const int k = 1 + (int)(pc / rp.ng);
     const uint32_t j0 = (pc % rp.ng) * rp.R;
     const uint32_t left = (uint32_t)d.jtot - j0;
@@ -835,11 +839,16 @@ namespace {
 constexpr double EULER_CACHED_BYTES = 256e6;
 
 template <typename T, int V, int NT>
-void euler_go(const HostArgs &a, const Dims &d, const RowPieces &rp, double dt, void *u, void *v, void *w, hipStream_t s)
+void euler_go(const HostArgs &a, const Dims &d, const EulerBlocks &b, double dt, void *u, void *v, void *w, hipStream_t s)
 {
-    const uint32_t nseg = (rp.R * rp.cpr + 255) / 256;  // above 1 where rows have more than 256 chunks
-    hipLaunchKernelGGL((euler_kernel<T, V, NT>), dim3(rp.np * nseg), dim3(256), 0, s, d, rp, nseg, (T)dt, a.kw0,
-                       (T *)u, (T *)v, (T *)w, (const T *)a.ut, (const T *)a.vt, (const T *)a.wt);
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(b.rp.np * b.nseg), dim3(b.threads), 0, s, d, b.rp, b.nseg, (T)dt, a.kw0, (T *)u,
+                           (T *)v, (T *)w, (const T *)a.ut, (const T *)a.vt, (const T *)a.wt);
+    };
+    if (b.threads > 256)  // only rows of more than 256 chunks
+        go(euler_kernel<T, V, NT, 512>);
+    else
+        go(euler_kernel<T, V, NT, 256>);
 }
 }  // namespace
 
@@ -851,14 +860,14 @@ hipError_t launch_euler(const HostArgs &a, double dt, void *u, void *v, void *w,
     if (narrow) d.gc = 1;
     if ((int64_t)a.jtot * a.ktot >= ((int64_t)1 << 31)) return hipErrorInvalidValue;  // 32-bit piece index
     const int V = row_chunk(a);
-    const RowPieces rp = block_pieces(a, V);
+    const EulerBlocks b = euler_blocks(a, V);
     const bool nt = 3.0 * a.itot * a.jtot * a.ktot * (a.dtype == KL_F32 ? 4 : 8) > EULER_CACHED_BYTES;
     if (a.dtype == KL_F32)
-        V == 4 ? (nt ? euler_go<float, 4, 1>(a, d, rp, dt, u, v, w, s) : euler_go<float, 4, 0>(a, d, rp, dt, u, v, w, s))
-               : euler_go<float, 1, 0>(a, d, rp, dt, u, v, w, s);
+        V == 4 ? (nt ? euler_go<float, 4, 1>(a, d, b, dt, u, v, w, s) : euler_go<float, 4, 0>(a, d, b, dt, u, v, w, s))
+               : euler_go<float, 1, 0>(a, d, b, dt, u, v, w, s);
     else
-        V == 2 ? (nt ? euler_go<double, 2, 1>(a, d, rp, dt, u, v, w, s) : euler_go<double, 2, 0>(a, d, rp, dt, u, v, w, s))
-               : euler_go<double, 1, 0>(a, d, rp, dt, u, v, w, s);
+        V == 2 ? (nt ? euler_go<double, 2, 1>(a, d, b, dt, u, v, w, s) : euler_go<double, 2, 0>(a, d, b, dt, u, v, w, s))
+               : euler_go<double, 1, 0>(a, d, b, dt, u, v, w, s);
     const hipError_t e = hipGetLastError();
     return e == hipSuccess && narrow ? launch_fill_ghosts(a, u, v, w, s) : e;
 }

@@ -1,5 +1,5 @@
-"""kl_euler on rows of more than 256 chunks of 16 bytes: blocks take 256 chunks of
-several such rows in a run."""
+"""kl_euler on rows around 256 chunks of 16 bytes (several rows a block below, one
+above) and 512 (several blocks a row above)."""
 import numpy as np
 import pytest
 import torch
@@ -12,8 +12,8 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("layout", ["padded", "plain"])
 @pytest.mark.parametrize("gc", [1, 3])
 @pytest.mark.parametrize("bc", [0, 1, 2], ids=["zerograd", "nopen", "zperiodic"])
-@pytest.mark.parametrize("dtype,itot", [(0, 1023), (0, 1024), (0, 1025), (0, 2047), (0, 2052), (1, 511), (1, 512), (1, 513),
-                                        (1, 560), (1, 1026), (1, 2049)])
+@pytest.mark.parametrize("dtype,itot", [(0, 1023), (0, 1024), (0, 1025), (0, 2047), (0, 2048), (0, 2052), (0, 4099),
+                                        (1, 511), (1, 512), (1, 513), (1, 560), (1, 1024), (1, 1026), (1, 2049)])
 def test_long_rows_advance_like_short_ones(dtype, itot, bc, gc, layout):
     """Bitwise the update of the same values with x and y exchanged (short rows): the
     update is pointwise, and every ghost layer is the ghost fill's."""
