@@ -161,17 +161,27 @@ bool takes_row_length(const Variant &v, const kl_grid_t *g)
     return rf_chunks(g->itot, v.vx) <= rf_max_chunks(v.bx);
 }
 
+// Whether whole chunks of V points make up rows that fill segments of 64 chunks.
+bool fills_waves(int itot, int V)
+{
+    const int cpr = rf_chunks(itot, V);
+    return itot % V == 0 && itot >= 0.94 * ((cpr + 63) / 64) * 64 * V;
+}
+
 // The tile for rows that the row-flattened ones do not take or lose on: one whose
 // march is short enough to fill the chip and that stays near the fastest over
 // 16 to 19 such sizes of 5e6 points and more (552x97x77 to 2048x256x64; mean
 // against the fastest of each size: FP64 advec_u 1.05, diff_uvw 1.07, fused pass
 // 1.03, fused step 1.02; FP32 1.06, 1.08, 1.09, 1.04).  The step's march is the longer
 // the more points there are.
-const char *wide_rows_tile(int kernel, int dtype, double points)
+const char *wide_rows_tile(int kernel, int dtype, int itot, double points)
 {
     const bool f32 = dtype == KL_F32;
     switch (kernel) {
-    case KL_KERNEL_ADVEC_U: return f32 ? "zc_v4_b64x4_k16_x2_nt1_w1" : "zl_v2_b64x8_k32_x0_nt1_w1";
+    case KL_KERNEL_ADVEC_U:
+        if (!f32) return "zl_v2_b64x8_k32_x0_nt1_w1";
+        if (itot <= 512 && fills_waves(itot, 4)) return "zl_v4_b64x4_k64_x3_nt1_w1";
+        return itot <= 1024 ? "zc_v2_b64x4_k16_x2_nt1_w1" : "zc_v4_b64x4_k16_x2_nt1_w1";
     case KL_KERNEL_DIFF_UVW: return f32 ? "zl_v4_b64x8_k16_x0_nt1_w1" : "zl_v2_b64x8_k32_x0_nt1_w1";
     case KL_KERNEL_ADVEC_DIFF: return f32 ? "ad_v4_b64x4_k64_x2_nt1" : "ad_v2_b64x8_k32_x2_nt1";
     default: break;  // the fused step
@@ -203,12 +213,18 @@ const char *wide_rows_tile(int kernel, int dtype, double points)
 //    fill its block to 400 of 512 threads and either the fields are small (FP32
 //    50 MB, FP64 70: 400x300x100 FP32 80, long-row tile 91; above, 512x64x508 98,
 //    105 row-flattened; 208x200x200 FP64 114, 129; above, 400x300x100 167, 172) or
-//    the rows leave a fifth of the other tiles' lanes without a point (264x187x264
-//    FP64 176, 182), up to 192 chunks; and where no vector divides the rows
-//    (510x300x100 FP32 104, 138).
-//  - FP32 advec_u on rows of more than 128 chunks from 1.5e7 points: four arrays,
-//    where whole rows gain nothing (832x600x64 133, row-flattened 150;
-//    748x216x221 142, 158; 120 chunks, 480x400x100, 82, 65 row-flattened).
+//    the rows leave a fifth of the other tiles' lanes without a point, with five
+//    rows a block (102 chunks; 384x344x404 FP32 341, 371) or up to 192 chunks and
+//    120 MB (264x187x264 FP64 176, 182; above, 608x386x313 FP32 433, 552); and
+//    where no vector divides the rows (510x300x100 FP32 104, 138).
+//  - advec_u: four arrays, where whole rows gain nothing on large grids.  The
+//    long-row tile on FP32 rows of more than 128 chunks from 2e7 points (832x600x64
+//    133, row-flattened 150; 524x402x283 256, 294; below, 560x300x100 72, 60), from
+//    6e7 the nearest fixed one (1000x1000x64 225, 256); on FP32 rows of 81 to 128
+//    chunks that fill segments of 64, from 1.5e7 (with diff_uvw after it
+//    512x512x120 290, 309), else from 5e7 (384x344x404 213, 225; below, 448x448x200
+//    175, 164); on FP64 rows of more than 80 from 4e7 (512x261x304 300, 333;
+//    420x705x137 348, 332).
 //  - Longer rows: wide_rows_tile (FP64 704x400x80 diff_uvw 313, nearest record 449);
 //    below 5e6 points the nearest fixed tile of the same shape, whose march follows
 //    the height.
@@ -253,22 +269,23 @@ int unrecorded_variant(const kl_grid_t *g, int kernel, const std::vector<SizeRec
         if (g->itot >= 8) return named("rf_t512", 0);
         return named(kernel == KL_KERNEL_DIFF_SMAG ? "s2_v1_b64x8_k16_x0_nt0" : "a5_v1_b64x8_k16_x0_nt0", 0);
     }
-    const bool big = bytes >= 4e8;
-    if (dist <= (big ? 0.1 : 0.0125)) return near;
+    if (dist <= (bytes >= 4e8 ? 0.1 : 0.0125)) return near;
     const bool rows_fit = cpr <= rf_max_chunks(512), short_rows = cpr <= rf_max_chunks(256);
     const int flat = !rows_fit ? 0 : named(short_rows ? "rf_t256" : "rf_t512", 0);
     const int wide = points < 5e6 ? near_fixed
-                                  : named(wide_rows_tile(kernel, g->dtype, points), rows_fit ? flat : near_fixed);
+                                  : named(wide_rows_tile(kernel, g->dtype, g->itot, points), rows_fit ? flat : near_fixed);
     if (step) {
         if (short_rows) return flat;
-        const bool idle = cpr <= 192 && g->itot < 0.8 * ((cpr + 63) / 64) * 64 * V;
+        const bool idle = g->itot < 0.8 * ((cpr + 63) / 64) * 64 * V && (cpr <= 102 || (cpr <= 192 && bytes < 120e6));
         const bool takes = rows_fit && 512 / cpr * cpr >= 400 && (bytes < (f32 ? 50e6 : 70e6) || idle);
         return takes || (rows_fit && g->itot % V) ? flat : wide;
     }
     if (few) return dist <= 0.3 ? near : bytes < (double)(1 << 19) ? 0 : flat;
     if (!rows_fit) return wide;
-    if (kernel == KL_KERNEL_ADVEC_U && f32 && cpr > 128 && points > 1.5e7 && g->itot % V == 0)
-        return points < 6e7 ? wide : near_fixed;
+    if (kernel == KL_KERNEL_ADVEC_U && !short_rows && g->itot % 2 == 0) {
+        const double from = !f32 ? 4e7 : cpr > 128 ? 2e7 : fills_waves(g->itot, V) ? 1.5e7 : 5e7;
+        if (points > from) return f32 && cpr > 128 && points >= 6e7 ? near_fixed : wide;
+    }
     return flat;
 }
 }  // namespace
