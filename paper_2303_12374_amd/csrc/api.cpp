@@ -168,24 +168,40 @@ bool fills_waves(int itot, int V)
     return itot % V == 0 && itot >= 0.94 * ((cpr + 63) / 64) * 64 * V;
 }
 
-// The tile for rows that the row-flattened ones do not take or lose on: one whose
-// march is short enough to fill the chip and that stays near the fastest over
-// 16 to 19 such sizes of 5e6 points and more (552x97x77 to 2048x256x64; mean
-// against the fastest of each size: FP64 advec_u 1.05, diff_uvw 1.07, fused pass
-// 1.03, fused step 1.02; FP32 1.06, 1.08, 1.09, 1.04).  The step's march is the longer
-// the more points there are.
+// The tile for rows that the row-flattened ones do not take or lose on.  Small
+// grids need short marches to fill the chip, and no far record gives one: against
+// the fastest of each of 19 sizes of rows of more than 256 chunks and up to 5e6
+// points (548x9x123 to 1892x84x21) the mean is FP64 advec_u 1.07, diff_uvw 1.17,
+// fused pass 1.06, fused step 1.03; FP32 1.03, 1.10, 1.07, 1.03 (nearest record
+// 1.07, 2.7, 1.20, 1.03; 1.03, 1.8, 1.08, 1.13; 614x10x112 FP64 diff_uvw 18 us, 126).
+// From there on, 16 to 19 sizes (552x97x77 to 2048x256x64): FP64 1.05, 1.07, 1.03,
+// 1.02; FP32 1.06, 1.08, 1.09, 1.04.  FP32 rows are longer and keep the short
+// marches for more points (1940x18x211 FP32 advec_u, diff_uvw, fused pass, fused
+// step 1.07, 1.03, 1.14, 1.08 against 1.57, 1.50, 1.60, 1.48).  The step's march is
+// the longer the more points there are.
 const char *wide_rows_tile(int kernel, int dtype, int itot, double points)
 {
-    const bool f32 = dtype == KL_F32;
+    const bool f32 = dtype == KL_F32, small = points < 5e6, longer = f32 && itot > 1024 && points < 1.15e7;
     switch (kernel) {
     case KL_KERNEL_ADVEC_U:
+        if (points < (!f32 ? 7.5e6 : itot > 1024 ? 2e7 : 1.15e7))
+            return f32 && itot % 2 == 0 ? "zc_v2_b64x1_k16_x1" : "zc_v1_b64x1_k16_x1";
         if (!f32) return "zl_v2_b64x8_k32_x0_nt1_w1";
         if (itot <= 512 && fills_waves(itot, 4)) return "zl_v4_b64x4_k64_x3_nt1_w1";
         return itot <= 1024 ? "zc_v2_b64x4_k16_x2_nt1_w1" : "zc_v4_b64x4_k16_x2_nt1_w1";
-    case KL_KERNEL_DIFF_UVW: return f32 ? "zl_v4_b64x8_k16_x0_nt1_w1" : "zl_v2_b64x8_k32_x0_nt1_w1";
-    case KL_KERNEL_ADVEC_DIFF: return f32 ? "ad_v4_b64x4_k64_x2_nt1" : "ad_v2_b64x8_k32_x2_nt1";
+    case KL_KERNEL_DIFF_UVW:
+        if (small) return f32 ? "default" : "zl_v2_b64x8_k8_x0_nt0_w1";
+        if (longer) return "zc_v4_b64x1_k16_x1";
+        return f32 ? "zl_v4_b64x8_k16_x0_nt1_w1" : "zl_v2_b64x8_k32_x0_nt1_w1";
+    case KL_KERNEL_ADVEC_DIFF:
+        if (small) return f32 ? "default" : "ad_v2_b64x4_k8_x0_nt0";
+        if (f32 && points < 2e7) return "ad_v4_b64x4_k8_x0_nt0";
+        return f32 ? "ad_v4_b64x4_k64_x2_nt1" : "ad_v2_b64x8_k32_x2_nt1";
     default: break;  // the fused step
     }
+    if (itot % (f32 ? 4 : 2)) return "step_v1_b64x4_k8_x0_nt0";
+    if (small) return "step_v2_b64x4_k8_x0_nt0";
+    if (longer) return "step_v4_b64x4_k8_x0_nt0";
     if (!f32) return points < 6e7 ? "step_v2_b64x4_k32_x2_nt1_w1_h3y" : "step_v2_b64x8_k64_x2_nt1_w1_h3y";
     return points < 2.4e7 ? "step_v4_b64x4_k16_x2_nt1_w1_h3y"
                           : points < 6e7 ? "step_v4_b64x4_k32_x2_nt1_w1_h3y" : "step_v4_b64x8_k64_x2_nt1_w1_h3y";
@@ -209,7 +225,8 @@ const char *wide_rows_tile(int kernel, int dtype, int itot, double points)
 //    record 33).  Rows too long for it: the default (1000x16x16 FP64 advec_u 8, the
 //    nearest record 19).
 //  - The fused step's row-flattened tile writes its images itself and falls behind
-//    on long rows of large grids.  Rows of more than 80 chunks take it where they
+//    on long rows of large grids.  Rows of more than 80 chunks take it below 5e6
+//    points (264x100x60 FP64 24, nearest fixed tile 39), and where they
 //    fill its block to 400 of 512 threads and either the fields are small (FP32
 //    50 MB, FP64 70: 400x300x100 FP32 80, long-row tile 91; above, 512x64x508 98,
 //    105 row-flattened; 208x200x200 FP64 114, 129; above, 400x300x100 167, 172) or
@@ -217,7 +234,11 @@ const char *wide_rows_tile(int kernel, int dtype, int itot, double points)
 //    rows a block (102 chunks; 384x344x404 FP32 341, 371) or up to 192 chunks and
 //    120 MB (264x187x264 FP64 176, 182; above, 608x386x313 FP32 433, 552); and
 //    where no vector divides the rows (510x300x100 FP32 104, 138).
-//  - advec_u: four arrays, where whole rows gain nothing on large grids.  The
+//  - advec_u on rows of more than 80 chunks: four arrays, where whole rows gain
+//    nothing on large grids and blocks of 512 threads are few on small ones.  From
+//    1e6 points a tile of one row (FP32 up to 1.15e7 points 520x100x60 12,
+//    row-flattened 17, above 400x300x100 44, 39; FP64 up to 7.5e6 264x100x60 13, 16,
+//    above 336x200x120 69, 55; below 1e6 510x70x17 FP64 12, 10).  The
 //    long-row tile on FP32 rows of more than 128 chunks from 2e7 points (832x600x64
 //    133, row-flattened 150; 524x402x283 256, 294; below, 560x300x100 72, 60), from
 //    6e7 the nearest fixed one (1000x1000x64 225, 256); on FP32 rows of 81 to 128
@@ -226,8 +247,7 @@ const char *wide_rows_tile(int kernel, int dtype, int itot, double points)
 //    175, 164); on FP64 rows of more than 80 from 4e7 (512x261x304 300, 333;
 //    420x705x137 348, 332).
 //  - Longer rows: wide_rows_tile (FP64 704x400x80 diff_uvw 313, nearest record 449);
-//    below 5e6 points the nearest fixed tile of the same shape, whose march follows
-//    the height.
+//    where its vector does not divide them the default.
 //  - The paper's schemes have one row-flattened tile, fastest or within 2% of it
 //    at every size tried from 2^19 points up; below, the default (100x37x61 9.4,
 //    nearest record 55).  It does not take rows of fewer than 8 points: their 1-wide
@@ -272,19 +292,18 @@ int unrecorded_variant(const kl_grid_t *g, int kernel, const std::vector<SizeRec
     if (dist <= (bytes >= 4e8 ? 0.1 : 0.0125)) return near;
     const bool rows_fit = cpr <= rf_max_chunks(512), short_rows = cpr <= rf_max_chunks(256);
     const int flat = !rows_fit ? 0 : named(short_rows ? "rf_t256" : "rf_t512", 0);
-    const int wide = points < 5e6 ? near_fixed
-                                  : named(wide_rows_tile(kernel, g->dtype, g->itot, points), rows_fit ? flat : near_fixed);
+    const int wide = named(wide_rows_tile(kernel, g->dtype, g->itot, points), flat);
     if (step) {
-        if (short_rows) return flat;
+        if (short_rows || (rows_fit && (points < 5e6 || g->itot % V))) return flat;
         const bool idle = g->itot < 0.8 * ((cpr + 63) / 64) * 64 * V && (cpr <= 102 || (cpr <= 192 && bytes < 120e6));
-        const bool takes = rows_fit && 512 / cpr * cpr >= 400 && (bytes < (f32 ? 50e6 : 70e6) || idle);
-        return takes || (rows_fit && g->itot % V) ? flat : wide;
+        return rows_fit && 512 / cpr * cpr >= 400 && (bytes < (f32 ? 50e6 : 70e6) || idle) ? flat : wide;
     }
     if (few) return dist <= 0.3 ? near : bytes < (double)(1 << 19) ? 0 : flat;
     if (!rows_fit) return wide;
-    if (kernel == KL_KERNEL_ADVEC_U && !short_rows && g->itot % 2 == 0) {
+    if (kernel == KL_KERNEL_ADVEC_U && !short_rows) {
         const double from = !f32 ? 4e7 : cpr > 128 ? 2e7 : fills_waves(g->itot, V) ? 1.5e7 : 5e7;
-        if (points > from) return f32 && cpr > 128 && points >= 6e7 ? near_fixed : wide;
+        if (points >= 1e6 && points < (f32 ? 1.15e7 : 7.5e6)) return wide;
+        if (points > from && g->itot % 2 == 0) return f32 && cpr > 128 && points >= 6e7 ? near_fixed : wide;
     }
     return flat;
 }

@@ -85,6 +85,22 @@ def test_small_grid_does_not_take_a_far_records_tile(m, tmp_path, kernel, dtype)
     assert selected(m, kernel, dtype, (500, 20, 30))[0] != far
 
 
+@pytest.mark.parametrize("kernel,dtype,size,name", [
+    ("step", 1, (264, 100, 60), "rf_t512"), ("step", 0, (532, 64, 64), "rf_t512"), ("step", 0, (510, 300, 100), "rf_t512"),
+    ("step", 1, (614, 10, 112), "step_v2_b64x4_k8_x0_nt0"), ("step", 0, (1302, 60, 60), "step_v1_b64x4_k8_x0_nt0"),
+    ("diff_uvw", 1, (614, 10, 112), "zl_v2_b64x8_k8_x0_nt0_w1"), ("diff_uvw", 0, (1136, 12, 137), "default"),
+    ("advec_diff", 0, (1239, 91, 91), "default"), ("advec_diff", 0, (1136, 23, 267), "ad_v4_b64x4_k8_x0_nt0"),
+    ("advec_u", 0, (520, 100, 60), "zc_v2_b64x1_k16_x1"), ("advec_u", 0, (501, 100, 50), "zc_v1_b64x1_k16_x1"),
+    ("advec_u", 1, (178, 166, 18), "rf_t512"), ("advec_u", 1, (336, 200, 120), "rf_t512")])
+def test_small_grids_of_long_rows(m, tmp_path, kernel, dtype, size, name):
+    """Short marches where few points have to fill the chip, whatever the records far away say."""
+    v = 4 if dtype == 0 else 2
+    far = {"step": f"step_v{v}_b64x8_k64_x2_nt1_w1_h3y", "advec_diff": f"ad_v{v}_b64x4_k64_x2_nt1"}
+    write(m, tmp_path, {kernel: [(dtype, (512, 512, 512), far.get(kernel, f"zl_v{v}_b64x8_k32_x2_nt1_w1"))]})
+    got, ok = selected(m, kernel, dtype, size)
+    assert ok and got == name
+
+
 def test_every_configuration_the_rules_name_exists(m):
     """A misspelt name would quietly fall to the nearest record."""
     src = open(os.path.join(ROOT, "paper_2303_12374_amd", "csrc", "api.cpp")).read()
