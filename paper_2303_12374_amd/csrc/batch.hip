@@ -3,11 +3,12 @@
 //
 // Every grid runs advec_u followed by diff_uvw as one fused pass (the tile of
 // kl_advec_diff: 9 values per point moved instead of 14, bitwise the result
-// of the two separate kernels).  Each grid gets its configuration from the
-// wisdom files like a single-grid launch (nearest problem size on this GPU,
-// Section "Kernel Selection and Compilation"); grids whose selected
-// configuration has no persistent form use an LDS z-march configuration
-// sized to the grid.  The configuration selected for the most grid points
+// of the two separate kernels).  Each grid gets its configuration as a
+// single-grid launch does (wisdom files, Section "Kernel Selection and
+// Compilation"); grids whose selected configuration has no persistent form, or
+// segments wider than their rows, use the row-flattened tile, or, with rows
+// longer than that takes, an LDS z-march of the widest vector that divides
+// them.  The configuration selected for the most grid points
 // then takes every grid it can serve, the next one the rest it can serve, and
 // so on (all configurations give the same bits).  Grids are grouped by
 // (dtype, configuration); every group becomes one persistent kernel whose
@@ -124,20 +125,57 @@ bool batch_fits(const Variant &v, const kl_grid_t *g, const void *const *ptrs, i
     return v.family == FAMILY_RF || 64 * v.vx <= std::max(64, g->itot);
 }
 
-// Eight levels: short tiles end level, and what they read twice (three levels
-// each) is still cached; 56 grids FP32 689 us, with 16 levels 706, with 32 709;
-// 28 grids 298, 304, 320; 22 grids FP64 434, 438, 445.  Four where eight leave
-// CUs without a tile (three grids: 34 us, with two levels 40).
-int rf_batch_levels(const Variant &v, int vi, const std::vector<kl_grid_t> &grids, const std::vector<int> &sel, int ncu)
+// Stores that stay in the caches pay where the next launch finds them there (one
+// served 128^3 FP64 request, 101 MB, 55 us a tick streamed, 47 cached; eight
+// 32x32x512 FP32 grids accumulating 76 and 49); beyond 256 MB they displace what is
+// still to be read (six grids up to 512x512x128 FP64 697, 715).  Cleared tendencies
+// are streamed in any case: they are not read (eight 32x32x512 FP64 grids 61, 69).
+bool batch_cached(const std::vector<kl_grid_t> &grids)
+{
+    double bytes = 0;
+    for (const kl_grid_t &g : grids) bytes += 6.0 * g.itot * g.jtot * g.ktot * (g.dtype == KL_F32 ? 4 : 8);
+    return bytes <= 256e6;
+}
+
+// Levels per row-flattened tile.  Where the tiles are about as many as run at a
+// time, one each: 16 or 32 levels if that makes them fit (served steps, us a
+// tick: two 128^3 FP64 79 with 8 levels, 59 with 16; 256^3 FP32 138 and, with 32,
+// 114; four 128^3 FP32 77 and 61; one, which fits with 8, 33 and 45 with 16).
+// More tiles than that: eight levels, short tiles end level, and what they read
+// twice (three levels each) is still cached; 56 grids FP32 689 us, with 16 levels
+// 706, with 32 709; 22 grids FP64 434, 438, 445.  Four where eight leave CUs
+// without a tile (three grids: 34 us, with two levels 40).
+int rf_batch_levels(const Variant &v, int vi, const std::vector<kl_grid_t> &grids, const std::vector<int> &sel, int ncu,
+                    int slots)
 {
     if (v.family != FAMILY_RF) return 0;
-    int64_t tiles = 0;
-    for (size_t n = 0; n < grids.size(); ++n)
-        if (grids[n].dtype == v.dtype && sel[n] == vi) {
-            const TileShape t = batch_tiles(v, &grids[n], 8);
-            tiles += (int64_t)t.nby * t.nbz;
-        }
-    return tiles < ncu ? 4 : 8;
+    auto tiles = [&](int kb) {
+        int64_t sum = 0;
+        for (size_t n = 0; n < grids.size(); ++n)
+            if (grids[n].dtype == v.dtype && sel[n] == vi) {
+                const TileShape t = batch_tiles(v, &grids[n], kb);
+                sum += (int64_t)t.nby * t.nbz;
+            }
+        return sum;
+    };
+    if (tiles(8) < ncu) return 4;
+    for (int kb = 8; kb <= 32; kb *= 2)
+        if (tiles(kb) <= slots) return kb;
+    return 8;
+}
+
+// Block b starts with tile b and runs on XCD b % 8: of tiles that all start at
+// once each XCD is given a run of the list, whose neighbours share their halo
+// rows in its L2 (one served 128^3 FP64 request 47 -> 43 us a tick).  Longer lists
+// keep their order: blocks draw as they finish, and the runs end unevenly (eight
+// served grids of 64^3 to 512x512x128 FP32 693 us, spread 728).
+void spread_tiles(const Variant &v, int slots, std::vector<int4> &tiles)
+{
+    const size_t n = tiles.size();
+    if (v.family != FAMILY_RF || n > (size_t)slots) return;
+    std::vector<int4> out(n);
+    for (size_t i = 0; i < n; ++i) out[i] = tiles[i % 8 * (n / 8) + std::min(i % 8, n % 8) + i / 8];
+    tiles.swap(out);
 }
 
 TileShape batch_tiles(const Variant &v, const kl_grid_t *g, int rf_kb)
@@ -337,6 +375,7 @@ int build(Batch &b, void *const *fields)
     if (e == hipSuccess) e = hipGetDeviceProperties(&prop, dev);
     if (e != hipSuccess) return hip_fail(e, "device properties");
     const int ncu = prop.multiProcessorCount;
+    auto slots = [&](const Variant &v) { return ncu * (b.zero ? v.occupancy_fresh() : v.occupancy()); };
 
     // groups
     std::map<std::tuple<int, int, int>, size_t> gidx;
@@ -361,7 +400,8 @@ int build(Batch &b, void *const *fields)
         for (size_t n = 0; n < b.grids.size(); ++n) {
             const int dtype = b.grids[n].dtype;
             if (!levels.count({dtype, sel[n]}))
-                levels[{dtype, sel[n]}] = rf_batch_levels(variants(kernel, dtype)[sel[n]], sel[n], b.grids, sel, ncu);
+                levels[{dtype, sel[n]}] = rf_batch_levels(variants(kernel, dtype)[sel[n]], sel[n], b.grids, sel, ncu,
+                                                          slots(variants(kernel, dtype)[sel[n]]));
         }
         // the row-flattened pass writes one ghost column on each side itself
         // where rows are whole chunks
@@ -410,12 +450,13 @@ int build(Batch &b, void *const *fields)
         std::vector<int4> sorted(ord.size());
         for (size_t n = 0; n < ord.size(); ++n) sorted[n] = gr.tiles[ord[n]];
         gr.tiles.swap(sorted);
+        const Variant &v = variants(gr.kernel, gr.dtype)[gr.variant];
+        spread_tiles(v, slots(v), gr.tiles);
         if ((e = upload(&gr.d_tiles, gr.tiles.data(), gr.tiles.size() * sizeof(int4))) != hipSuccess)
             return hip_fail(e, "tiles");
         if ((e = hipMalloc((void **)&gr.d_queue, 2 * sizeof(int))) != hipSuccess) return hip_fail(e, "queue");
         if ((e = hipMemset(gr.d_queue, 0, 2 * sizeof(int))) != hipSuccess) return hip_fail(e, "queue");
-        const Variant &v = variants(gr.kernel, gr.dtype)[gr.variant];
-        gr.nblocks = persistent_blocks((int64_t)gr.tiles.size(), ncu, b.zero ? v.occupancy_fresh() : v.occupancy());
+        gr.nblocks = persistent_blocks((int64_t)gr.tiles.size(), slots(v));
         b.ntiles += (int64_t)gr.tiles.size();
     }
     // ghost fill and conservation-sum jobs, one per grid
@@ -477,11 +518,11 @@ int build(Batch &b, void *const *fields)
         if (e != hipSuccess) rc = hip_fail(e, "fill launch");
         ++b.nkernels;
     }
+    const bool cached = batch_cached(b.grids);
     for (Group &gr : b.groups) {
         if (rc != KL_OK) break;
         const Variant &v = variants(gr.kernel, gr.dtype)[gr.variant];
-        e = (b.zero ? v.batch_fresh : v.batch)(b.d_desc[gr.dtype], gr.d_tiles, (int)gr.tiles.size(), gr.nblocks,
-                                               gr.d_queue, cs);
+        e = v.persistent(b.zero, cached)(b.d_desc[gr.dtype], gr.d_tiles, (int)gr.tiles.size(), gr.nblocks, gr.d_queue, cs);
         if (e != hipSuccess) rc = hip_fail(e, v.name);
         ++b.nkernels;
     }

@@ -43,11 +43,11 @@ typedef hipError_t (*LaunchFn)(const HostArgs &, hipStream_t);
 typedef hipError_t (*BatchFn)(const void *, const void *, int, int, int *, hipStream_t);
 typedef int (*OccFn)();  // resident blocks per CU of the batched kernel
 
-// Blocks of a persistent tile walk: every resident slot (ncu * occ), at most
-// one per tile.
-inline int persistent_blocks(int64_t ntiles, int ncu, int occ)
+// Blocks of a persistent tile walk: every resident slot (CUs times blocks per
+// CU), at most one per tile.
+inline int persistent_blocks(int64_t ntiles, int slots)
 {
-    const int64_t nb = ntiles < (int64_t)ncu * occ ? ntiles : (int64_t)ncu * occ;
+    const int64_t nb = ntiles < slots ? ntiles : slots;
     return (int)(nb > 0 ? nb : 1);
 }
 
@@ -59,13 +59,20 @@ struct Variant {
     int kernel, dtype, family;
     int vx, bx, by, kb, xcd;  // x vector width, block shape, z-march length, XCD order
     LaunchFn launch;
-    BatchFn batch;  // persistent tile-list form (LDS z-march family only), else null
+    BatchFn batch;  // persistent tile-list form (LDS z-march and row-flattened tiles), else null
     OccFn occupancy;
     // advec_diff only: the same configuration onto tendencies that start at
     // zero and are not read (FUSE_FRESH), and its persistent form
     LaunchFn fresh = nullptr;
     BatchFn batch_fresh = nullptr;
     OccFn occupancy_fresh = nullptr;
+    // the persistent form with stores that stay in the caches, where it differs
+    // (row-flattened tiles): for launches whose arrays fit there
+    BatchFn batch_cached = nullptr;
+    BatchFn persistent(bool cleared, bool cached) const
+    {
+        return cleared ? batch_fresh : cached && batch_cached ? batch_cached : batch;
+    }
 };
 
 // Registry (index 0 of every list is the default configuration).
@@ -132,9 +139,14 @@ struct TileShape {
 };
 // (row-flattened tiles: rf_kb levels per tile, from rf_batch_levels).
 TileShape batch_tiles(const Variant &v, const kl_grid_t *g, int rf_kb);
+// Whether the six arrays of all grids fit the memory-side cache together.
+bool batch_cached(const std::vector<kl_grid_t> &grids);
 // Levels per row-flattened tile in a persistent kernel that advances the grids
-// n with sel[n] == vi together.
-int rf_batch_levels(const Variant &v, int vi, const std::vector<kl_grid_t> &grids, const std::vector<int> &sel, int ncu);
+// n with sel[n] == vi together on ncu CUs, `slots` blocks at a time.
+int rf_batch_levels(const Variant &v, int vi, const std::vector<kl_grid_t> &grids, const std::vector<int> &sel, int ncu,
+                    int slots);
+// Order of such a kernel's tiles, largest first on entry.
+void spread_tiles(const Variant &v, int slots, std::vector<int4> &tiles);
 // Configuration of grid g for `kernel` in batched (persistent) form, or -1.
 int batch_variant(const kl_grid_t *g, int kernel, void *const f[6]);
 // Regroup grids (6 field pointers each) for fewer persistent kernels: see batch.hip.

@@ -132,6 +132,14 @@ struct GpuExec {
     int cur_slot = 0;
     std::unordered_map<const Req *, const double *> pending;
     std::map<const Variant *, int> occ;  // resident blocks per CU of batched kernels
+
+    int slots(const Variant &v)
+    {
+        auto oc = occ.find(&v);
+        if (oc == occ.end()) oc = occ.emplace(&v, v.occupancy()).first;
+        return ncu * oc->second;
+    }
+
     // work queue of the persistent step kernels (two device ints): the kernels
     // run one after another on the server stream, and each returns it to zero
     int *d_queue = nullptr;
@@ -264,8 +272,8 @@ struct GpuExec {
         for (size_t n = 0; n < act.size(); ++n) {
             const int dtype = grids[n].dtype;
             if (!levels.count({dtype, sel[n]}))
-                levels[{dtype, sel[n]}] =
-                    rf_batch_levels(variants(KL_KERNEL_STEP, dtype)[sel[n]], sel[n], grids, sel, ncu);
+                levels[{dtype, sel[n]}] = rf_batch_levels(variants(KL_KERNEL_STEP, dtype)[sel[n]], sel[n], grids, sel,
+                                                          ncu, slots(variants(KL_KERNEL_STEP, dtype)[sel[n]]));
         }
         for (size_t n = 0; n < act.size(); ++n) {
             const Req &q = *act[n];
@@ -294,6 +302,8 @@ struct GpuExec {
                              });
             auto &tl = groups[kv.first];
             for (const auto &t : kv.second) tl.push_back(t.second);
+            const Variant &v = variants(KL_KERNEL_STEP, std::get<0>(kv.first))[std::get<1>(kv.first)];
+            spread_tiles(v, slots(v), tl);
         }
         // pack tables: [desc f32][desc f64][group tiles...]
         size_t off = 0;
@@ -317,15 +327,14 @@ struct GpuExec {
         }
         if ((e = hipMemcpyAsync(d, h, off, hipMemcpyHostToDevice, stream)) != hipSuccess) return hip_fail(e, "tables");
         const size_t o_desc[2] = {o_df, o_dd};
+        const bool cached = batch_cached(grids);
         size_t gi = 0;
         for (auto &kv : groups) {
             const int dt = std::get<0>(kv.first), vi = std::get<1>(kv.first);
             const Variant &v = variants(KL_KERNEL_STEP, dt)[vi];
             const int nt = (int)kv.second.size();
-            auto oc = occ.find(&v);
-            if (oc == occ.end()) oc = occ.emplace(&v, v.occupancy()).first;
-            const int nb = persistent_blocks(nt, ncu, oc->second);
-            if ((e = v.batch(d + o_desc[dt], d + o_g[gi], nt, nb, d_queue, stream)) != hipSuccess)
+            const int nb = persistent_blocks(nt, slots(v));
+            if ((e = v.persistent(false, cached)(d + o_desc[dt], d + o_g[gi], nt, nb, d_queue, stream)) != hipSuccess)
                 return hip_fail(e, v.name);
             ++*launches;
             ++gi;

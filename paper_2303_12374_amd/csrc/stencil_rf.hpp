@@ -26,8 +26,9 @@
 // and 52 KB of LDS, two or three per CU.  Measured against the fastest of the
 // other tiles (us): advec_u 301x203x151 FP32 65 -> 32, FP64 133 -> 66;
 // diff_uvw 320x320x160 FP32 151 -> 94, 301x203x151 FP64 268 -> 113; fused pass
-// 128^3 FP64 32 -> 28; fused step 128^3 FP32 21 -> 16, 256^3 97 -> 90.  Rows of
-// 640 points and more are left to the other tiles, which split them in x.
+// 128^3 FP64 32 -> 29; fused step, two buffers in turn, 128^3 FP32 23 -> 17, 256^3
+// 102 -> 99.  Rows of more than 256 chunks are left to the other tiles, which split
+// them in x, and some shorter ones (unrecorded_variant in api.cpp).
 //
 // The per-point functions are those of stencil.hpp: results are bitwise those
 // of every other configuration.
@@ -345,13 +346,17 @@ __global__ __launch_bounds__(THREADS, 2) void rf_kernel(StencilArgs<T> a)
     rf_tile<T, V, MODE, NT>(a, (int)(b - tz * (unsigned)a.nby), (int)tz, reinterpret_cast<T *>(rf_lds));
 }
 
-// Persistent form: tile = (grid, -, ty, tz).
+// Persistent form: tile = (grid, -, ty, tz).  A block's first tile takes no ticket,
+// which on small grids is a good part of the walk (64 grids of 16^3 FP32 24 -> 20
+// us) and puts the tiles where the list says (spread_tiles).  The z-march tiles draw
+// it: their lists keep neighbours together, and blocks do not start in order (256^3
+// FP32 fused pass drawn 109, not drawn 117).
 template <typename T, int V, int MODE, int NT, int THREADS>
 __global__ __launch_bounds__(THREADS, 2) void rf_batch(const StencilArgs<T> *__restrict__ grids,
                                                        const int4 *__restrict__ tiles, int ntiles, int *queue)
 {
     extern __shared__ __align__(16) unsigned char rf_lds[];
-    for (int n = next_tile(queue, -1); n < ntiles; n = next_tile(queue, n)) {
+    for (int n = next_tile<true>(queue, -1); n < ntiles; n = next_tile<true>(queue, n)) {
         const int4 tl = tiles[n];
         const StencilArgs<T> a = global_args(grids[tl.x]);
         rf_tile<T, V, MODE, NT, (MODE & RF_STEP) == 0>(a, tl.z, tl.w, reinterpret_cast<T *>(rf_lds));

@@ -404,15 +404,18 @@ __global__ __launch_bounds__(64 * BY, WPE) void advec_u_zl(StencilArgs<T> a)
 // the first).  Without a queue the assignment is static: block b takes tiles
 // b, b + gridDim.x, ...  With a queue (two device ints, both 0 at launch)
 // one lane draws the next ticket from queue[0], so blocks that finish their
-// tiles early take more and the walk ends with the blocks about level.
+// tiles early take more and the walk ends with the blocks about level; with FIRST
+// block b starts with tile b and draws from then on.
 // Every tile is computed once, by one block, with the same arithmetic, so
 // the results do not depend on which block takes which tile.
+template <bool FIRST = false>
 __device__ __forceinline__ int next_tile(int *queue, int prev)
 {
-    if (!queue) return prev < 0 ? (int)blockIdx.x : prev + (int)gridDim.x;
+    if (prev < 0 && (FIRST || !queue)) return (int)blockIdx.x;
+    if (!queue) return prev + (int)gridDim.x;
     __shared__ int ticket;
     __syncthreads();  // every wave has read the previous ticket
-    if (threadIdx.x == 0 && threadIdx.y == 0) ticket = atomicAdd(queue, 1);
+    if (threadIdx.x == 0 && threadIdx.y == 0) ticket = (FIRST ? (int)gridDim.x : 0) + atomicAdd(queue, 1);
     __syncthreads();
     return ticket;
 }

@@ -201,10 +201,10 @@ hipError_t launch_rf(const HostArgs &h, hipStream_t s)
     return hipGetLastError();
 }
 
-template <typename T, int V, int MODE, int THREADS>
+template <typename T, int V, int MODE, int THREADS, int NT = 1>
 hipError_t launch_rf_batch(const void *descs, const void *tiles, int ntiles, int nblocks, int *queue, hipStream_t s)
 {
-    hipLaunchKernelGGL((rf_batch<T, V, MODE, 1, THREADS>), dim3(nblocks), dim3(THREADS),
+    hipLaunchKernelGGL((rf_batch<T, V, MODE, NT, THREADS>), dim3(nblocks), dim3(THREADS),
                        THREADS == 256 ? RF_LDS_256 : RF_LDS_512, s, (const StencilArgs<T> *)descs, (const int4 *)tiles,
                        ntiles, queue);
     return hipGetLastError();
@@ -529,7 +529,7 @@ hipError_t launch_smag_zl(const HostArgs &h, hipStream_t s)
     Variant{"rf_t" KL_STR(THREADS), KERN, DT, FAMILY_RF, V, THREADS, 1, 0, 0, &launch_rf<T, V, MODE, THREADS>, \
             &launch_rf_batch<T, V, MODE, THREADS>, &rf_batch_occupancy<T, V, MODE, THREADS>,                \
             &launch_rf<T, V, (MODE) | RF_FRESH, THREADS>, &launch_rf_batch<T, V, (MODE) | RF_FRESH, THREADS>, \
-            &rf_batch_occupancy<T, V, (MODE) | RF_FRESH, THREADS>}
+            &rf_batch_occupancy<T, V, (MODE) | RF_FRESH, THREADS>, &launch_rf_batch<T, V, MODE, THREADS, 0>}
 
 #define KL_RFL(T, DT, KERN, V)                                                                              \
     Variant{"rf_t512", KERN, DT, FAMILY_RF, V, 512, 1, 0, 0, &launch_les_rf<T, V, KERN>, nullptr, nullptr}
@@ -561,4 +561,5 @@ hipError_t launch_smag_zl(const HostArgs &h, hipStream_t s)
     Variant{"rf_t" KL_STR(THREADS), KL_KERNEL_STEP, DT, FAMILY_RF, V, THREADS, 1, 0, 0,                     \
             &launch_rf<T, V, RF_ADVEC | RF_DIFF | RF_STEP, THREADS>,                                        \
             &launch_rf_batch<T, V, RF_ADVEC | RF_DIFF | RF_STEP, THREADS>,                                  \
-            &rf_batch_occupancy<T, V, RF_ADVEC | RF_DIFF | RF_STEP, THREADS>}
+            &rf_batch_occupancy<T, V, RF_ADVEC | RF_DIFF | RF_STEP, THREADS>, nullptr, nullptr, nullptr,    \
+            &launch_rf_batch<T, V, RF_ADVEC | RF_DIFF | RF_STEP, THREADS, 0>}
