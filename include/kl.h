@@ -226,7 +226,7 @@ int kl_step(const kl_grid_t *g, double visc, double dt, void *u, void *v, void *
  * The arithmetic and its order are those of kl_step (tendencies
  * zeroed, advec_u, diff_uvw, forward Euler, ghost refill), so the result is
  * bitwise identical to kl_step's, while the kernel moves 6 values per point
- * instead of 26.  Inputs and outputs must not overlap; the outputs' padding
+ * where kl_step moves 15.  Inputs and outputs must not overlap; the outputs' padding
  * cells are not written.  Configuration from the wisdom file step.wisdom. */
 int kl_step_fused(const kl_grid_t *g, double visc, double dt, const void *u, const void *v, const void *w,
                   void *u_out, void *v_out, void *w_out, void *stream);
@@ -435,15 +435,18 @@ int kl_batch_create(const kl_grid_t *grids, void *const *fields, int32_t n, doub
 
 /* Steps of a batch's graph besides the tendencies (kl_batch_create_ex). */
 enum {
-    KL_BATCH_ZERO_TENDENCIES = 1u, /* ut, vt, wt := 0 before the tendencies (by the tendency kernels themselves) */
-    KL_BATCH_FILL_GHOSTS = 2u,     /* first: the ghost cells of u, v, w as kl_fill_ghosts (all grids, one kernel per dtype) */
+    KL_BATCH_ZERO_TENDENCIES = 1u, /* the tendencies start at 0 instead of ut, vt, wt as they are */
+    KL_BATCH_FILL_GHOSTS = 2u,     /* the ghost cells of u, v, w as kl_fill_ghosts: first, one kernel per dtype over all
+                                      grids; some x columns by the tendency kernels, which do not read them */
     KL_BATCH_SUMS = 4u             /* last: each grid's conservation sums as kl_reduce_fp64(what = 0) */
 };
 
 /* kl_batch_create with the graph's other steps chosen by `flags`
- * (KL_BATCH_*): [ghost fill] -> [tendencies := 0] -> the fused tendency
- * groups -> [conservation sums].  The ghost fill gives every grid's u, v, w
- * the same ghost values, bit for bit, as kl_fill_ghosts.  With
+ * (KL_BATCH_*): [ghost fill] -> the fused tendency groups, onto cleared
+ * tendencies or those that are there -> [conservation sums].  With
+ * KL_BATCH_FILL_GHOSTS every grid's u, v, w have the ghost values of
+ * kl_fill_ghosts after a replay, bit for bit, and the tendencies follow from
+ * them.  With
  * KL_BATCH_SUMS, `sums` is a device array of 3 doubles per grid (grid g at
  * sums[3g .. 3g+2]: sum ut*dz_k, sum vt*dz_k, sum wt*dzh_k), written by every
  * replay with the bits kl_reduce_fp64(what = 0) gives for that grid; the
