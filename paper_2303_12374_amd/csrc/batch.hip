@@ -375,7 +375,12 @@ int build(Batch &b, void *const *fields)
     if (e == hipSuccess) e = hipGetDeviceProperties(&prop, dev);
     if (e != hipSuccess) return hip_fail(e, "device properties");
     const int ncu = prop.multiProcessorCount;
-    auto slots = [&](const Variant &v) { return ncu * (b.zero ? v.occupancy_fresh() : v.occupancy()); };
+    std::map<const Variant *, int> occ;  // blocks that run at a time
+    auto slots = [&](const Variant &v) {
+        auto oc = occ.find(&v);
+        if (oc == occ.end()) oc = occ.emplace(&v, ncu * (b.zero ? v.occupancy_fresh() : v.occupancy())).first;
+        return oc->second;
+    };
 
     // groups
     std::map<std::tuple<int, int, int>, size_t> gidx;
