@@ -11,6 +11,7 @@
 #include <mutex>
 #include <string>
 #include <tuple>
+#include <unordered_map>
 
 #include "kl_internal.hpp"
 
@@ -143,15 +144,23 @@ void clear_plans()
     g_plans.clear();
 }
 
-namespace {
 int variant_index(int kernel, int dtype, const std::string &name)
 {
-    const auto &vs = variants(kernel, dtype);
-    for (size_t n = 0; n < vs.size(); ++n)
-        if (name == vs[n].name) return (int)n;
-    return -1;
+    using Names = std::unordered_map<std::string, int>;
+    static const std::vector<Names> names = [] {
+        std::vector<Names> all(2 * KL_NUM_KERNELS);
+        for (int n = 0; n < 2 * KL_NUM_KERNELS; ++n) {
+            const auto &vs = variants(n / 2, n % 2);
+            for (size_t i = 0; i < vs.size(); ++i) all[n].emplace(vs[i].name, (int)i);
+        }
+        return all;
+    }();
+    const Names &of = names[2 * kernel + dtype];
+    const auto it = of.find(name);
+    return it == of.end() ? -1 : it->second;
 }
 
+namespace {
 // Whether v takes rows of g's length at all; the layout and the pointers of a
 // call decide the rest (variant_eligible).
 bool takes_row_length(const Variant &v, const kl_grid_t *g)
@@ -266,8 +275,8 @@ int unrecorded_variant(const kl_grid_t *g, int kernel, const std::vector<SizeRec
     int near = 0, near_fixed = 0;
     double dist = INFINITY, dist_fixed = INFINITY;
     for (const SizeRecord &r : records) {
-        const int n = variant_index(kernel, g->dtype, r.variant);
-        if (n < 0 || !takes_row_length(vs[n], g) || !(r.size[0] > 0 && r.size[1] > 0 && r.size[2] > 0)) continue;
+        const int n = r.variant;
+        if (!takes_row_length(vs[n], g) || !(r.size[0] > 0 && r.size[1] > 0 && r.size[2] > 0)) continue;
         double d = 0;
         for (int a = 0; a < 3; ++a) d += log(r.size[a] / sizes[a]) * log(r.size[a] / sizes[a]);
         d = sqrt(d);

@@ -66,7 +66,10 @@ struct JParser {
                 }
                 ++p;
             } else {
-                out += *p++;
+                const char *q = p;
+                while (q < end && *q != '"' && *q != '\\') ++q;
+                out.append(p, q);
+                p = q;
             }
         }
         if (p >= end) return false;
@@ -80,6 +83,7 @@ struct JParser {
         if (p >= end) return false;
         if (*p == '{') {
             v.kind = JVal::OBJ;
+            v.obj.reserve(16);
             ++p;
             ws();
             if (p < end && *p == '}') {
@@ -147,11 +151,14 @@ struct JParser {
         }
         if (lit("null")) return true;
         char *q = nullptr;
-        std::string tmp(p, (size_t)std::min<ptrdiff_t>(end - p, 64));
-        v.num = strtod(tmp.c_str(), &q);
-        if (q == tmp.c_str()) return false;
+        char tmp[65];
+        const size_t n = (size_t)std::min<ptrdiff_t>(end - p, 64);
+        memcpy(tmp, p, n);
+        tmp[n] = 0;
+        v.num = strtod(tmp, &q);
+        if (q == tmp) return false;
         v.kind = JVal::NUM;
-        p += (q - tmp.c_str());
+        p += q - tmp;
         return true;
     }
 };

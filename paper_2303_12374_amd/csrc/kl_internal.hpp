@@ -165,8 +165,10 @@ const char *kernel_name(int kernel);
 // size; *records (if not null): the records the choice was made from, in file order.
 struct SizeRecord {
     double size[3];
-    std::string variant;
+    int variant;  // index
 };
+// Index of a configuration's name, -1 if there is none.
+int variant_index(int kernel, int dtype, const std::string &name);
 int wisdom_select(const std::string &dir, int kernel, int dtype, const DeviceIdent &dev, int itot, int jtot, int ktot,
                   std::string *variant, int *level, bool *same_size = nullptr,
                   std::vector<SizeRecord> *records = nullptr);

